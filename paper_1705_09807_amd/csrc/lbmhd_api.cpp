@@ -117,6 +117,19 @@ int check_ctx(const lbm_ctx* ctx, bool need_state) {
   return LBM_OK;
 }
 
+// Whether work on this stream is being recorded into a graph.  A recorded run of
+// n steps must leave the state in the buffer that n one-step sweeps leave it in,
+// so that an even number of steps can be replayed.
+bool capturing(hipStream_t st) {
+  if (!st) return false;  // the null stream cannot be captured
+  hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &s) != hipSuccess) {
+    (void)hipGetLastError();
+    return true;
+  }
+  return s != hipStreamCaptureStatusNone;
+}
+
 }  // namespace
 
 extern "C" {
@@ -221,12 +234,23 @@ int lbm_step(lbm_ctx* ctx, int64_t n) {
     if (e != hipSuccess) return hip_fail(e, "lbm_step");
     ctx->lag_ready = true;
   }
-  for (int64_t k = 0; k < n; ++k) {
-    const bool refresh = !ctx->corr_ready || ctx->t % ctx->corr_every == 0;
-    hipError_t e = lbm::launch_step(ctx->L, ctx->t, refresh);
+  const int most = n > 1 && !capturing(ctx->L.stream) ? lbm::multi_steps(ctx->L) : 1;
+  for (int64_t k = 0; k < n;) {
+    // as few sweeps as possible, of nearly equal numbers of steps
+    const int64_t left = n - k, sweeps = (left + most - 1) / most;
+    const int adv = int((left + sweeps - 1) / sweeps);
+    hipError_t e;
+    if (adv > 1) {
+      e = lbm::launch_steps(ctx->L, adv);
+    } else {
+      const bool refresh = !ctx->corr_ready || ctx->t % ctx->corr_every == 0;
+      e = lbm::launch_step(ctx->L, ctx->t, refresh);
+    }
     if (e != hipSuccess) return hip_fail(e, "lbm_step");
     ctx->corr_ready = ctx->L.learned;
-    ++ctx->t;
+    ctx->L.cur ^= 1;
+    ctx->t += adv;
+    k += adv;
   }
   return LBM_OK;
 }

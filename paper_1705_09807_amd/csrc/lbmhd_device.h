@@ -8,6 +8,10 @@
 
 namespace lbm {
 
+// a b + c with one rounding.
+__device__ __forceinline__ float fmadd(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double fmadd(double a, double b, double c) { return __builtin_fma(a, b, c); }
+
 // Subgrid terms of the filtered equilibria (Sec. 2.1 FilterExampleSmall with
 // density gradients dropped, Sec. 3).  g*_ab = D_b m_a, h*_ab = D_b B_a; with
 // k2 = closure_scale Delta^2 / 12:
@@ -29,20 +33,21 @@ struct Closure {
 template <typename C>
 __device__ __forceinline__ Closure<C> closure_terms(C gxx, C gxy, C gyx, C gyy, C hxx, C hxy, C hyx, C hyy,
                                                     C pxx_, C pxy_, C pyx_, C pyy_, C inv_rho, C k2) {
+#pragma clang fp contract(off)
   const C kr = k2 * inv_rho;
-  const C pxx = kr * (gxx * gxx + gxy * gxy);
-  const C pyy = kr * (gyx * gyx + gyy * gyy);
-  const C pxy = kr * (gxx * gyx + gxy * gyy);
-  const C qxx = k2 * (hxx * hxx + hxy * hxy);
-  const C qyy = k2 * (hyx * hyx + hyy * hyy);
-  const C qxy = k2 * (hxx * hyx + hxy * hyy);
-  const C rxy = kr * (gxx * pyx_ + gxy * pyy_);
-  const C ryx = kr * (gyx * pxx_ + gyy * pxy_);
+  const C pxx = fmadd(gxx, gxx, gxy * gxy);  // products over their common factors (k2 / rho, k2)
+  const C pyy = kr * fmadd(gyx, gyx, gyy * gyy);
+  const C pxy = fmadd(gxx, gyx, gxy * gyy);
+  const C qxx = fmadd(hxx, hxx, hxy * hxy);
+  const C qyy = k2 * fmadd(hyx, hyx, hyy * hyy);
+  const C qxy = k2 * fmadd(hxx, hyx, hxy * hyy);
+  const C rxy = fmadd(gxx, pyx_, gxy * pyy_);
+  const C ryx = kr * fmadd(gyx, pxx_, gyy * pxy_);
   Closure<C> c;
-  c.tau_xy = pxy - qxy;
-  c.tau_d = (pxx - pyy) - (qxx - qyy);
-  c.tau_s = pxx + pyy;
-  c.eps = rxy - ryx;
+  c.tau_xy = fmadd(kr, pxy, -qxy);
+  c.tau_d = fmadd(kr, pxx, -pyy) - fmadd(k2, qxx, -qyy);
+  c.tau_s = fmadd(kr, pxx, pyy);
+  c.eps = fmadd(kr, rxy, -ryx);
   return c;
 }
 
@@ -60,10 +65,11 @@ __device__ __forceinline__ Closure<C> closure_terms(C gxx, C gxy, C gyx, C gyy, 
 template <typename C>
 __device__ __forceinline__ Closure<C> closure_terms_full(const C gr[5][2], C mx, C my, C bx, C by, C inv_rho,
                                                          C k2) {
+#pragma clang fp contract(off)
   const C ax = gr[4][0] * inv_rho, ay = gr[4][1] * inv_rho;
-  return closure_terms(gr[0][0] - mx * ax, gr[0][1] - mx * ay, gr[1][0] - my * ax, gr[1][1] - my * ay,
-                       gr[2][0], gr[2][1], gr[3][0], gr[3][1],
-                       gr[2][0] - bx * ax, gr[2][1] - bx * ay, gr[3][0] - by * ax, gr[3][1] - by * ay, inv_rho, k2);
+  return closure_terms(fmadd(-mx, ax, gr[0][0]), fmadd(-mx, ay, gr[0][1]), fmadd(-my, ax, gr[1][0]),
+                       fmadd(-my, ay, gr[1][1]), gr[2][0], gr[2][1], gr[3][0], gr[3][1], fmadd(-bx, ax, gr[2][0]),
+                       fmadd(-bx, ay, gr[2][1]), fmadd(-by, ax, gr[3][0]), fmadd(-by, ay, gr[3][1]), inv_rho, k2);
 }
 
 // Discrete gradient from a 3x3 neighbourhood (value at offset (dx, dy)).
@@ -71,10 +77,11 @@ __device__ __forceinline__ Closure<C> closure_terms_full(const C gr[5][2], C mx,
 // symmetry), i.e. 3 sum_i w_i c_i a(x + c_i); central5: (a_E - a_W)/2.
 template <typename C, int STENCIL>
 __device__ __forceinline__ void grad3x3(C e, C w, C n, C s, C ne, C nw, C se, C sw, C& dx, C& dy) {
+#pragma clang fp contract(off)
   if ((STENCIL & 1) == LBM_STENCIL_ISO9) {  // the LOCAL variants use the same two stencils
     const C third = C(1.0 / 3.0), twelfth = C(1.0 / 12.0);
-    dx = (e - w) * third + ((ne + se) - (nw + sw)) * twelfth;
-    dy = (n - s) * third + ((ne + nw) - (se + sw)) * twelfth;
+    dx = fmadd(e - w, third, ((ne + se) - (nw + sw)) * twelfth);
+    dy = fmadd(n - s, third, ((ne + nw) - (se + sw)) * twelfth);
   } else {
     dx = (e - w) * C(0.5);
     dy = (n - s) * C(0.5);

@@ -32,6 +32,7 @@ struct Launch {
   double rho0 = 1;                // rest density subtracted from stored f (0 for FP64)
   double bref[2] = {0, 0};        // reference field subtracted from stored g (0 for FP64)
   void* state = nullptr;          // caller-owned population storage
+  int cur = 0;                    // fused schedule: buffer (0 or 1) that holds the current state
   void* work = nullptr;           // caller-owned work buffer
   size_t off_mb = 0;              // moment planes for the in-place closure sweep
                                   // (two sets for the lagged schedule, set t & 1
@@ -64,7 +65,12 @@ size_t work_layout(Launch& L);
 hipError_t launch_init_kh(const Launch& L, const lbm_kh_params& kh);
 hipError_t launch_init_sech2(const Launch& L, const lbm_sech2_params& jet);
 hipError_t launch_init_moments(const Launch& L, int64_t t, const double* mom);
-// State at time t -> t + 1; with the learned closure, corr_refresh = false
+// Fused schedule: the most timesteps one launch can advance (1: launch_step
+// only), and k > 1 steps in one launch, from buffer cur into the other one.
+int multi_steps(const Launch& L);
+hipError_t launch_steps(const Launch& L, int k);
+// State at time t -> t + 1 (fused schedule: from buffer cur into the other
+// one); with the learned closure, corr_refresh = false
 // reuses the correction planes of an earlier step instead of evaluating the
 // network on this state.
 hipError_t launch_step(const Launch& L, int64_t t, bool corr_refresh = true);

@@ -25,360 +25,22 @@
 //    read set of a cell equals its write set, so cells never race.  With the
 //    closure on, a moment sweep writes m and B to four planes first.
 //
-// All arithmetic that defines the method (moments, closure, collision,
-// equilibria) lives in the __device__ functions below and is shared by every
-// kernel, so both schedules compute identical values.
+// All arithmetic that defines the method (moments, closure, collision) lives
+// in the __device__ functions of lbmhd_cell.h and lbmhd_device.h and is shared
+// by every kernel, so all schedules compute identical values.
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
 #include <type_traits>
 
+#include "lbmhd_cell.h"
 #include "lbmhd_device.h"
 #include "lbmhd_internal.h"
 #include "lbmhd_learned.h"
 #include "lbmhd_mlp_device.h"
 
 namespace lbm {
-
-// ---------------------------------------------------------------------------
-// Lattice (Sec. 2): D2Q9 velocities; the vector distribution uses the first
-// QG of them: five (D2Q5, the default) or all nine (D2Q9, Sec. 2's own
-// lattice for g).  Population q: f_q (q < 9), g_x,q-9 (9 .. 8+QG),
-// g_y,q-9-QG (9+QG .. 8+2QG); NPOP = 9 + 2 QG populations per cell.
-// ---------------------------------------------------------------------------
-__host__ __device__ constexpr int cx9(int i) {
-  return (i == 1 || i == 5 || i == 8) ? 1 : ((i == 3 || i == 6 || i == 7) ? -1 : 0);
-}
-__host__ __device__ constexpr int cy9(int i) {
-  return (i == 2 || i == 5 || i == 6) ? 1 : ((i == 4 || i == 7 || i == 8) ? -1 : 0);
-}
-__host__ __device__ constexpr int opp9(int i) {
-  return i == 0 ? 0 : (i < 5 ? ((i + 1) % 4) + 1 : ((i - 3) % 4) + 5);
-}
-template <int QG> constexpr int kPop = 9 + 2 * QG;
-template <int QG = 5>
-__host__ __device__ constexpr int qbase(int q) { return q < 9 ? q : (q < 9 + QG ? q - 9 : q - 9 - QG); }
-template <int QG = 5>
-__host__ __device__ constexpr int qcx(int q) { return cx9(qbase<QG>(q)); }
-template <int QG = 5>
-__host__ __device__ constexpr int qcy(int q) { return cy9(qbase<QG>(q)); }
-template <int QG = 5>
-__host__ __device__ constexpr int qopp(int q) {
-  return q < 9 ? opp9(q) : (q < 9 + QG ? 9 + opp9(q - 9) : 9 + QG + opp9(q - 9 - QG));
-}
-// D2Q9 weights (rest deviation of f, and g on D2Q9) and D2Q5 weights of the
-// vector distribution.
-__host__ __device__ constexpr double w9(int i) { return i == 0 ? 4.0 / 9.0 : (i < 5 ? 1.0 / 9.0 : 1.0 / 36.0); }
-__host__ __device__ constexpr double w5(int i) { return i == 0 ? 1.0 / 3.0 : 1.0 / 6.0; }
-template <int QG>
-__host__ __device__ constexpr double wg(int i) { return QG == 5 ? w5(i) : w9(i); }
-
-static_assert(opp9(1) == 3 && opp9(2) == 4 && opp9(3) == 1 && opp9(4) == 2, "opposites");
-static_assert(opp9(5) == 7 && opp9(6) == 8 && opp9(7) == 5 && opp9(8) == 6, "opposites");
-static_assert(qcx(10) == 1 && qcy(16) == 1 && qopp(15) == 17, "vector planes");
-static_assert(qcx<9>(14) == 1 && qcy<9>(20) == 1 && qopp<9>(23) == 25 && qopp<9>(14) == 16, "D2Q9 vector planes");
-static_assert(kPop<5> == kQ, "D2Q5 population count");
-
-template <typename S> struct ComputeOf { using type = float; };
-template <> struct ComputeOf<double> { using type = double; };
-
-// Storage codecs.  FP64 and FP32 store values as they are.  The 16-bit
-// storage types hold the deviations (see below) for FP32 arithmetic: FP16
-// scaled by 2^8, which lifts the small deviations out of the FP16 subnormal
-// range (normal values start at 6.1e-5) while the largest ones (~0.1) stay
-// far below 65504; BF16 unscaled (it has the FP32 exponent range).  All
-// conversions round to nearest even.
-template <typename S> struct Codec {
-  static constexpr float kScale = 1.0f;
-};
-template <> struct Codec<_Float16> {
-  static constexpr float kScale = 256.0f;
-};
-template <typename C, typename S>
-__device__ __forceinline__ C decode(S v) {
-  if constexpr (sizeof(S) == 2)
-    return C(float(v) * (1.0f / Codec<S>::kScale));
-  else
-    return C(v);
-}
-template <typename S, typename C>
-__device__ __forceinline__ S encode(C v) {
-  if constexpr (sizeof(S) == 2)
-    return S(float(v) * Codec<S>::kScale);
-  else
-    return S(v);
-}
-
-__device__ __forceinline__ int wrap1(int v, int n) { return v < 0 ? v + n : (v >= n ? v - n : v); }
-
-// Rates in the compute type, with the 1/|row|^2 of T^-1 = T^T diag(1/|row|^2)
-// folded in: |row|^2 = 9, 6, 6, 4, 4, 12, 12, 180, 20 for M0..M8.
-template <typename C>
-struct Rates {
-  C s3q, s4q, s5q, s6q, s7q, s8q;
-  C sm, k2, rho0;
-  C bx0, by0;  // reference field of the stored g deviations
-};
-
-template <typename C>
-static Rates<C> make_rates(const Launch& L) {
-  Rates<C> r;
-  r.s3q = C(L.rate[3] / 4.0);
-  r.s4q = C(L.rate[4] / 4.0);
-  r.s5q = C(L.rate[5] / 12.0);
-  r.s6q = C(L.rate[6] / 12.0);
-  r.s7q = C(L.rate[7] / 180.0);
-  r.s8q = C(L.rate[8] / 20.0);
-  r.sm = C(L.sm);
-  r.k2 = C(L.k2);
-  r.rho0 = C(L.rho0);
-  r.bx0 = C(L.bref[0]);
-  r.by0 = C(L.bref[1]);
-  return r;
-}
-
-// ---------------------------------------------------------------------------
-// Per-cell arithmetic of the method
-// ---------------------------------------------------------------------------
-template <typename C>
-struct Mom {
-  C drho, mx, my, dbx, dby;  // rho - rho0, rho u, B - B_ref
-};
-
-// rho = sum f_i, rho u = sum c_i f_i, B = sum g_i (Sec. 2), from the stored
-// deviations f_i - w_i rho0 and g_i - w'_i B_ref (sum_i w_i = sum_i w'_i = 1,
-// sum_i w_i c_i = 0).  Fixed summation order: every kernel gets bit-identical
-// moments for a cell.
-template <int QG, typename C>
-__device__ __forceinline__ Mom<C> moments_of(const C* v) {
-  Mom<C> m;
-  m.drho = (((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]))) + v[8];
-  m.mx = ((v[1] - v[3]) + (v[5] - v[6])) + (v[8] - v[7]);
-  m.my = ((v[2] - v[4]) + (v[5] - v[7])) + (v[6] - v[8]);
-  if constexpr (QG == 5) {
-    m.dbx = ((v[9] + v[10]) + (v[11] + v[12])) + v[13];
-    m.dby = ((v[14] + v[15]) + (v[16] + v[17])) + v[18];
-  } else {
-    m.dbx = (((v[9] + v[10]) + (v[11] + v[12])) + ((v[13] + v[14]) + (v[15] + v[16]))) + v[17];
-    m.dby = (((v[18] + v[19]) + (v[20] + v[21])) + ((v[22] + v[23]) + (v[24] + v[25]))) + v[26];
-  }
-  return m;
-}
-
-template <typename C>
-__device__ __forceinline__ Mom<C> moments19(const C v[kQ]) {
-  return moments_of<5>(v);
-}
-
-// One collision of the 19 populations of a cell (Sec. 2, Sec. 3).
-//  f: the collision term of LBKinEqn with rate tensor s' = T^-1 S T, i.e.
-//     f* = f - T^-1 S (M - M_eq), M = T f, M_eq the filtered KinMomentEq table
-//     (rho u_x rho u_y / rho - B_x B_y + tau_xy, ...).  Conserved M0..M2 have
-//     rate 0, so only rows 3..8 are formed, and T^-1 = T^T diag(1/|row|^2).
-//     In deviation storage M(w rho0) = (rho0, 0, ..., 0, 5 rho0 / 3) shifts
-//     only M8's equilibrium.
-//  g: g* = g - s_m (g - g_eq), g_eq_i = w'_i (B + 3 [(c.u) B - (c.B) u]) on D2Q5
-//     or D2Q9, which is g_eq_ix = w'_i (B_x - 3 c_iy E), g_eq_iy = w'_i (B_y +
-//     3 c_ix E) with E = (m_x B_y - m_y B_x) / rho + eps.  On D2Q9 this is the
-//     moment-space SRT of MagTMatrix / MagMomentEq: with one rate for every
-//     moment, relaxing T_m g towards N^eq and mapping back is relaxing g
-//     towards T_m^-1 N^eq, the D2Q9 geq.
-template <int QG, typename C>
-__device__ __forceinline__ void collide_q(C* v, const Mom<C>& m, const Closure<C>& cl, const Rates<C>& r) {
-  const C rho = r.rho0 + m.drho;
-  const C ir = C(1) / rho;
-  const C mx = m.mx, my = m.my, bx = r.bx0 + m.dbx, by = r.by0 + m.dby;
-  // rows 3..8 of T applied to the stored deviations
-  const C d56 = v[5] - v[6], d78 = v[7] - v[8], d87 = v[8] - v[7];
-  const C s14 = (v[1] + v[2]) + (v[3] + v[4]);
-  const C s58 = (v[5] + v[6]) + (v[7] + v[8]);
-  const C M3 = d56 + d78;
-  const C M4 = (v[1] + v[3]) - (v[2] + v[4]);
-  const C M5 = C(2) * (v[3] - v[1]) + d56 + d87;
-  const C M6 = C(2) * (v[4] - v[2]) + (v[5] + v[6]) - (v[7] + v[8]);
-  const C M7 = C(4) * v[0] - C(5) * s14 + C(4) * s58;
-  const C M8 = C(4) * v[0] - s58;
-  // filtered equilibrium moments (deviation form for M8)
-  const C q2 = (mx * mx + my * my) * ir;
-  const C e3 = mx * my * ir - bx * by + cl.tau_xy;
-  const C e4 = (mx * mx - my * my) * ir - (bx * bx - by * by) + cl.tau_d;
-  const C e7 = C(-3) * q2 - C(3) * cl.tau_s;
-  const C e8 = C(5.0 / 3.0) * m.drho + e7;
-  const C d3 = r.s3q * (M3 - e3);
-  const C d4 = r.s4q * (M4 - e4);
-  const C d5 = r.s5q * (M5 + mx);
-  const C d6 = r.s6q * (M6 + my);
-  const C d7 = r.s7q * (M7 - e7);
-  const C d8 = r.s8q * (M8 - e8);
-  const C g7 = C(5) * d7, h = C(4) * d7 - d8;
-  v[0] -= C(4) * (d7 + d8);
-  v[1] -= (d4 - C(2) * d5) - g7;
-  v[2] -= (-d4 - C(2) * d6) - g7;
-  v[3] -= (d4 + C(2) * d5) - g7;
-  v[4] -= (C(2) * d6 - d4) - g7;
-  v[5] -= (d3 + d5 + d6) + h;
-  v[6] -= (d6 - d3 - d5) + h;
-  v[7] -= (d3 - d5 - d6) + h;
-  v[8] -= (d5 - d3 - d6) + h;
-  // vector distribution, SRT; the w'_i B_ref part of the stored deviation
-  // cancels against that of g_eq
-  const C E = (mx * by - my * bx) * ir + cl.eps;
-  const C E3 = C(3) * E;
-#pragma unroll
-  for (int i = 0; i < QG; ++i) {
-    const C wi = C(wg<QG>(i));
-    const C gx = wi * (m.dbx - C(cy9(i)) * E3);
-    const C gy = wi * (m.dby + C(cx9(i)) * E3);
-    v[9 + i] -= r.sm * (v[9 + i] - gx);
-    v[9 + QG + i] -= r.sm * (v[9 + QG + i] - gy);
-  }
-}
-
-template <typename C>
-__device__ __forceinline__ void collide19(C v[kQ], const Mom<C>& m, const Closure<C>& cl, const Rates<C>& r) {
-  collide_q<5>(v, m, cl, r);
-}
-
-// Closure gradients from local non-equilibrium moments (LOCAL stencils),
-// with the stencil vorticity wm = D_x m_y - D_y m_x.  First-order
-// Chapman-Enskog of the pre-collision populations: M3 - M3^eq =
-// -(2 rho / (3 s3)) S_xy, M4 - M4^eq = -(2 rho / (3 s4)) (S_xx - S_yy) with the
-// unfiltered equilibria, S_xx = -S_yy (incompressible), D m = rho D u; and
-// D_b B_a = -3 s_m (Lam_ba - Lam^eq_ba), Lam_ba = sum_i c_ib g_ia, Lam^eq_xy =
-// E, Lam^eq_yx = -E.  The stored deviations have the same M3, M4 and Lam
-// (the rest state has none).  gr[k] = (D_x, D_y) of m_x, m_y, B_x, B_y.
-template <typename C>
-__device__ __forceinline__ void local_gradients(const C v[kQ], const Mom<C>& m, const Rates<C>& r, C wm,
-                                                C gr[4][2]) {
-  // evaluated as written (no contraction into FMAs), so every copy of an
-  // unrolled row body gives the same bits
-#pragma clang fp contract(off)
-  const C rho = r.rho0 + m.drho;
-  const C ir = C(1) / rho;
-  const C bx = r.bx0 + m.dbx, by = r.by0 + m.dby;
-  const C M3 = (v[5] - v[6]) + (v[7] - v[8]);
-  const C M4 = (v[1] + v[3]) - (v[2] + v[4]);
-  const C e3 = m.mx * m.my * ir - bx * by;
-  const C e4 = (m.mx * m.mx - m.my * m.my) * ir - (bx * bx - by * by);
-  // rho S: s3 = 4 s3q and s4 = 4 s4q exactly
-  const C rsxy = C(-6) * r.s3q * (M3 - e3);
-  const C rsxx = C(-3) * r.s4q * (M4 - e4);
-  gr[0][0] = rsxx;
-  gr[0][1] = rsxy - C(0.5) * wm;
-  gr[1][0] = rsxy + C(0.5) * wm;
-  gr[1][1] = -rsxx;
-  const C E = (m.mx * by - m.my * bx) * ir;
-  const C k = C(-3) * r.sm;
-  gr[2][0] = k * (v[10] - v[12]);
-  gr[2][1] = k * ((v[11] - v[13]) + E);
-  gr[3][0] = k * ((v[15] - v[17]) - E);
-  gr[3][1] = k * (v[16] - v[18]);
-}
-
-// ---------------------------------------------------------------------------
-// Fused schedule (two buffers, pull streaming).  A buffer holds the
-// post-collision populations of the previous step at their source cell, so
-// the state at time t is f_q(x) = buf[q][x - c_q]: every sweep gathers with
-// loads shifted by at most one cell and stores aligned, coalesced rows.
-// ---------------------------------------------------------------------------
-
-// Two consecutive stored values (one aligned load or store).
-template <typename S> using Vec2 = S __attribute__((ext_vector_type(2)));
-typedef unsigned u32x2_t __attribute__((ext_vector_type(2)));
-typedef unsigned u32x4_t __attribute__((ext_vector_type(4)));
-
-// Addressing.  A buffer is ny lattice rows, each holding the NPOP population
-// rows of that lattice row one after another, `pitch` elements apart:
-// element (q, x, y) at (y * NPOP + q) * pitch + x.  Keeping the populations
-// of a lattice row together means the workgroups that run at the same time
-// read and write a few contiguous stretches of memory instead of one stretch
-// per population plane.  An access is a wave-uniform row base (the lattice
-// row's offset, 64-bit, plus q * pitch, in scalar registers) plus a 32-bit
-// byte offset of the column, the scalar-base + vector-offset form of global
-// loads and stores.
-template <typename S>
-__device__ __forceinline__ const S* at(const S* __restrict__ base, int64_t row_off, uint32_t col_off) {
-  return reinterpret_cast<const S*>(reinterpret_cast<const char*>(base) + row_off + col_off);
-}
-template <typename S>
-__device__ __forceinline__ S* at(S* __restrict__ base, int64_t row_off, uint32_t col_off) {
-  return reinterpret_cast<S*>(reinterpret_cast<char*>(base) + row_off + col_off);
-}
-
-// Streaming store: non-temporal when the working set exceeds the caches.
-template <bool NT, typename T>
-__device__ __forceinline__ void store(T* p, T v) {
-  if (NT)
-    __builtin_nontemporal_store(v, p);
-  else
-    *p = v;
-}
-
-// Byte offsets of the lattice rows y - 1, y, y + 1 (periodic) and of the
-// columns x - 1, x, x + 1 of a cell.
-struct Rows {
-  int64_t s, c, n;
-};
-template <typename S, int QG = 5>
-__device__ __forceinline__ Rows rows_of(int y, int ny, int64_t pitch) {
-  const int64_t rb = int64_t(kPop<QG>) * pitch * int64_t(sizeof(S));
-  Rows r;
-  r.c = int64_t(y) * rb;
-  r.s = int64_t(y == 0 ? ny - 1 : y - 1) * rb;
-  r.n = int64_t(y + 1 == ny ? 0 : y + 1) * rb;
-  return r;
-}
-struct Cols {
-  uint32_t w, c, e;
-};
-template <typename S>
-__device__ __forceinline__ Cols cols_of(int x, int nx) {
-  Cols c;
-  c.c = uint32_t(x) * uint32_t(sizeof(S));
-  c.w = uint32_t(x == 0 ? nx - 1 : x - 1) * uint32_t(sizeof(S));
-  c.e = uint32_t(x + 1 == nx ? 0 : x + 1) * uint32_t(sizeof(S));
-  return c;
-}
-
-// f_q(x, y) = src[q][x - c_q][y - c_q] for one cell.
-template <typename S, typename C, int QG = 5>
-__device__ __forceinline__ void pull_cell(const S* __restrict__ src, int64_t pitch, const Rows& rw, const Cols& cl,
-                                          C* v) {
-#pragma unroll
-  for (int q = 0; q < kPop<QG>; ++q) {
-    const uint32_t xo = qcx<QG>(q) > 0 ? cl.w : (qcx<QG>(q) < 0 ? cl.e : cl.c);
-    const int64_t yo = qcy<QG>(q) > 0 ? rw.s : (qcy<QG>(q) < 0 ? rw.n : rw.c);
-    v[q] = decode<C>(*at(src + q * pitch, yo, xo));
-  }
-}
-
-// Two horizontally adjacent cells x, x + 1 (x even, nx even): the c_x = 0
-// populations come in one aligned two-element load.
-template <typename S, typename C, int QG = 5>
-__device__ __forceinline__ void pull_pair(const S* __restrict__ src, int64_t pitch, int nx, const Rows& rw, int x,
-                                          C* a, C* b) {
-  using V2 = Vec2<S>;
-  const uint32_t es = uint32_t(sizeof(S));
-  const uint32_t xw = uint32_t(x == 0 ? nx - 1 : x - 1) * es, x0 = uint32_t(x) * es, x1 = x0 + es;
-  const uint32_t x2 = uint32_t(x + 2 == nx ? 0 : x + 2) * es;
-#pragma unroll
-  for (int q = 0; q < kPop<QG>; ++q) {
-    const int64_t yo = qcy<QG>(q) > 0 ? rw.s : (qcy<QG>(q) < 0 ? rw.n : rw.c);
-    const S* pq = src + q * pitch;
-    if (qcx<QG>(q) == 0) {
-      const V2 t = *reinterpret_cast<const V2*>(at(pq, yo, x0));
-      a[q] = decode<C>(t.x);
-      b[q] = decode<C>(t.y);
-    } else if (qcx<QG>(q) > 0) {
-      a[q] = decode<C>(*at(pq, yo, xw));
-      b[q] = decode<C>(*at(pq, yo, x0));
-    } else {
-      a[q] = decode<C>(*at(pq, yo, x1));
-      b[q] = decode<C>(*at(pq, yo, x2));
-    }
-  }
-}
 
 // Closure off (Delta = 0).  One row segment of 2 * 128 cells per workgroup,
 // two cells per thread, aligned two-element stores.  Requires nx even.
@@ -397,11 +59,11 @@ k_fused_dns_pair(const S* __restrict__ src, S* __restrict__ dst, int nx, int ny,
   const Closure<C> cl = {C(0), C(0), C(0), C(0)};
   {
     const Mom<C> m = moments_of<QG>(a);
-    collide_q<QG>(a, m, cl, r);
+    collide_q<QG, false>(a, m, cl, r);
   }
   {
     const Mom<C> m = moments_of<QG>(b);
-    collide_q<QG>(b, m, cl, r);
+    collide_q<QG, false>(b, m, cl, r);
   }
   const uint32_t xo = uint32_t(x) * uint32_t(sizeof(S));
 #pragma unroll
@@ -413,7 +75,6 @@ k_fused_dns_pair(const S* __restrict__ src, S* __restrict__ dst, int nx, int ny,
   }
 }
 
-template <typename S> using Vec4 = S __attribute__((ext_vector_type(4)));
 
 // Closure off, any nx: one cell per thread, row segments of 256 cells.
 template <typename S, typename C, bool NT, int QG>
@@ -428,7 +89,7 @@ k_fused_dns(const S* __restrict__ src, S* __restrict__ dst, int nx, int ny, int6
   pull_cell<S, C, QG>(src, pitch, rw, cl, v);
   const Mom<C> m = moments_of<QG>(v);
   const Closure<C> zero = {C(0), C(0), C(0), C(0)};
-  collide_q<QG>(v, m, zero, r);
+  collide_q<QG, false>(v, m, zero, r);
 #pragma unroll
   for (int q = 0; q < kPop<QG>; ++q) store<NT>(at(dst + q * pitch, rw.c, cl.c), encode<S>(v[q]));
 }
@@ -449,7 +110,6 @@ k_fused_dns(const S* __restrict__ src, S* __restrict__ dst, int nx, int ny, int6
 // learned correction are added to the analytic subgrid terms of every cell.
 // MODE kClosureFull: the ring carries rho - rho0 as a fifth field and the
 // closure keeps the filtered-density gradient terms.
-enum { kClosurePlain = 0, kClosureCorr = 1, kClosureFull = 2 };
 
 template <typename S, typename C, int W, int STENCIL, bool NT, int MODE, int QG>
 __global__ void __launch_bounds__(W + 64)
@@ -541,7 +201,7 @@ k_fused_les(const S* __restrict__ src, S* __restrict__ dst, int nx, int ny, int6
           cl.tau_s += txx + tyy;
           cl.eps += eps;
         }
-        collide_q<QG>(cur, m, cl, r);
+        collide_q<QG, true>(cur, m, cl, r);
         const int64_t yo = int64_t(y) * int64_t(kPop<QG>) * pitch * int64_t(sizeof(S));
 #pragma unroll
         for (int q = 0; q < kPop<QG>; ++q) store<NT>(at(dst + q * pitch, yo, cx.c), encode<S>(cur[q]));
@@ -559,103 +219,6 @@ k_fused_les(const S* __restrict__ src, S* __restrict__ dst, int nx, int ny, int6
       }
     }
   }
-}
-
-// A cell's populations as stored (16-bit values decoded where they are used).
-template <typename S, int QG>
-struct RawCell {
-  S v[kPop<QG>];
-};
-template <typename S, typename C, int QG>
-__device__ __forceinline__ void decode_raw(const RawCell<S, QG>& c, C* v) {
-#pragma unroll
-  for (int q = 0; q < kPop<QG>; ++q) v[q] = decode<C>(c.v[q]);
-}
-
-// Buffer addressing of the wave-strip sweep: a buffer resource per lattice
-// row (its base held in scalar registers), the population's row offset as
-// the scalar offset and the column's byte offset as the per-lane offset, so a
-// load or store costs no per-lane address arithmetic.  Raw resources
-// (stride 0) of num_records = the lattice row's bytes; every access of a row
-// lies inside it, except the stores of lanes that own no output column,
-// which take an offset past num_records: the hardware's range check drops
-// them, so the row body has no branch around its stores.  (nx <= 32768, as
-// lbm_create requires, keeps a lattice row below 27 * 32768 * 4 B = 3.5 MB
-// and a row of input vectors at 512 KB, far below kDropOffset.)
-constexpr uint32_t kDropOffset = 0x80000000u;
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t row_rsrc(const void* base, uint32_t bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, int(bytes), 0x00020000);
-}
-template <typename S>
-__device__ __forceinline__ S buf_load(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
-  if constexpr (sizeof(S) == 2)
-    return __builtin_bit_cast(S, __builtin_amdgcn_raw_buffer_load_b16(r, int(voff), int(soff), 0));
-  else
-    return __builtin_bit_cast(S, __builtin_amdgcn_raw_buffer_load_b32(r, int(voff), int(soff), 0));
-}
-template <typename S, bool NT>
-__device__ __forceinline__ void buf_store(S v, __amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
-  constexpr int aux = NT ? 2 : 0;  // non-temporal
-  if constexpr (sizeof(S) == 2)
-    __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(unsigned short, v), r, int(voff), int(soff), aux);
-  else
-    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, int(voff), int(soff), aux);
-}
-
-// Buffer loads and stores of T (4, 8 or 16 bytes: one, two or four stored values).
-template <typename T>
-__device__ __forceinline__ T buf_load_v(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
-  if constexpr (sizeof(T) == 4)
-    return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(r, int(voff), int(soff), 0));
-  else if constexpr (sizeof(T) == 8)
-    return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(r, int(voff), int(soff), 0));
-  else
-    return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b128(r, int(voff), int(soff), 0));
-}
-template <typename T, bool NT>
-__device__ __forceinline__ void buf_store_v(T v, __amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
-  constexpr int aux = NT ? 2 : 0;
-  if constexpr (sizeof(T) == 4)
-    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, int(voff), int(soff), aux);
-  else if constexpr (sizeof(T) == 8)
-    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2_t, v), r, int(voff), int(soff), aux);
-  else
-    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, v), r, int(voff), int(soff), aux);
-}
-
-// f_q(x, y) = src[q][x - c_q][y - c_q] of one cell, as stored; ys, yc, yn
-// are the (periodic) rows y - 1, y, y + 1, pq the bytes between population
-// rows.
-template <typename S, int QG>
-__device__ __forceinline__ void pull_raw(const S* __restrict__ src, uint32_t pq, int ys, int yc, int yn,
-                                         const Cols& cl, RawCell<S, QG>& c) {
-  const uint32_t rowb = uint32_t(kPop<QG>) * pq;
-  const char* b = reinterpret_cast<const char*>(src);
-  const __amdgpu_buffer_rsrc_t rs = row_rsrc(b + int64_t(ys) * rowb, rowb);
-  const __amdgpu_buffer_rsrc_t rc = row_rsrc(b + int64_t(yc) * rowb, rowb);
-  const __amdgpu_buffer_rsrc_t rn = row_rsrc(b + int64_t(yn) * rowb, rowb);
-#pragma unroll
-  for (int q = 0; q < kPop<QG>; ++q) {
-    const uint32_t xo = qcx<QG>(q) > 0 ? cl.w : (qcx<QG>(q) < 0 ? cl.e : cl.c);
-    const __amdgpu_buffer_rsrc_t rr = qcy<QG>(q) > 0 ? rs : (qcy<QG>(q) < 0 ? rn : rc);
-    c.v[q] = buf_load<S>(rr, xo, uint32_t(q) * pq);
-  }
-}
-
-// Workgroups go to the XCDs in turn: workgroup b of a one-dimensional grid
-// runs on XCD b % 8.  xcd_contiguous renumbers the nb workgroups so that each
-// XCD takes one contiguous range of work items, so neighbouring row segments
-// (or strips) run side by side on one XCD and the cache lines at their common
-// edge, which both read, come from that XCD's L2 instead of two.  A bijection
-// of 0 .. nb-1 for any nb, so results do not depend on the XCD count of the
-// device or partition; only the cache benefit assumes eight.  Measured with the same results: the closure sweep
-// at 8192^2 FP32 1701-1750 against 1761-1782 us (its reads 1.03x instead of
-// 1.12x the algorithmic bytes at 4096^2), the 16-bit DNS sweep at 8192^2
-// 844-862 against 916-918 us (FP16); the FP32 pair kernel was 3 % slower with
-// it and keeps its two-dimensional grid.
-__device__ __forceinline__ int xcd_contiguous(int b, int nb) {
-  const int xcd = b & 7, k = b >> 3, q = nb >> 3, rm = nb & 7;
-  return xcd < rm ? xcd * (q + 1) + k : rm * (q + 1) + (xcd - rm) * q + k;
 }
 
 // Closure off, 16-bit storage, nx a multiple of 4: four cells per thread, so
@@ -711,7 +274,7 @@ k_fused_dns_quad(const S* __restrict__ src, S* __restrict__ dst, int nx, int ny,
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
     const Mom<C> m = moments19(v[k]);
-    collide19(v[k], m, cl, r);
+    collide19<false>(v[k], m, cl, r);
   }
   const __amdgpu_buffer_rsrc_t d = row_rsrc(reinterpret_cast<char*>(dst) + int64_t(y) * rowb, rowb);
 #pragma unroll
@@ -849,7 +412,7 @@ k_fused_les_f(const S* __restrict__ src, S* __restrict__ dst, int nx, int ny, in
       cl.tau_s += cc[0] + cc[2];
       cl.eps += cc[3];
     }
-    collide_q<QG>(cur, m, cl, r);
+    collide_q<QG, true>(cur, m, cl, r);
     const __amdgpu_buffer_rsrc_t d = row_rsrc(reinterpret_cast<char*>(dst) + int64_t(y) * rowb, rowb);
 #pragma unroll
     for (int q = 0; q < NP; ++q) buf_store<S, NT>(encode<S>(cur[q]), d, xo_store, uint32_t(q) * pq);
@@ -943,7 +506,7 @@ __global__ void __launch_bounds__(kAARow) k_aa_dns(S* __restrict__ A, int nx, in
   aa_load<S, C, ODD>(A, pitch, rw, cl, v);
   const Mom<C> m = moments19(v);
   const Closure<C> zero = {C(0), C(0), C(0), C(0)};
-  collide19(v, m, zero, r);
+  collide19<false>(v, m, zero, r);
   aa_store<S, C, ODD>(A, pitch, rw, cl, v);
 }
 
@@ -1019,7 +582,7 @@ k_aa_les(S* __restrict__ A, const C* __restrict__ mb, int nx, int ny, int64_t pi
   if constexpr (STENCIL >= LBM_STENCIL_LOCAL_ISO9) local_gradients(v, m, r, gr[1][0] - gr[0][1], gr);
   const Closure<C> cls = closure_terms(gr[0][0], gr[0][1], gr[1][0], gr[1][1], gr[2][0], gr[2][1], gr[3][0],
                                        gr[3][1], ir, r.k2);
-  collide19(v, m, cls, r);
+  collide19<true>(v, m, cls, r);
   aa_store<S, C, ODD>(A, pitch, rw, cl, v);
 }
 
@@ -1053,7 +616,7 @@ k_aa_les_lagged(S* __restrict__ A, const C* __restrict__ mb_prev, C* __restrict_
   const C ir = C(1) / (r.rho0 + m.drho);
   const Closure<C> cls = closure_terms(gr[0][0], gr[0][1], gr[1][0], gr[1][1], gr[2][0], gr[2][1], gr[3][0],
                                        gr[3][1], ir, r.k2);
-  collide19(v, m, cls, r);
+  collide19<true>(v, m, cls, r);
   aa_store<S, C, ODD>(A, pitch, rw, cl, v);
 }
 
@@ -1588,11 +1151,17 @@ static const dim3 kTile(64, 4);
 // aa_segment).
 static dim3 aa_grid(const Launch& L) { return dim3((L.nx + kAARow - 1) / kAARow * L.ny); }
 
+// The buffer that holds the current state (fused schedule: buffer L.cur), and
+// the one the next sweep of the fused schedule writes.
 template <typename S>
-static S* buffer_at(const Launch& L, int64_t t) {
+static S* buffer_index(const Launch& L, int b) {
   char* base = static_cast<char*>(L.state);
-  if (L.schedule == LBM_SCHED_FUSED && (t & 1)) base += buffer_offset_bytes(L.nx, L.ny, L.dtype, L.qg);
+  if (L.schedule == LBM_SCHED_FUSED && b) base += buffer_offset_bytes(L.nx, L.ny, L.dtype, L.qg);
   return reinterpret_cast<S*>(base);
+}
+template <typename S>
+static S* current_buffer(const Launch& L) {
+  return buffer_index<S>(L, L.cur);
 }
 
 static RestRef rest_ref(const Launch& L) { return RestRef{L.rho0, L.bref[0], L.bref[1]}; }
@@ -1730,18 +1299,18 @@ static hipError_t cell_inputs_typed(const Launch& L, int64_t t, CellIn* out) {
     const int ry = fused_rows(L.nx, L.ny, W, L.cus, 128);
     const dim3 g(((L.nx + W - 1) / W) * ((L.ny + ry - 1) / ry));  // numbered XCD-contiguously in the kernel
     if (W == 512)
-      hipLaunchKernelGGL((k_cell_inputs_f<S, 512>), g, dim3(512 + 64), 0, L.stream, buffer_at<S>(L, t), L.nx, L.ny,
+      hipLaunchKernelGGL((k_cell_inputs_f<S, 512>), g, dim3(512 + 64), 0, L.stream, current_buffer<S>(L), L.nx, L.ny,
                          L.pitch, ry, rest_ref(L), pk, out);
     else if (W == 256)
-      hipLaunchKernelGGL((k_cell_inputs_f<S, 256>), g, dim3(256 + 64), 0, L.stream, buffer_at<S>(L, t), L.nx, L.ny,
+      hipLaunchKernelGGL((k_cell_inputs_f<S, 256>), g, dim3(256 + 64), 0, L.stream, current_buffer<S>(L), L.nx, L.ny,
                          L.pitch, ry, rest_ref(L), pk, out);
     else
-      hipLaunchKernelGGL((k_cell_inputs_f<S, 64>), g, dim3(64 + 64), 0, L.stream, buffer_at<S>(L, t), L.nx, L.ny,
+      hipLaunchKernelGGL((k_cell_inputs_f<S, 64>), g, dim3(64 + 64), 0, L.stream, current_buffer<S>(L), L.nx, L.ny,
                          L.pitch, ry, rest_ref(L), pk, out);
   } else {
     const int strips = cell_input_strips(L.nx);
     hipLaunchKernelGGL((k_cell_inputs<S>), dim3((strips + 3) / 4, (L.ny + kCellInRows - 1) / kCellInRows),
-                       dim3(256), 0, L.stream, buffer_at<S>(L, t), L.nx, L.ny, L.pitch, rest_ref(L), strips, pk, out);
+                       dim3(256), 0, L.stream, current_buffer<S>(L), L.nx, L.ny, L.pitch, rest_ref(L), strips, pk, out);
   }
   return hipGetLastError();
 }
@@ -1776,8 +1345,8 @@ static hipError_t step_typed(const Launch& L, int64_t t, bool corr_refresh) {
   const dim3 grid = aa_grid(L);
   const bool les = L.k2 != 0.0;
   if (L.schedule == LBM_SCHED_FUSED) {
-    const S* src = buffer_at<S>(L, t);
-    S* dst = buffer_at<S>(L, t + 1);
+    const S* src = current_buffer<S>(L);
+    S* dst = buffer_index<S>(L, L.cur ^ 1);
     const float* corr = nullptr;
     if (L.learned) {
       float* c = reinterpret_cast<float*>(static_cast<char*>(L.work) + L.off_corr);
@@ -1877,7 +1446,7 @@ template <typename S>
 static hipError_t init_typed(const Launch& L, const lbm_kh_params& kh) {
   return by_lattice<S>(L, [&](auto qg) {
     hipLaunchKernelGGL((k_init_kh<S, decltype(qg)::value>), tile_grid(L.nx, L.ny), kTile, 0, L.stream,
-                       buffer_at<S>(L, 0), L.nx, L.ny, L.pitch, layout_at(L, 0), rest_ref(L), kh);
+                       current_buffer<S>(L), L.nx, L.ny, L.pitch, layout_at(L, 0), rest_ref(L), kh);
     return hipGetLastError();
   });
 }
@@ -1895,7 +1464,7 @@ template <typename S>
 static hipError_t init_sech2_typed(const Launch& L, const lbm_sech2_params& jet) {
   return by_lattice<S>(L, [&](auto qg) {
     hipLaunchKernelGGL((k_init_sech2<S, decltype(qg)::value>), tile_grid(L.nx, L.ny), kTile, 0, L.stream,
-                       buffer_at<S>(L, 0), L.nx, L.ny, L.pitch, layout_at(L, 0), rest_ref(L), jet);
+                       current_buffer<S>(L), L.nx, L.ny, L.pitch, layout_at(L, 0), rest_ref(L), jet);
     return hipGetLastError();
   });
 }
@@ -1913,7 +1482,7 @@ template <typename S>
 static hipError_t init_moments_typed(const Launch& L, int64_t t, const double* mom) {
   return by_lattice<S>(L, [&](auto qg) {
     hipLaunchKernelGGL((k_init_moments<S, decltype(qg)::value>), tile_grid(L.nx, L.ny), kTile, 0, L.stream,
-                       buffer_at<S>(L, t), mom, L.nx, L.ny, L.pitch, layout_at(L, t), rest_ref(L));
+                       current_buffer<S>(L), mom, L.nx, L.ny, L.pitch, layout_at(L, t), rest_ref(L));
     return hipGetLastError();
   });
 }
@@ -1931,7 +1500,7 @@ template <typename S>
 static hipError_t get_typed(const Launch& L, int64_t t, double* out) {
   return by_lattice<S>(L, [&](auto qg) {
     hipLaunchKernelGGL((k_get_state<S, decltype(qg)::value>), tile_grid(L.nx, L.ny), kTile, 0, L.stream,
-                       buffer_at<S>(L, t), out, L.nx, L.ny, L.pitch, layout_at(L, t), rest_ref(L));
+                       current_buffer<S>(L), out, L.nx, L.ny, L.pitch, layout_at(L, t), rest_ref(L));
     return hipGetLastError();
   });
 }
@@ -1949,7 +1518,7 @@ template <typename S>
 static hipError_t set_typed(const Launch& L, int64_t t, const double* in) {
   return by_lattice<S>(L, [&](auto qg) {
     hipLaunchKernelGGL((k_set_state<S, decltype(qg)::value>), tile_grid(L.nx, L.ny), kTile, 0, L.stream,
-                       buffer_at<S>(L, t), in, L.nx, L.ny, L.pitch, layout_at(L, t), rest_ref(L));
+                       current_buffer<S>(L), in, L.nx, L.ny, L.pitch, layout_at(L, t), rest_ref(L));
     return hipGetLastError();
   });
 }
@@ -1967,7 +1536,7 @@ template <typename S>
 static hipError_t moments_typed(const Launch& L, int64_t t, double* out, bool mark) {
   return by_lattice<S>(L, [&](auto qg) {
     hipLaunchKernelGGL((k_moments_out<S, decltype(qg)::value>), dim3((L.nx + 255) / 256, L.ny), dim3(256), 0,
-                       L.stream, buffer_at<S>(L, t), out, L.nx, L.ny, L.pitch, layout_at(L, t), rest_ref(L), mark);
+                       L.stream, current_buffer<S>(L), out, L.nx, L.ny, L.pitch, layout_at(L, t), rest_ref(L), mark);
     return hipGetLastError();
   });
 }

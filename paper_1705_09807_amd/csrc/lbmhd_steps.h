@@ -1,0 +1,322 @@
+// Sweeps that advance the fused schedule by several timesteps per launch
+// (temporal blocking).
+//
+// A one-step sweep moves every population through HBM once per step and is
+// bound by that: at 4096^2 FP32 its loads and stores alone take as long as the
+// whole sweep (410 us closure off, 440 us on), while its arithmetic needs a
+// fifth of the time.  The sweep here keeps the states between the steps on the
+// chip: a workgroup marches up a column strip with one group of waves per step;
+// each group collides a row a few rows behind the group before it and hands the
+// post-collision populations on through LDS, so HBM sees one read and one write
+// of the state per K steps.  Step s of a strip is valid on one column less at
+// each side than step s - 1 (closure off), or two (one for the gradients, one for
+// the streaming), so T columns of a group give T - 2 H stored ones and the outer
+// H are recomputed by the neighbouring strip; likewise a segment of rows starts
+// H rows early and ends H rows late.
+//
+// Values handed on are rounded to the storage type exactly as a store and a load
+// would, and the arithmetic is the shared per-cell code, evaluated as written:
+// the results equal those of one-step sweeps bit for bit.
+//
+// Measured, us per step, one-step sweep -> K steps per launch: 4096^2 FP32
+// closure off 411 -> 140 (K = 4), on 442 -> 178 (K = 3); 8192^2 BF16 855 -> 368
+// and 940 -> 588; 4096^2 FP64 955 -> 341 and 873 -> 350; 1024^2 FP32 25.7 -> 11
+// and 27.7 -> 18; 4096^2 D2Q9 FP32 590 -> 240 and 627 -> 249.  What bounds it now:
+// at 4096^2 FP32 a launch moves its 2.55 GB at 4.6-4.9 TB/s with the closure and
+// the vector ALUs busy about half the time; 16-bit storage is bound by the vector
+// ALUs (8192^2 BF16: about 230 instructions a cell and step, 410 of the 588 us).
+// The same steps evaluated one after another by one group of waves (each lane
+// every step of its column) took 252 us at K = 2 and 224 at K = 3 (4096^2 FP32,
+// closure on): a wave's arithmetic, its LDS and its loads then wait on each other.
+#pragma once
+
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include <type_traits>
+
+#include "lbmhd_cell.h"
+#include "lbmhd_device.h"
+#include "lbmhd_internal.h"
+
+namespace lbm {
+
+// Most steps per launch: what the LDS holds in groups of 256 columns (FP64 with the
+// closure: 128, whose registers allow no more).
+constexpr int ms_most_steps(size_t bytes, bool les, int qg) {
+  if (bytes == 8) return qg == 9 ? 2 : 3;  // D2Q9 with the closure, three steps: registers spill (111 against 70 us)
+  return les || qg == 9 ? 3 : 4;
+}
+
+// Columns per group, columns stored per strip, rows per segment, workgroups.
+struct MsShape {
+  int lanes, w, ry, blocks;
+};
+MsShape ms_shape(const Launch& L, int halo, int max_lanes, int per_cu_lds);
+
+constexpr int kClosureOff = 3;           // k_steps: a mode of its own beside the closure variants
+
+// LDS rows that hand population q from one step to the next: a row written in
+// iteration j is read in j + 1 by the populations that move down, j + 2 by those
+// that stay in their row and j + 3 by those that move up, always before that
+// iteration's write.
+template <int QG>
+constexpr int ms_slots(int q) { return qcy<QG>(q) < 0 ? 1 : (qcy<QG>(q) == 0 ? 2 : 3); }
+template <int QG>
+constexpr int ms_row(int q) {
+  int k = 0;
+  for (int p = 0; p < q; ++p) k += ms_slots<QG>(p);
+  return k;
+}
+template <int QG>
+constexpr int kMsRows = ms_row<QG>(kPop<QG>);
+
+// LDS of k_steps for at most LN columns (and one pad column at each side).
+template <typename S, int MODE, int QG, int K, int LN>
+struct MsLds {
+  static constexpr int kMsStride = LN + 2;
+  using C = typename ComputeOf<S>::type;
+  static constexpr bool LES = MODE != kClosureOff, FULL = MODE == kClosureFull;
+  struct alignas(4 * sizeof(C)) Quad {
+    C v[4];
+  };
+  Quad mom[LES ? K : 1][LES ? 3 : 1][LES ? kMsStride : 1];  // m, B - B_ref by step, row slot, lane + 1
+  C rho[FULL ? K : 1][FULL ? 3 : 1][FULL ? kMsStride : 1];
+  S pop[K - 1][kMsRows<QG>][kMsStride];                     // handed-on populations
+};
+
+// K steps per launch.  A workgroup holds K groups of T = blockDim / K lanes, one
+// per step, and marches up the rows of its strip; the lanes of a group own the
+// same columns.  In iteration i
+//  first half:  group 0 has row i (loaded an iteration earlier), group s > 0
+//               gathers row i - LAG s of its step from the populations that
+//               group s - 1 handed on; with the closure each puts the row's
+//               moments into its ring (three row slots);
+//  second half: each group collides that row (closure off), or the row before it
+//               with the gradients from its ring, and hands it on or, in the
+//               last group, stores it.
+// A barrier after each half.  One wave of every group runs on every SIMD, so
+// while one waits for its loads, LDS or the barrier's slowest wave the others'
+// arithmetic fills in; a group needs the registers of a single step.
+template <typename S, int STENCIL, int MODE, int QG, int K, int LN>
+__global__ void __launch_bounds__(LN* K)
+k_steps(const S* __restrict__ src, S* __restrict__ dst, int nx, int ny, int64_t pitch, int w, int ry,
+        Rates<typename ComputeOf<S>::type> r) {
+  using C = typename ComputeOf<S>::type;
+  using Lds = MsLds<S, MODE, QG, K, LN>;
+  using Quad = typename Lds::Quad;
+  constexpr bool LES = Lds::LES;
+  constexpr int NP = kPop<QG>, NF = Lds::FULL ? 5 : 4;
+  constexpr int H = LES ? 2 * K - 1 : K - 1;  // recomputed columns at each side, rows at each end
+  constexpr int LAG = LES ? 3 : 2, COL = LES ? 1 : 0;
+  extern __shared__ __attribute__((aligned(16))) char ms_lds[];
+  Lds& lds = *reinterpret_cast<Lds*>(ms_lds);
+
+  const int T = blockDim.x / K;
+  const int step = __builtin_amdgcn_readfirstlane(threadIdx.x / T);
+  const int tid = threadIdx.x - step * T, l = tid + 1;
+  // numbered XCD-contiguously: the strips of a segment run side by side on one
+  // XCD and share the lines at their edges in its L2
+  const int nstrip = (nx + w - 1) / w;
+  const int vb = xcd_contiguous(blockIdx.x, gridDim.x);
+  const int x0 = (vb % nstrip) * w, x1 = min(x0 + w, nx);
+  const int y0 = (vb / nstrip) * ry, y1 = min(y0 + ry, ny);
+  const int first = y0 - H, last = y1 - 1 + H;  // rows of the first step's moments
+  const int end = y1 + LAG * (K - 1) + COL;     // iterations first .. end - 1
+  // columns of the lanes: x0 - H + tid, periodic; lanes past the right halo
+  // repeat its last column
+  int x = min(x0 - H + tid, x1 - 1 + H);
+  x = x < 0 ? x + nx : (x >= nx ? x - nx : x);
+  const Cols cx = cols_of<S>(x, nx);
+  const uint32_t pq = uint32_t(pitch) * uint32_t(sizeof(S));
+  auto wrapy = [&](int y) { return y < 0 ? y + ny : (y >= ny ? y - ny : y); };
+
+  auto put = [&](int s, int sl, const C* v) __attribute__((always_inline)) {
+    if constexpr (LES) {
+      const Mom<C> m = moments_of<QG>(v);
+      lds.mom[s][sl][l] = Quad{m.mx, m.my, m.dbx, m.dby};
+      if constexpr (NF == 5) lds.rho[s][sl][l] = m.drho;
+    }
+  };
+  // collision of a cell whose row sits in slot sc of step s's ring, its southern
+  // and northern neighbours' rows in ss and sn
+  auto collide = [&](int s, int ss, int sc, int sn, C* v) __attribute__((always_inline)) {
+    const Mom<C> m = moments_of<QG>(v);
+    Closure<C> cl = {C(0), C(0), C(0), C(0)};
+    if constexpr (LES) {
+      const auto& q = lds.mom[s];
+      const Quad e = q[sc][l + 1], o = q[sc][l - 1], n = q[sn][l], so = q[ss][l], ne = q[sn][l + 1],
+                 nw = q[sn][l - 1], se = q[ss][l + 1], sw = q[ss][l - 1];
+      C gr[NF][2];
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        grad3x3<C, STENCIL>(e.v[k], o.v[k], n.v[k], so.v[k], ne.v[k], nw.v[k], se.v[k], sw.v[k], gr[k][0], gr[k][1]);
+      const C ir = C(1) / (r.rho0 + m.drho);
+      if constexpr (Lds::FULL) {
+        const auto& p = lds.rho[s];
+        grad3x3<C, STENCIL>(p[sc][l + 1], p[sc][l - 1], p[sn][l], p[ss][l], p[sn][l + 1], p[sn][l - 1], p[ss][l + 1],
+                            p[ss][l - 1], gr[4][0], gr[4][1]);
+        cl = closure_terms_full(gr, m.mx, m.my, r.bx0 + m.dbx, r.by0 + m.dby, ir, r.k2);
+      } else {
+        if constexpr (STENCIL >= LBM_STENCIL_LOCAL_ISO9 && QG == 5)
+          local_gradients(v, m, r, gr[1][0] - gr[0][1], gr);
+        cl = closure_terms(gr[0][0], gr[0][1], gr[1][0], gr[1][1], gr[2][0], gr[2][1], gr[3][0], gr[3][1], ir, r.k2);
+      }
+    }
+    collide_q<QG, LES>(v, m, cl, r);
+  };
+  // parity of the iteration: which of two slots
+  auto hand_on = [&](int s, int u, int par, const C* v) __attribute__((always_inline)) {
+#pragma unroll
+    for (int q = 0; q < NP; ++q) {
+      const int sl = qcy<QG>(q) > 0 ? u : (qcy<QG>(q) == 0 ? par : 0);
+      lds.pop[s][ms_row<QG>(q) + sl][l] = encode<S>(v[q]);
+    }
+  };
+  auto gather = [&](int s, int u, int par, C* v) __attribute__((always_inline)) {
+#pragma unroll
+    for (int q = 0; q < NP; ++q) {
+      const int sl = qcy<QG>(q) > 0 ? u : (qcy<QG>(q) == 0 ? par : 0);
+      v[q] = decode<C>(lds.pop[s - 1][ms_row<QG>(q) + sl][l - qcx<QG>(q)]);
+    }
+  };
+  using N0 = std::integral_constant<int, 0>;
+  using N1 = std::integral_constant<int, 1>;
+  using N2 = std::integral_constant<int, 2>;
+
+  if (step == 0) {
+    RawCell<S, QG> raw[3];
+    auto pull = [&](int row, RawCell<S, QG>& c) __attribute__((always_inline)) {
+      const int y = min(row, last);
+      pull_raw<S, QG>(src, pq, wrapy(y - 1), wrapy(y), wrapy(y + 1), cx, c);
+    };
+    auto iter = [&](int i, int par, auto uc) __attribute__((always_inline)) {
+      constexpr int u0 = decltype(uc)::value, u1 = (u0 + 2) % 3, u2 = (u0 + 1) % 3;  // rows i, i - 1, i - 2
+      pull(i + 1, raw[u2]);
+      __builtin_amdgcn_sched_barrier(0);
+      C v[NP];
+      if constexpr (LES) {
+        decode_raw<S, C, QG>(raw[u0], v);
+        put(0, u0, v);
+      }
+      __syncthreads();
+      decode_raw<S, C, QG>(raw[LES ? u1 : u0], v);
+      collide(0, u2, u1, u0, v);
+      hand_on(0, u0, par, v);
+      __syncthreads();
+    };
+    pull(first, raw[0]);
+    for (int i = first, par = 0; i < end; i += 3, par ^= 1) {  // past `end`: nothing is stored
+      iter(i, par, N0{});
+      iter(i + 1, par ^ 1, N1{});
+      iter(i + 2, par, N2{});
+    }
+  } else {
+    // s > 0; the last group stores
+    const int s = step;
+    C vs[3][NP];  // rows gathered and not yet collided
+    const bool owner = tid >= H && tid < H + (x1 - x0);
+    auto iter = [&](int i, int par, auto uc, auto sc) __attribute__((always_inline)) {
+      constexpr int u0 = decltype(uc)::value, u1 = (u0 + 2) % 3, u2 = (u0 + 1) % 3, st = decltype(sc)::value;
+      gather(st, u0, par, vs[u0]);
+      put(st, u0, vs[u0]);
+      __syncthreads();
+      C v[NP];
+#pragma unroll
+      for (int q = 0; q < NP; ++q) v[q] = vs[LES ? u1 : u0][q];
+      collide(st, u2, u1, u0, v);
+      if constexpr (st + 1 < K) {
+        hand_on(st, u0, par, v);
+      } else {
+        const int y = i - LAG * st - COL;
+        const bool mine = y >= y0 && y < y1;
+        const uint32_t rowb = uint32_t(NP) * pq;
+        const __amdgpu_buffer_rsrc_t d =
+            row_rsrc(reinterpret_cast<char*>(dst) + int64_t(mine ? y : y0) * rowb, rowb);
+        const uint32_t xo = owner && mine ? cx.c : kDropOffset;
+#pragma unroll
+        for (int q = 0; q < NP; ++q) buf_store<S, false>(encode<S>(v[q]), d, xo, uint32_t(q) * pq);
+      }
+      __syncthreads();
+    };
+    auto loop = [&](auto sc) __attribute__((always_inline)) {
+      for (int i = first, par = 0; i < end; i += 3, par ^= 1) {
+        iter(i, par, N0{}, sc);
+        iter(i + 1, par ^ 1, N1{}, sc);
+        iter(i + 2, par, N2{}, sc);
+      }
+    };
+    if (s == 1) loop(N1{});
+    if constexpr (K > 2) {
+      if (s == 2) loop(N2{});
+    }
+    if constexpr (K > 3) {
+      if (s == 3) loop(std::integral_constant<int, 3>{});
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Host side
+// ---------------------------------------------------------------------------
+template <typename S, int STENCIL, int MODE, int QG, int K, int LN>
+static hipError_t launch_k_steps(const Launch& L) {
+  using C = typename ComputeOf<S>::type;
+  using Lds = MsLds<S, MODE, QG, K, LN>;
+  static_assert(sizeof(Lds) <= 160 * 1024, "LDS of a compute unit");
+  const MsShape sh = ms_shape(L, MODE != kClosureOff ? 2 * K - 1 : K - 1, LN, 160 * 1024 / sizeof(Lds));
+  const auto kernel = &k_steps<S, STENCIL, MODE, QG, K, LN>;
+  if (sizeof(Lds) > 64 * 1024) {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(Lds));
+    if (e != hipSuccess) return e;
+  }
+  char* base = static_cast<char*>(L.state);
+  const size_t off = buffer_offset_bytes(L.nx, L.ny, L.dtype, L.qg);
+  hipLaunchKernelGGL(kernel, dim3(sh.blocks), dim3(sh.lanes * K), sizeof(Lds), L.stream,
+                     reinterpret_cast<const S*>(base + (L.cur ? off : 0)),
+                     reinterpret_cast<S*>(base + (L.cur ? 0 : off)), L.nx, L.ny, L.pitch, sh.w, sh.ry,
+                     make_rates<C>(L));
+  return hipGetLastError();
+}
+
+// The instance for this run's closure, stencil and k (2 .. ms_most_steps).
+template <typename S, int MODE, int QG, int K, int LN>
+static hipError_t launch_k_stencil(const Launch& L) {
+  if constexpr (MODE == kClosurePlain && QG == 5) {
+    if (L.stencil == LBM_STENCIL_LOCAL_ISO9) return launch_k_steps<S, LBM_STENCIL_LOCAL_ISO9, MODE, QG, K, LN>(L);
+    if (L.stencil == LBM_STENCIL_LOCAL_CENTRAL5)
+      return launch_k_steps<S, LBM_STENCIL_LOCAL_CENTRAL5, MODE, QG, K, LN>(L);
+  }
+  if constexpr (MODE != kClosureOff) {
+    if (L.stencil == LBM_STENCIL_CENTRAL5) return launch_k_steps<S, LBM_STENCIL_CENTRAL5, MODE, QG, K, LN>(L);
+  }
+  return launch_k_steps<S, LBM_STENCIL_ISO9, MODE, QG, K, LN>(L);
+}
+
+template <typename S, int MODE, int QG, int LN>
+static hipError_t launch_k(const Launch& L, int k) {
+  constexpr int most = ms_most_steps(sizeof(S), MODE != kClosureOff, QG);
+  if constexpr (most >= 4) {
+    if (k == 4) return launch_k_stencil<S, MODE, QG, 4, LN>(L);
+  }
+  if constexpr (most >= 3) {
+    if (k == 3) return launch_k_stencil<S, MODE, QG, 3, LN>(L);
+  }
+  return k == 2 ? launch_k_stencil<S, MODE, QG, 2, LN>(L) : hipErrorInvalidValue;
+}
+
+template <typename S>
+static hipError_t launch_steps_typed(const Launch& L, int k) {
+  constexpr int LN = sizeof(S) == 8 ? 128 : 256;  // closure on
+  if constexpr (sizeof(S) >= 4) {
+    if (L.qg == 9) {
+      if (L.k2 == 0.0) return launch_k<S, kClosureOff, 9, 256>(L, k);
+      return L.full ? launch_k<S, kClosureFull, 9, LN>(L, k) : launch_k<S, kClosurePlain, 9, LN>(L, k);
+    }
+  }
+  if (L.k2 == 0.0) return launch_k<S, kClosureOff, 5, 256>(L, k);
+  return L.full ? launch_k<S, kClosureFull, 5, LN>(L, k) : launch_k<S, kClosurePlain, 5, LN>(L, k);
+}
+
+}  // namespace lbm

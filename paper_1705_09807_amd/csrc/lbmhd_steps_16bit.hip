@@ -1,0 +1,80 @@
+// Multi-step sweeps (lbmhd_steps.h) for FP16 and BF16 storage, and their
+// dispatch.
+#include <algorithm>
+
+#include "lbmhd_steps.h"
+
+namespace lbm {
+
+// Measured on MI355X, 256^2 .. 8192^2, microseconds per step:
+//  * groups of 256 columns, of 128 with the closure off on small grids, where
+//    more and narrower strips fill the chip (512^2 FP32 5.4 against 7.2, 1024^2
+//    10.6 against 11.8, 2048^2 36.8 against 34.1);
+//  * one workgroup per compute unit: few, tall segments keep few rows of the
+//    state open and recompute least (4096^2 FP32 closure on 175 against 180 with
+//    two, 2048^2 51 against 59); two for 16-bit storage on tall segments, where
+//    the arithmetic of two hides each other's barriers (8192^2 BF16 588 against
+//    620, 4096^2 161 against 157);
+//  * on large grids strips of whole 64-byte sectors where that takes at most 1/32
+//    more strips (8192^2 FP32 closure off 503 against 544, on 665 against 708),
+//    with D2Q9, whose rows are longest, whole 128-byte lines for at most 1/8 more
+//    (4096^2 closure off 240 against 318, on 249 against 299); 16-bit storage is
+//    bound by its arithmetic and takes the fewest strips.
+MsShape ms_shape(const Launch& L, int halo, int max_lanes, int per_cu_lds) {
+  const int64_t cells = int64_t(L.nx) * L.ny;
+  const int bytes = int(storage_bytes(L.dtype));
+  MsShape s;
+  s.lanes = L.k2 == 0.0 && cells < 800000 ? 128 : max_lanes;
+  s.lanes = std::min(s.lanes, (L.nx + 2 * halo + 63) / 64 * 64);
+  const int most = s.lanes - 2 * halo;
+  int strips = (L.nx + most - 1) / most;
+  s.w = (L.nx + strips - 1) / strips;
+  if (bytes > 2 && cells >= (1 << 23)) {
+    const int unit = (L.qg == 9 ? 128 : 64) / bytes, part = L.qg == 9 ? 8 : 32;
+    const int up = (s.w + unit - 1) / unit * unit, w = up <= most ? up : most / unit * unit;
+    const int n = (L.nx + w - 1) / w;
+    if (part * n <= (part + 1) * strips) {
+      s.w = w;
+      strips = n;
+    }
+  }
+  int segs = std::max(1, L.cus / strips);
+  if (bytes == 2 && per_cu_lds > 1 && L.ny / segs >= 512) segs = std::max(1, 2 * L.cus / strips);
+  s.ry = (L.ny + segs - 1) / segs;
+  s.blocks = strips * ((L.ny + s.ry - 1) / s.ry);
+  return s;
+}
+
+// Grids below these sizes take one-step sweeps: the rows and columns that a
+// sweep of several steps recomputes, and its longer pipeline, then cost more than
+// the traffic it saves.  Measured (several steps against one): closure on, FP32
+// 512^2 12.1 against 9.7 us and 700^2 12.3 against 16.0; BF16 512^2 12.5 against
+// 9.6, 1024^2 19.1 against 19.5; FP64 two steps 128^2 7.1 against 7.8, three
+// steps 512^2 14.4 against 13.7 for two, 1024^2 30.3 against 37.8; closure off,
+// FP32 256^2 3.8 against 5.0 and 64^2 2.7 against 3.3, FP64 64^2 3.7 against 3.4,
+// 128^2 4.0 against 5.2, BF16 512^2 5.7 against 5.8.
+int multi_steps(const Launch& L) {
+  if (L.schedule != LBM_SCHED_FUSED || L.learned || L.nx < 16 || L.ny < 16) return 1;
+  const int64_t cells = int64_t(L.nx) * L.ny;
+  const size_t bytes = storage_bytes(L.dtype);
+  const bool les = L.k2 != 0.0;
+  const int most = ms_most_steps(bytes, les, L.qg);
+  if (bytes == 2) return cells >= (les ? 1000000 : 300000) ? most : 1;
+  if (!les) return bytes == 8 && cells < 10000 ? 1 : most;
+  if (bytes == 4) return cells >= 360000 ? most : 1;
+  return cells >= 400000 ? most : (cells >= 10000 ? 2 : 1);
+}
+
+hipError_t launch_steps_fp64(const Launch& L, int k);
+hipError_t launch_steps_fp32(const Launch& L, int k);
+
+hipError_t launch_steps(const Launch& L, int k) {
+  switch (L.dtype) {
+    case LBM_FP64: return launch_steps_fp64(L, k);
+    case LBM_FP32: return launch_steps_fp32(L, k);
+    case LBM_FP16: return launch_steps_typed<_Float16>(L, k);
+    default: return launch_steps_typed<__bf16>(L, k);
+  }
+}
+
+}  // namespace lbm

@@ -1,0 +1,117 @@
+"""Sweeps of several timesteps per launch against one-step sweeps.
+
+lbm_step(n) of the fused schedule takes several steps per launch where the grid
+is large enough; lbm_step(1) always takes the one-step sweep, which the oracle
+tests pin.  Both evaluate the same per-cell arithmetic as written and round the
+states between the steps to the storage type, so the states must be equal bit
+for bit (tolerance 0).
+"""
+
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+# (nx, ny, steps) by path: at the smallest grids of the path, on both sides of
+# strip and segment edges, ragged strips and segments, remainders of n
+SMALL = [(16, 16, 7), (17, 19, 4), (122, 21, 5), (123, 64, 6), (251, 300, 9)]
+FP64_LES = [(100, 100, 5), (118, 90, 4), (119, 257, 7), (700, 601, 6)]
+FP32_LES = [(600, 600, 5), (246, 1500, 4), (247, 1601, 7), (4900, 75, 3), (16, 22501, 2)]
+LOW_LES = [(1000, 1000, 5), (247, 4096, 4), (5000, 201, 3)]
+
+
+def _require_gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+
+
+def _start(nx, ny, **kw):
+    from paper_1705_09807_amd import Sim
+    s = Sim(nx=nx, ny=ny, nu=2e-3, eta=3e-3, s5=1.6, s6=1.4, s7=1.2, s8=1.7, b_ref=(0.01, 0.0), **kw)
+    g = torch.Generator(device="cuda").manual_seed(nx * 7 + ny)
+    m = 0.02 * (2 * torch.rand(5, ny, nx, generator=g, device="cuda", dtype=torch.float64) - 1)
+    m[0] += 1.0
+    m[3] += 0.01
+    s.init_from_moments(m)
+    return s
+
+
+def _check(nx, ny, n, **kw):
+    _require_gpu()
+    print("multistep", nx, ny, n, kw, flush=True)
+    a, b = _start(nx, ny, **kw), _start(nx, ny, **kw)
+    a.step(n)
+    for _ in range(n):
+        b.step(1)
+    x, y = a.get_state(), b.get_state()
+    assert torch.isfinite(y).all()
+    assert a.t == b.t == n
+    assert torch.equal(x, y)
+    assert torch.equal(a.moments(), b.moments())
+    # and on from there: the current buffer is tracked over odd and even sweeps
+    a.step(3)
+    for _ in range(3):
+        b.step(1)
+    assert torch.equal(a.get_state(), b.get_state())
+
+
+@pytest.mark.parametrize("dtype", ["fp64", "fp32", "fp16", "bf16"])
+@pytest.mark.parametrize("nx,ny,n", SMALL + [(600, 517, 11), (4100, 80, 13)])
+def test_closure_off(nx, ny, n, dtype):
+    _check(nx, ny, n, dtype=dtype, delta=0.0)
+
+
+@pytest.mark.parametrize("stencil", ["iso9", "central5", "local_iso9", "local_central5"])
+@pytest.mark.parametrize("dtype,nx,ny,n", [("fp64", *c) for c in FP64_LES] + [("fp32", *c) for c in FP32_LES]
+                         + [("fp16", *c) for c in LOW_LES] + [("bf16", *c) for c in LOW_LES])
+def test_closure_on(dtype, nx, ny, n, stencil):
+    _check(nx, ny, n, dtype=dtype, delta=4.0, grad_stencil=stencil)
+
+
+@pytest.mark.parametrize("stencil", ["iso9", "central5"])
+@pytest.mark.parametrize("mag", ["d2q5", "d2q9"])
+@pytest.mark.parametrize("dtype,nx,ny,n", [("fp64", 119, 257, 7), ("fp64", 700, 601, 5), ("fp32", 247, 1601, 7),
+                                           ("fp16", 247, 4096, 4)])
+def test_density_gradients(dtype, nx, ny, n, mag, stencil):
+    if mag == "d2q9" and dtype == "fp16":
+        pytest.skip("D2Q9 takes FP64 and FP32 storage")
+    _check(nx, ny, n, dtype=dtype, delta=3.0, grad_stencil=stencil, closure="full", mag_lattice=mag)
+
+
+@pytest.mark.parametrize("delta", [0.0, 3.0])
+@pytest.mark.parametrize("dtype,nx,ny,n", [("fp64", 123, 90, 5), ("fp32", 246, 1500, 4), ("fp32", 253, 1601, 7),
+                                           ("fp32", 4096, 2048, 3)])
+def test_d2q9(dtype, nx, ny, n, delta):
+    _check(nx, ny, n, dtype=dtype, delta=delta, mag_lattice="d2q9")
+
+
+def test_large_grids():
+    """Sector-aligned strips and two workgroups per compute unit."""
+    _check(8192, 1024, 4, dtype="fp32", delta=4.0)
+    _check(8190, 1030, 4, dtype="fp64", delta=0.0)
+    _check(2000, 8200, 4, dtype="bf16", delta=4.0)
+
+
+@pytest.mark.parametrize("dtype,delta,n", [("fp32", 0.0, 4), ("fp32", 4.0, 6), ("fp64", 2.0, 4)])
+def test_captured_steps_replay(dtype, delta, n):
+    """An even number of steps recorded into a graph advances the state at every replay."""
+    _require_gpu()
+    st = torch.cuda.Stream()
+    with torch.cuda.stream(st):
+        a = _start(640, 600, dtype=dtype, delta=delta)
+        b = _start(640, 600, dtype=dtype, delta=delta)
+        a.step(n)  # eager first
+        b.step(n)
+    st.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=st):
+        a.step(n)
+    for k in range(3):
+        graph.replay()
+        torch.cuda.synchronize()
+        with torch.cuda.stream(st):
+            b.step(n)
+            x, y = a.get_state(), b.get_state()
+        st.synchronize()
+        assert torch.equal(x, y), k
