@@ -660,107 +660,232 @@ __global__ void __launch_bounds__(256) k_gauss_taps(double sigma2, int R, double
   if (r <= 2 * R) taps[r] = wv[r] / wv[255];
 }
 
-__global__ void __launch_bounds__(64)
-k_filter_x(const double* __restrict__ mom, int nx, int ny, int factor, int R, const double* __restrict__ taps,
+// x pass.  A workgroup forms the 12 products of one row's fine cells once (they are
+// used by 2 R / FACTOR + 1 outputs), in LDS, and each of its four waves
+// filters three of them: a lane computes B adjacent outputs, so a value read from LDS
+// serves up to B of them.  A fine cell x of the segment sits at [x % (B FACTOR)][x /
+// (B FACTOR)], so the lanes of a wave, B FACTOR cells apart, read consecutive
+// doubles.  Taps are uniform (scalar loads).  Bound by HBM (40 B read, 96 B /
+// FACTOR written per fine cell) and the LDS reads.  Measured 4096^2, FACTOR 4, R = 24:
+// one thread per output forming its own products (and three divisions) per tap
+// 1502 us, this form 441 us.
+template <int FACTOR>
+struct FilterX {
+  static constexpr int B = FACTOR <= 4 ? 2 : 1;       // outputs per lane
+  static constexpr int P = B * FACTOR;                // fine cells between lanes
+  static constexpr int NI = 64 + (2 * 127 + P - 1) / P + 1;
+};
+
+template <int FACTOR>
+__global__ void __launch_bounds__(256)
+k_filter_x(const double* __restrict__ mom, int nx, int ny, int R, const double* __restrict__ taps,
            double* __restrict__ tmp) {
-  const int cx = nx / factor;
-  const int X = blockIdx.x * 64 + threadIdx.x, y = blockIdx.y;
-  if (X >= cx) return;
+  constexpr int B = FilterX<FACTOR>::B, P = FilterX<FACTOR>::P, NI = FilterX<FACTOR>::NI;
+  extern __shared__ double prod[];  // [12][P][NI]
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int k0 = 3 * __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int cx = nx / FACTOR;
+  const int X0 = blockIdx.x * 64 * B, y = blockIdx.y;
   const int64_t n = (int64_t)nx * ny;
-  double acc[12];
-#pragma unroll
-  for (int k = 0; k < 12; ++k) acc[k] = 0.0;
-  for (int r = -R; r <= R; ++r) {
-    int xx = (X * factor + r) % nx;
+  const double* row = mom + (int64_t)y * nx;
+  for (int e = tid; e < 64 * P + 2 * R; e += 256) {
+    int xx = (X0 * FACTOR - R + e) % nx;
     if (xx < 0) xx += nx;
-    const int64_t c = (int64_t)y * nx + xx;
-    const double rho = mom[c], mx = mom[n + c], my = mom[2 * n + c], bx = mom[3 * n + c], by = mom[4 * n + c];
-    const double w = taps[r + R];
+    const double rho = row[xx], mx = row[n + xx], my = row[2 * n + xx], bx = row[3 * n + xx], by = row[4 * n + xx];
     const double p[12] = {rho, mx, my, bx, by, mx * mx / rho, mx * my / rho, my * my / rho,
                           bx * bx, bx * by, by * by, (mx * by - my * bx) / rho};
 #pragma unroll
-    for (int k = 0; k < 12; ++k) acc[k] += w * p[k];
+    for (int k = 0; k < 12; ++k) prod[(k * P + e % P) * NI + e / P] = p[k];
+  }
+  __syncthreads();
+  double acc[3][B];
+#pragma unroll
+  for (int k = 0; k < 3; ++k)
+#pragma unroll
+    for (int b = 0; b < B; ++b) acc[k][b] = 0.0;
+  const double* v = prod + k0 * P * NI + lane;
+  // position t of a lane's window is tap t - b FACTOR of its output b
+  const int end = 2 * R + (B - 1) * FACTOR;
+  for (int t0 = 0; t0 <= end; t0 += P) {
+    const double* vq = v + t0 / P;
+    if (t0 >= (B - 1) * FACTOR && t0 + P - 1 <= 2 * R) {  // every tap of the body exists
+#pragma unroll
+      for (int p = 0; p < P; ++p)
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+          const double a = vq[(k * P + p) * NI];
+#pragma unroll
+          for (int b = 0; b < B; ++b) acc[k][b] += taps[t0 + p - b * FACTOR] * a;
+        }
+    } else {
+      for (int p = 0; p < P; ++p)
+#pragma unroll
+        for (int b = 0; b < B; ++b) {
+          const int r = t0 + p - b * FACTOR;
+          if (r < 0 || r > 2 * R) continue;  // uniform
+          const double w = taps[r];
+#pragma unroll
+          for (int k = 0; k < 3; ++k) acc[k][b] += w * vq[(k * P + p) * NI];
+        }
+    }
   }
   const int64_t cn = (int64_t)cx * ny;
+  const int X = X0 + lane * B;
 #pragma unroll
-  for (int k = 0; k < 12; ++k) tmp[k * cn + (int64_t)y * cx + X] = acc[k];
+  for (int k = 0; k < 3; ++k) {
+    double* out = tmp + (k0 + k) * cn + (int64_t)y * cx + X;
+#pragma unroll
+    for (int b = 0; b < B; ++b)
+      if (X + b < cx) out[b] = acc[k][b];
+  }
 }
 
+// y pass: a lane computes kFilterYB outputs of one column, so a row it reads
+// serves several of them.  Measured 4096^2 by 4, R = 24: 503 us with one output
+// per thread, 202 us.
+constexpr int kFilterYB = 4;
 __global__ void __launch_bounds__(64)
 k_filter_y(const double* __restrict__ tmp, int nx, int ny, int factor, int R, const double* __restrict__ taps,
            double* __restrict__ out) {
   const int cx = nx / factor, cy = ny / factor;
-  const int X = blockIdx.x * 64 + threadIdx.x, Y = blockIdx.y, k = blockIdx.z;
+  const int X = blockIdx.x * 64 + threadIdx.x, Y = blockIdx.y * kFilterYB, k = blockIdx.z;
   if (X >= cx) return;
   const int64_t cn = (int64_t)cx * ny;
-  double acc = 0.0;
-  for (int r = -R; r <= R; ++r) {
-    int yy = (Y * factor + r) % ny;
-    if (yy < 0) yy += ny;
-    acc += taps[r + R] * tmp[k * cn + (int64_t)yy * cx + X];
+  const double* col = tmp + k * cn + X;
+  double acc[kFilterYB];
+#pragma unroll
+  for (int b = 0; b < kFilterYB; ++b) acc[b] = 0.0;
+  const int end = 2 * R + (kFilterYB - 1) * factor;
+  int yy = (Y * factor - R) % ny;
+  if (yy < 0) yy += ny;
+  auto next = [&]() __attribute__((always_inline)) {
+    const double a = col[(int64_t)yy * cx];
+    yy = yy + 1 == ny ? 0 : yy + 1;
+    return a;
+  };
+  auto some = [&](int t) __attribute__((always_inline)) {
+    const double a = next();
+#pragma unroll
+    for (int b = 0; b < kFilterYB; ++b) {
+      const int r = t - b * factor;
+      if (r >= 0 && r <= 2 * R) acc[b] += taps[r] * a;  // uniform
+    }
+  };
+  int t = 0;
+  for (; t < (kFilterYB - 1) * factor && t <= end; ++t) some(t);
+  for (; t + 3 <= 2 * R; t += 4) {  // every tap exists
+    double a[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) a[j] = next();
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int b = 0; b < kFilterYB; ++b) acc[b] += taps[t + j - b * factor] * a[j];
   }
-  out[(int64_t)k * cx * cy + (int64_t)Y * cx + X] = acc;
+  for (; t <= end; ++t) some(t);
+#pragma unroll
+  for (int b = 0; b < kFilterYB; ++b)
+    if (Y + b < cy) out[(int64_t)k * cx * cy + (int64_t)(Y + b) * cx + X] = acc[b];
 }
 
 // ---------------------------------------------------------------------------
 // Training samples on the coarse grid: inputs and exact-minus-analytic
-// targets of every cell (FP64 arithmetic, FP32 output).
+// targets of every cell (FP64 arithmetic, FP32 output).  A workgroup takes a
+// tile of cells: velocities (one division per component and cell) and B of the
+// tile with a two-cell halo in LDS, from them the seven FP32 input fields with a
+// one-cell halo, and from those the rows, 16 lanes per cell with 16-byte stores.
+// Bound by the 272 B written per cell.  Measured 1024^2: one thread per cell
+// recomputing every neighbour's fields 842 us, 98 us.
 // ---------------------------------------------------------------------------
+constexpr int kSampX = 32, kSampY = 8;
+
 template <int STENCIL>
 __global__ void __launch_bounds__(256)
 k_closure_samples(const double* __restrict__ c12, int nx, int ny, double k2, float* __restrict__ xo,
                   float* __restrict__ to) {
-  const int x = blockIdx.x * 64 + threadIdx.x, y = blockIdx.y * 4 + threadIdx.y;
-  if (x >= nx || y >= ny) return;
+  constexpr int DX = kSampX + 4, DY = kSampY + 4, FX = kSampX + 2, FY = kSampY + 2;
+  __shared__ double uv[4][DY][DX];     // u_x, u_y, B_x, B_y
+  __shared__ float fld[7 * FY * FX + 1];  // input fields; the last entry is the zero pad
+  const int tid = threadIdx.x;
+  const int x0 = blockIdx.x * kSampX, y0 = blockIdx.y * kSampY;
   const int64_t n = (int64_t)nx * ny;
-  auto at = [&](int k, int dx, int dy) {
-    int xx = (x + dx) % nx, yy = (y + dy) % ny;
-    if (xx < 0) xx += nx;
-    if (yy < 0) yy += ny;
-    return c12[k * n + (int64_t)yy * nx + xx];
+  auto wrap = [](int v, int m) {
+    v %= m;
+    return v < 0 ? v + m : v;
   };
-  auto field = [&](int f, int dx, int dy) -> double {
-    switch (f) {
-      case 0: return at(0, dx, dy);
-      case 1: return at(1, dx, dy) / at(0, dx, dy);
-      case 2: return at(2, dx, dy) / at(0, dx, dy);
-      case 3: return at(3, dx, dy);
-      default: return at(4, dx, dy);
+  for (int e = tid; e < DY * DX; e += 256) {
+    const int ly = e / DX, lx = e - ly * DX;
+    const int64_t c = (int64_t)wrap(y0 + ly - 2, ny) * nx + wrap(x0 + lx - 2, nx);
+    const double rho = c12[c];
+    uv[0][ly][lx] = c12[n + c] / rho;
+    uv[1][ly][lx] = c12[2 * n + c] / rho;
+    uv[2][ly][lx] = c12[3 * n + c];
+    uv[3][ly][lx] = c12[4 * n + c];
+    if (ly >= 1 && ly <= FY && lx >= 1 && lx <= FX) fld[(ly - 1) * FX + lx - 1] = float(rho);
+  }
+  if (tid == 0) fld[7 * FY * FX] = 0.0f;
+  __syncthreads();
+  for (int e = tid; e < FY * FX; e += 256) {
+    const int fy = e / FX, fx = e - fy * FX, ly = fy + 1, lx = fx + 1;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) fld[(k + 1) * FY * FX + e] = float(uv[k][ly][lx]);
+    // w: (u_y, u_x); J_z: (B_y, B_x)
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const auto& p = uv[2 * k + 1];
+      const auto& q = uv[2 * k];
+      fld[(5 + k) * FY * FX + e] =
+          float(0.5 * (p[ly][lx + 1] - p[ly][lx - 1]) - 0.5 * (q[ly + 1][lx] - q[ly - 1][lx]));
     }
-  };
-  const int64_t c = (int64_t)y * nx + x;
-  float* xr = xo + c * 64;
-  for (int f = 0; f < 7; ++f)
-    for (int dy = -1; dy <= 1; ++dy)
-      for (int dx = -1; dx <= 1; ++dx) {
-        double v;
-        if (f < 5) {
-          v = field(f, dx, dy);
-        } else {
-          const int a = f == 5 ? 2 : 4, b = f == 5 ? 1 : 3;  // w: (u_y, u_x); J_z: (B_y, B_x)
-          v = 0.5 * (field(a, dx + 1, dy) - field(a, dx - 1, dy)) - 0.5 * (field(b, dx, dy + 1) - field(b, dx, dy - 1));
-        }
-        xr[f * 9 + (dy + 1) * 3 + (dx + 1)] = float(v);
-      }
-  xr[63] = 0.0f;
+  }
+  __syncthreads();
+  {
+    // features 4 q .. 4 q + 3 of a cell from its corner's entry
+    const int q = tid & 15;
+    int off[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int k = 4 * q + j, f = k / 9, d = k - 9 * f;
+      off[j] = k < 63 ? f * FY * FX + (d / 3) * FX + d % 3 : -1;
+    }
+    for (int c = tid >> 4; c < kSampX * kSampY; c += 16) {
+      const int cy = c / kSampX, cxl = c - cy * kSampX;
+      if (x0 + cxl >= nx || y0 + cy >= ny) continue;
+      const int base = cy * FX + cxl;
+      f32x4 v;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) v[j] = fld[off[j] < 0 ? 7 * FY * FX : base + off[j]];
+      *reinterpret_cast<f32x4*>(xo + ((int64_t)(y0 + cy) * nx + x0 + cxl) * 64 + 4 * q) = v;
+    }
+  }
+  const int x = x0 + (tid & (kSampX - 1)), y = y0 + tid / kSampX;
+  if (x >= nx || y >= ny) return;
+  const int xe = x + 1 == nx ? 0 : x + 1, xw = x == 0 ? nx - 1 : x - 1;
+  const int64_t rc = (int64_t)y * nx, rn = (int64_t)(y + 1 == ny ? 0 : y + 1) * nx,
+                rs = (int64_t)(y == 0 ? ny - 1 : y - 1) * nx, c = rc + x;
+  auto at = [&](int k) { return c12[k * n + c]; };
   // exact subgrid terms of the filtered products
-  const double rho = at(0, 0, 0), mx = at(1, 0, 0), my = at(2, 0, 0), bx = at(3, 0, 0), by = at(4, 0, 0);
-  const double rxx = at(5, 0, 0) - mx * mx / rho, rxy = at(6, 0, 0) - mx * my / rho, ryy = at(7, 0, 0) - my * my / rho;
-  const double qxx = at(8, 0, 0) - bx * bx, qxy = at(9, 0, 0) - bx * by, qyy = at(10, 0, 0) - by * by;
-  const double eps = at(11, 0, 0) - (mx * by - my * bx) / rho;
+  const double rho = at(0), mx = at(1), my = at(2), bx = at(3), by = at(4);
+  const double rxx = at(5) - mx * mx / rho, rxy = at(6) - mx * my / rho, ryy = at(7) - my * my / rho;
+  const double qxx = at(8) - bx * bx, qxy = at(9) - bx * by, qyy = at(10) - by * by;
+  const double eps = at(11) - (mx * by - my * bx) / rho;
   // analytic closure of the filtered fields
   double g[4][2];
-  for (int k = 0; k < 4; ++k)
-    grad3x3<double, STENCIL>(at(1 + k, 1, 0), at(1 + k, -1, 0), at(1 + k, 0, 1), at(1 + k, 0, -1), at(1 + k, 1, 1),
-                             at(1 + k, -1, 1), at(1 + k, 1, -1), at(1 + k, -1, -1), g[k][0], g[k][1]);
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const double* f = c12 + (1 + k) * n;
+    grad3x3<double, STENCIL>(f[rc + xe], f[rc + xw], f[rn + x], f[rs + x], f[rn + xe], f[rn + xw], f[rs + xe],
+                             f[rs + xw], g[k][0], g[k][1]);
+  }
   const Closure<double> cl =
       closure_terms(g[0][0], g[0][1], g[1][0], g[1][1], g[2][0], g[2][1], g[3][0], g[3][1], 1.0 / rho, k2);
   const double a_xx = 0.5 * (cl.tau_s + cl.tau_d), a_yy = 0.5 * (cl.tau_s - cl.tau_d);
-  float* tr = to + c * 4;
-  tr[0] = float((rxx + 0.5 * (qyy - qxx)) - a_xx);
-  tr[1] = float((rxy - qxy) - cl.tau_xy);
-  tr[2] = float((ryy + 0.5 * (qxx - qyy)) - a_yy);
-  tr[3] = float(eps - cl.eps);
+  f32x4 v;
+  v[0] = float((rxx + 0.5 * (qyy - qxx)) - a_xx);
+  v[1] = float((rxy - qxy) - cl.tau_xy);
+  v[2] = float((ryy + 0.5 * (qxx - qyy)) - a_yy);
+  v[3] = float(eps - cl.eps);
+  *reinterpret_cast<f32x4*>(to + c * 4) = v;
 }
 
 // ---------------------------------------------------------------------------
@@ -1152,6 +1277,22 @@ size_t filter_work_bytes(int nx, int ny, int factor) {
   return 256 * sizeof(double) + (size_t)12 * (size_t)(nx / factor) * (size_t)ny * sizeof(double);
 }
 
+template <int FACTOR>
+static hipError_t launch_filter_x(const double* mom, int nx, int ny, int R, const double* taps, double* tmp,
+                                  hipStream_t st) {
+  using F = FilterX<FACTOR>;
+  const size_t lds = (size_t)12 * F::P * F::NI * sizeof(double);
+  if (lds > 64 * 1024) {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_filter_x<FACTOR>),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+  }
+  const int per = 64 * F::B;
+  hipLaunchKernelGGL((k_filter_x<FACTOR>), dim3((nx / FACTOR + per - 1) / per, ny), dim3(256), lds, st, mom, nx, ny, R,
+                     taps, tmp);
+  return hipGetLastError();
+}
+
 hipError_t launch_filter(const double* mom, int nx, int ny, int factor, double delta, double* out, void* work,
                          hipStream_t st) {
   const int R = filter_radius(delta);
@@ -1161,15 +1302,22 @@ hipError_t launch_filter(const double* mom, int nx, int ny, int factor, double d
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const int cx = nx / factor, cy = ny / factor;
-  hipLaunchKernelGGL(k_filter_x, dim3((cx + 63) / 64, ny), dim3(64), 0, st, mom, nx, ny, factor, R, taps, tmp);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  hipLaunchKernelGGL(k_filter_y, dim3((cx + 63) / 64, cy, 12), dim3(64), 0, st, tmp, nx, ny, factor, R, taps, out);
+  switch (factor) {
+    case 1: e = launch_filter_x<1>(mom, nx, ny, R, taps, tmp, st); break;
+    case 2: e = launch_filter_x<2>(mom, nx, ny, R, taps, tmp, st); break;
+    case 4: e = launch_filter_x<4>(mom, nx, ny, R, taps, tmp, st); break;
+    case 8: e = launch_filter_x<8>(mom, nx, ny, R, taps, tmp, st); break;
+    default: e = launch_filter_x<16>(mom, nx, ny, R, taps, tmp, st);
+  }
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_filter_y, dim3((cx + 63) / 64, (cy + kFilterYB - 1) / kFilterYB, 12), dim3(64), 0, st, tmp, nx,
+                     ny, factor, R, taps, out);
   return hipGetLastError();
 }
 
 hipError_t launch_closure_samples(const double* c12, int nx, int ny, double delta, int stencil, float* x, float* t,
                                   hipStream_t st) {
-  const dim3 g((nx + 63) / 64, (ny + 3) / 4), b(64, 4);
+  const dim3 g((nx + kSampX - 1) / kSampX, (ny + kSampY - 1) / kSampY), b(256);
   const double k2 = delta * delta / 12.0;
   if (stencil == LBM_STENCIL_ISO9)
     hipLaunchKernelGGL(k_closure_samples<LBM_STENCIL_ISO9>, g, b, 0, st, c12, nx, ny, k2, x, t);
