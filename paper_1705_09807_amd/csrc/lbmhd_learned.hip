@@ -1,13 +1,12 @@
-// HIP kernels (gfx950) of the learned subgrid closure, the filtered-DNS
-// pipeline that trains it, and the energy spectra.
+// HIP kernels (gfx950) of the learned subgrid closure and the filtered-DNS
+// pipeline that trains it.
 //
 // Method: Flint & Vahala, arXiv 1705.09807.  The analytic closure (Sec. 2.1
 // FilterExampleSmall, Sec. 3) keeps the Delta^2/12 term of the filtered
 // products; the learned closure adds a per-cell correction of the same four
 // subgrid terms (tau_xx, tau_xy, tau_yy, eps), predicted by a 63-64-64-4 ReLU
 // network trained on filtered DNS (the convolution of Sec. 1, VelFilter, with
-// a Gaussian of variance Delta^2/12).  The spectra are the radially binned
-// kinetic and magnetic energies compared in Sec. 4.
+// a Gaussian of variance Delta^2/12).
 //
 // Network on the matrix cores.  One wave evaluates 32 cells at a time in the
 // transposed form H^T = W^T X^T, so that every layer's output (rows = hidden
@@ -889,253 +888,6 @@ k_closure_samples(const double* __restrict__ c12, int nx, int ny, double k2, flo
 }
 
 // ---------------------------------------------------------------------------
-// Spectra.  Two complex fields per state, z_u = u_x + i u_y and z_B = B_x + i
-// B_y: over a bin that contains -k with every k, sum |Z(k)|^2 equals
-// sum |A(k)|^2 + |B(k)|^2 of the real fields' transforms.  Row FFTs, then
-// column FFTs that bin |Z|^2 / n^4 per column (deterministic: one thread per
-// bin walks its k_y range in order), then a fixed-order sum over columns.
-// Radix-2 decimation in time in LDS (bit-reversed load), FP64 twiddles from
-// sincospi.
-// ---------------------------------------------------------------------------
-__device__ __forceinline__ unsigned bitrev(unsigned v, int bits) { return __builtin_bitreverse32(v) >> (32 - bits); }
-
-// floor(sqrt(v)) and ceil(sqrt(v)) of a non-negative integer, exact.
-__device__ __forceinline__ int isqrt_floor(int64_t v) {
-  int64_t r = (int64_t)sqrt(double(v));
-  while (r * r > v) --r;
-  while ((r + 1) * (r + 1) <= v) ++r;
-  return (int)r;
-}
-__device__ __forceinline__ int isqrt_ceil(int64_t v) {
-  const int r = isqrt_floor(v);
-  return (int64_t)r * r == v ? r : r + 1;
-}
-
-__device__ void fft_lds(double2* a, int n, int bits) {
-  for (int half = 1; half < n; half <<= 1) {
-    __syncthreads();
-    for (int j = threadIdx.x; j < n / 2; j += blockDim.x) {
-      const int pos = j & (half - 1);
-      const int i0 = ((j - pos) << 1) + pos, i1 = i0 + half;
-      double s, c;
-      sincospi(-double(pos) / double(half), &s, &c);
-      const double2 u = a[i0], v = a[i1];
-      const double tr = c * v.x - s * v.y, ti = c * v.y + s * v.x;
-      a[i0] = make_double2(u.x + tr, u.y + ti);
-      a[i1] = make_double2(u.x - tr, u.y - ti);
-    }
-  }
-  __syncthreads();
-}
-
-// Column of a column-pass workgroup.  Workgroups are dealt to the 8 XCDs in
-// turn; this gives each XCD a contiguous range of columns, so the workgroups
-// that read neighbouring columns (the same cache lines of every row) share an
-// L2.  n is a power of two >= 8.
-__device__ __forceinline__ int column_of_block(int bx, int n) { return (bx & 7) * (n >> 3) + (bx >> 3); }
-
-__global__ void __launch_bounds__(256)
-k_fft_rows(const double* __restrict__ mom, int n, int bits, double2* __restrict__ work) {
-  extern __shared__ double2 a[];
-  const int y = blockIdx.x, pair = blockIdx.y;
-  const int64_t nn = (int64_t)n * n;
-  for (int x = threadIdx.x; x < n; x += blockDim.x) {
-    const int64_t c = (int64_t)y * n + x;
-    double re, im;
-    if (pair == 0) {
-      const double r = mom[c];
-      re = mom[nn + c] / r;
-      im = mom[2 * nn + c] / r;
-    } else {
-      re = mom[3 * nn + c];
-      im = mom[4 * nn + c];
-    }
-    a[bitrev(x, bits)] = make_double2(re, im);
-  }
-  fft_lds(a, n, bits);
-  for (int x = threadIdx.x; x < n; x += blockDim.x) work[pair * nn + (int64_t)y * n + x] = a[x];
-}
-
-__global__ void __launch_bounds__(256)
-k_fft_cols(const double2* __restrict__ work, int n, int bits, int nbins, double* __restrict__ part,
-           double* __restrict__ partx) {
-  extern __shared__ double2 a[];
-  const int kxi = column_of_block(blockIdx.x, n), pair = blockIdx.y;
-  const int64_t nn = (int64_t)n * n;
-  for (int y = threadIdx.x; y < n; y += blockDim.x) a[bitrev(y, bits)] = work[pair * nn + (int64_t)y * n + kxi];
-  fft_lds(a, n, bits);
-  const double inv = 1.0 / (double(n) * double(n));
-  const int kx = kxi < n / 2 ? kxi : kxi - n;
-  const int64_t kx2 = (int64_t)kx * kx;
-  double* out = part + ((int64_t)pair * n + kxi) * nbins;
-  // Bin b holds the k with floor(|k| + 1/2) = b, i.e. |k|^2 = 0 for b = 0 and
-  // b^2 - b + 1 <= |k|^2 <= b^2 + b for b >= 1 (exact in integers).  One
-  // thread per bin walks its |k_y| range upwards, +k_y before -k_y.
-  for (int b = threadIdx.x; b < nbins; b += blockDim.x) {
-    const int64_t lo = b == 0 ? 0 : (int64_t)b * b - b + 1 - kx2;
-    const int64_t hi = (int64_t)b * b + b - kx2;
-    double s = 0.0;
-    if (hi >= 0) {
-      const int a0 = lo <= 0 ? 0 : isqrt_ceil(lo);
-      int a1 = isqrt_floor(hi);
-      if (a1 > n / 2) a1 = n / 2;
-      for (int ay = a0; ay <= a1; ++ay) {
-        const int idx[2] = {ay == n / 2 ? n / 2 : ay, n - ay};
-        const int cnt = (ay == 0 || ay == n / 2) ? 1 : 2;
-        for (int u = 0; u < cnt; ++u) {
-          const double2 z = a[idx[u]];
-          s += (z.x * inv) * (z.x * inv) + (z.y * inv) * (z.y * inv);
-        }
-      }
-    }
-    out[b] = s;
-  }
-  if (threadIdx.x == 0) {
-    double s = 0.0;
-    for (int yi = 0; yi < n; ++yi) {
-      const double2 z = a[yi];
-      s += (z.x * inv) * (z.x * inv) + (z.y * inv) * (z.y * inv);
-    }
-    partx[(int64_t)pair * n + kxi] = s;
-  }
-}
-
-// Rows and columns longer than one LDS transform (n > kFftLds): n = n1 n2
-// with n2 = kFftLds.  With x = j1 n2 + j2 and k = k1 + n1 k2 (w_m =
-// exp(-2 pi i / m)),
-//   X[k1 + n1 k2] = sum_j2 w_n2^(j2 k2) [w_n^(j2 k1) sum_j1 a[j1 n2 + j2] w_n1^(j1 k1)],
-// so each workgroup takes one residue class k1: an n1-point DFT and a twiddle
-// per element, then one n2-point FFT in LDS.  The column pass stores the
-// scaled |Z|^2 per column; k_bin_cols then bins every column in the same
-// order as k_fft_cols.
-constexpr int kFftLds = 4096, kFftLdsBits = 12;
-
-__device__ __forceinline__ double2 cmul_w(double2 v, double num, double den) {
-  double s, c;
-  sincospi(-2.0 * num / den, &s, &c);
-  return make_double2(c * v.x - s * v.y, c * v.y + s * v.x);
-}
-
-__global__ void __launch_bounds__(256)
-k_fft_rows_big(const double* __restrict__ mom, int n, int n1, double2* __restrict__ work) {
-  extern __shared__ double2 a[];
-  const int y = blockIdx.x, k1 = blockIdx.y, pair = blockIdx.z;
-  const int64_t nn = (int64_t)n * n;
-  for (int j2 = threadIdx.x; j2 < kFftLds; j2 += blockDim.x) {
-    double2 s = make_double2(0.0, 0.0);
-    for (int j1 = 0; j1 < n1; ++j1) {
-      const int64_t c = (int64_t)y * n + (int64_t)j1 * kFftLds + j2;
-      double re, im;
-      if (pair == 0) {
-        const double r = mom[c];
-        re = mom[nn + c] / r;
-        im = mom[2 * nn + c] / r;
-      } else {
-        re = mom[3 * nn + c];
-        im = mom[4 * nn + c];
-      }
-      const double2 t = cmul_w(make_double2(re, im), double(j1 * k1), double(n1));
-      s.x += t.x;
-      s.y += t.y;
-    }
-    a[bitrev(j2, kFftLdsBits)] = cmul_w(s, double(j2) * double(k1), double(n));
-  }
-  fft_lds(a, kFftLds, kFftLdsBits);
-  for (int k2 = threadIdx.x; k2 < kFftLds; k2 += blockDim.x)
-    work[pair * nn + (int64_t)y * n + k1 + (int64_t)n1 * k2] = a[k2];
-}
-
-__global__ void __launch_bounds__(256)
-k_fft_cols_big(const double2* __restrict__ work, int n, int n1, double* __restrict__ pw) {
-  extern __shared__ double2 a[];
-  const int kxi = column_of_block(blockIdx.x, n), k1 = blockIdx.y, pair = blockIdx.z;
-  const int64_t nn = (int64_t)n * n;
-  const double inv = 1.0 / (double(n) * double(n));
-  for (int j2 = threadIdx.x; j2 < kFftLds; j2 += blockDim.x) {
-    double2 s = make_double2(0.0, 0.0);
-    for (int j1 = 0; j1 < n1; ++j1) {
-      const double2 t =
-          cmul_w(work[pair * nn + ((int64_t)j1 * kFftLds + j2) * n + kxi], double(j1 * k1), double(n1));
-      s.x += t.x;
-      s.y += t.y;
-    }
-    a[bitrev(j2, kFftLdsBits)] = cmul_w(s, double(j2) * double(k1), double(n));
-  }
-  fft_lds(a, kFftLds, kFftLdsBits);
-  double* col = pw + pair * nn + (int64_t)kxi * n;
-  for (int k2 = threadIdx.x; k2 < kFftLds; k2 += blockDim.x) {
-    const double2 z = a[k2];
-    col[k1 + (int64_t)n1 * k2] = (z.x * inv) * (z.x * inv) + (z.y * inv) * (z.y * inv);
-  }
-}
-
-// Bins of one column of scaled |Z|^2 (k_fft_cols' walk and order).
-__global__ void __launch_bounds__(256)
-k_bin_cols(const double* __restrict__ pw, int n, int nbins, double* __restrict__ part, double* __restrict__ partx) {
-  const int kxi = blockIdx.x, pair = blockIdx.y;
-  const double* col = pw + (int64_t)pair * n * n + (int64_t)kxi * n;
-  const int kx = kxi < n / 2 ? kxi : kxi - n;
-  const int64_t kx2 = (int64_t)kx * kx;
-  double* out = part + ((int64_t)pair * n + kxi) * nbins;
-  for (int b = threadIdx.x; b < nbins; b += blockDim.x) {
-    const int64_t lo = b == 0 ? 0 : (int64_t)b * b - b + 1 - kx2;
-    const int64_t hi = (int64_t)b * b + b - kx2;
-    double s = 0.0;
-    if (hi >= 0) {
-      const int a0 = lo <= 0 ? 0 : isqrt_ceil(lo);
-      int a1 = isqrt_floor(hi);
-      if (a1 > n / 2) a1 = n / 2;
-      for (int ay = a0; ay <= a1; ++ay) {
-        const int idx[2] = {ay == n / 2 ? n / 2 : ay, n - ay};
-        const int cnt = (ay == 0 || ay == n / 2) ? 1 : 2;
-        for (int u = 0; u < cnt; ++u) s += col[idx[u]];
-      }
-    }
-    out[b] = s;
-  }
-  if (threadIdx.x == 0) {
-    double s = 0.0;
-    for (int yi = 0; yi < n; ++yi) s += col[yi];
-    partx[(int64_t)pair * n + kxi] = s;
-  }
-}
-
-// Sums of the per-column bins in a fixed order: thread (bin, s) of a 64 x 16
-// block adds the columns s, s + 16, s + 32, ... of its bin (consecutive bins
-// are consecutive addresses), then the 16 partial sums are added in order of s.
-__global__ void __launch_bounds__(1024)
-k_spectra_final(const double* __restrict__ part, const double* __restrict__ partx, int n, int nbins,
-                double* __restrict__ ek, double* __restrict__ em, double* __restrict__ ekx) {
-  __shared__ double red[2][16][64];
-  const int bl = threadIdx.x, sl = threadIdx.y;
-  const int b = blockIdx.x * 64 + bl;
-  double su = 0.0, sb = 0.0;
-  if (b < nbins) {
-    for (int k = sl; k < n; k += 16) {
-      su += part[(int64_t)k * nbins + b];
-      sb += part[((int64_t)n + k) * nbins + b];
-    }
-  }
-  red[0][sl][bl] = su;
-  red[1][sl][bl] = sb;
-  __syncthreads();
-  if (sl == 0 && b < nbins) {
-    double tu = 0.0, tb = 0.0;
-    for (int i = 0; i < 16; ++i) {
-      tu += red[0][i][bl];
-      tb += red[1][i][bl];
-    }
-    ek[b] = 0.5 * tu;
-    em[b] = 0.5 * tb;
-  }
-  if (ekx && sl == 1 && b <= n / 2) {
-    double x = partx[b];
-    if (b != 0 && b != n / 2) x += partx[n - b];
-    ekx[b] = 0.5 * x;
-  }
-}
-
-// ---------------------------------------------------------------------------
 // Host launchers
 // ---------------------------------------------------------------------------
 static int train_blocks(int batch) {
@@ -1329,47 +1081,6 @@ hipError_t launch_closure_samples(const double* c12, int nx, int ny, double delt
 hipError_t launch_mlp_correct(const void* cell_in, const void* packed, float* corr, int nx, int ny, hipStream_t st) {
   hipLaunchKernelGGL(k_mlp_correct, dim3((nx + kCorrTX - 1) / kCorrTX, (ny + kCorrTY - 1) / kCorrTY), dim3(256), 0, st,
                      static_cast<const CellIn*>(cell_in), static_cast<const char*>(packed), corr, nx, ny);
-  return hipGetLastError();
-}
-
-int spectra_bins(int n) { return (int)floor(sqrt(2.0) * double(n / 2) + 0.5) + 1; }
-
-size_t spectra_work_bytes(int n) {
-  const size_t nn = (size_t)n * n;
-  const size_t big = n > kFftLds ? 2 * nn * sizeof(double) : 0;  // scaled |Z|^2 of the long columns
-  return 2 * nn * sizeof(double2) + big + (size_t)2 * n * spectra_bins(n) * sizeof(double) +
-         (size_t)2 * n * sizeof(double);
-}
-
-hipError_t launch_spectra(const double* mom, int n, double* ek, double* em, double* ekx, void* work, hipStream_t st) {
-  int bits = 0;
-  while ((1 << bits) < n) ++bits;
-  const int nb = spectra_bins(n);
-  double2* cw = static_cast<double2*>(work);
-  double* part = reinterpret_cast<double*>(cw + (size_t)2 * n * n);
-  hipError_t e;
-  if (n <= kFftLds) {
-    double* partx = part + (size_t)2 * n * nb;
-    const size_t lds = (size_t)n * sizeof(double2);
-    hipLaunchKernelGGL(k_fft_rows, dim3(n, 2), dim3(256), lds, st, mom, n, bits, cw);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_fft_cols, dim3(n, 2), dim3(256), lds, st, cw, n, bits, nb, part, partx);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-  } else {
-    double* pw = part;
-    part = pw + (size_t)2 * n * n;
-    const int n1 = n / kFftLds;
-    const size_t lds = (size_t)kFftLds * sizeof(double2);
-    hipLaunchKernelGGL(k_fft_rows_big, dim3(n, n1, 2), dim3(256), lds, st, mom, n, n1, cw);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_fft_cols_big, dim3(n, n1, 2), dim3(256), lds, st, cw, n, n1, pw);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_bin_cols, dim3(n, 2), dim3(256), 0, st, pw, n, nb, part, part + (size_t)2 * n * nb);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-  }
-  double* partx = part + (size_t)2 * n * nb;
-  const int fin = (nb > n / 2 + 1 ? nb : n / 2 + 1);
-  hipLaunchKernelGGL(k_spectra_final, dim3((fin + 63) / 64), dim3(64, 16), 0, st, part, partx, n, nb, ek, em, ekx);
   return hipGetLastError();
 }
 
