@@ -267,7 +267,7 @@ int lbm_moments(lbm_ctx* ctx, double* out_dev) {
   int rc = check_ctx(ctx, true);
   if (rc != LBM_OK) return rc;
   if (!out_dev || !aligned(out_dev)) return fail(LBM_EINVAL, "out_dev must be a non-NULL 256-byte aligned pointer");
-  hipError_t e = lbm::launch_moments(ctx->L, ctx->t, out_dev, false);
+  hipError_t e = lbm::launch_moments(ctx->L, ctx->t, out_dev);
   return e == hipSuccess ? LBM_OK : hip_fail(e, "lbm_moments");
 }
 

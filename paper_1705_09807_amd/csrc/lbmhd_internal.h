@@ -78,7 +78,7 @@ hipError_t launch_step(const Launch& L, int64_t t, bool corr_refresh = true);
 hipError_t launch_lag_prime(const Launch& L, int64_t t);
 hipError_t launch_get_state(const Launch& L, int64_t t, double* out);
 hipError_t launch_set_state(const Launch& L, int64_t t, const double* in);
-hipError_t launch_moments(const Launch& L, int64_t t, double* out, bool mark_nonfinite);
+hipError_t launch_moments(const Launch& L, int64_t t, double* out);
 // Diagnostics: enqueue, copy kDiagVals doubles to host, synchronise the stream.
 hipError_t launch_diagnostics(const Launch& L, int64_t t, double* vals_host);
 // Learned correction of the state at time t into 4 FP32 planes.

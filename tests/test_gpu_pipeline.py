@@ -76,3 +76,61 @@ def test_sample_tiles(nx, ny, stencil):
     assert np.all(np.abs(X - Xo) <= 1.2e-7 * np.abs(Xo) + 1e-12)
     assert np.all(X[:, 63] == 0.0)
     assert np.all(np.abs(T - To).max(axis=0) <= 1e-6 * np.abs(To).max(axis=0))
+
+
+@pytest.mark.parametrize("n", [8, 16, 32, 64, 128, 256, 512, 1024, 2048])
+def test_spectra_of_every_length(n):
+    """Every transform length up to 2048 (4096 and beyond have closed forms in the
+    other spectra test): white fields, so every bin holds energy.  FP64 on both
+    sides: within 1e-13 of the total, as there, and equal when repeated."""
+    from oracle import spectra as S
+    G = _gpu()
+    m = _fields(n, n, n)
+    d = torch.from_numpy(m).cuda()
+    got = G.spectra(d)
+    want = (*S.energy_spectra(*m), S.x_spectrum(m[1] / m[0], m[2] / m[0]))
+    for g, w in zip(got, want):
+        assert np.abs(g.cpu().numpy() - w).max() <= 1e-13 * w.sum()
+    for g, h in zip(got, G.spectra(d)):
+        assert torch.equal(g, h)
+
+
+@pytest.mark.parametrize("schedule,mag", [("fused", "d2q5"), ("fused", "d2q9"), ("aa", "d2q5")])
+@pytest.mark.parametrize("nx,ny", [(4, 4), (5, 4), (62, 9), (63, 64), (254, 7), (255, 33), (600, 19)])
+def test_diagnostics_strips(nx, ny, schedule, mag):
+    """Strip and segment edges of the diagnostics at both time parities: sums of the
+    moments the library returns, in FP64 (about 30 roundings per term: 1e-13)."""
+    _gpu()
+    from paper_1705_09807_amd import Sim
+    s = Sim(nx=nx, ny=ny, nu=1e-2, eta=1e-2, dtype="fp64", schedule=schedule, mag_lattice=mag)
+    s.init_from_moments(torch.from_numpy(_fields(nx, ny, nx + ny)))
+    for _ in range(2):
+        s.step(1)
+        d = s.diagnostics()
+        rho, mx, my, bx, by = s.moments().cpu().numpy()
+        ux, uy = mx / rho, my / rho
+        ddx = lambda a: (np.roll(a, -1, 1) - np.roll(a, 1, 1)) / 2  # noqa: E731
+        ddy = lambda a: (np.roll(a, -1, 0) - np.roll(a, 1, 0)) / 2  # noqa: E731
+        w, jz, dv = ddx(uy) - ddy(ux), ddx(by) - ddy(bx), ddx(bx) + ddy(by)
+        want = dict(mass=rho.sum(), e_kin=((mx ** 2 + my ** 2) / rho / 2).mean(), e_mag=((bx ** 2 + by ** 2) / 2).mean(),
+                    enstrophy=(w ** 2 / 2).mean(), j2=(jz ** 2).mean(), divb_max=np.abs(dv).max(),
+                    divb_rms=np.sqrt((dv ** 2).mean()))
+        for k, v in want.items():
+            assert abs(d[k] - v) <= 1e-13 * abs(v) + 1e-18, k
+        for k, a in (("mom_x", mx), ("mom_y", my), ("bsum_x", bx), ("bsum_y", by)):
+            assert abs(d[k] - a.sum()) <= 1e-13 * np.abs(a).sum(), k
+        assert d["nonfinite"] == 0
+
+
+@pytest.mark.parametrize("x,y", [(0, 0), (253, 3), (254, 8), (299, 40)])
+def test_diagnostics_counts_a_bad_cell(x, y):
+    _gpu()
+    from paper_1705_09807_amd import Sim
+    nx, ny = 300, 41
+    s = Sim(nx=nx, ny=ny, nu=1e-2, eta=1e-2, dtype="fp64")
+    s.init_from_moments(torch.from_numpy(_fields(nx, ny, 5)))
+    st = s.get_state()
+    st[11, y, x] = float("inf")
+    s.set_state(st)
+    d = s.diagnostics()
+    assert d["nonfinite"] == 1 and np.isnan(d["mass"])
