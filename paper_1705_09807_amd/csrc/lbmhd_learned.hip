@@ -75,48 +75,82 @@ k_mlp_pack(const float* __restrict__ p, const lbm_mlp_norm* __restrict__ norm, c
 // of the matrix-core network)
 // ---------------------------------------------------------------------------
 
-// Layer-1 operands of this lane from feature row `row` of x (FP32): z =
-// (x - shift) * scale per field, pad 0, rounded to bfloat16.  Sets *ood when
-// any |z| exceeds the limit; zf (may be null) receives the rounded values.
+typedef __attribute__((address_space(3))) void lds_void;
+typedef __attribute__((address_space(1))) void global_void;
+
+// Layer-1 operand kb of lane half h from the eight features u, v at kb*16 + h*8
+// (FP32): z = (x - shift) * scale per field, pad 0, rounded to bfloat16.  Sets
+// *ood when any |z| exceeds the limit; zf (may be null) receives the rounded values.
+__device__ __forceinline__ void feature_operands(const f32x4& u, const f32x4& v, int kb, int h, const lbm_mlp_norm* nm,
+                                                 bf16x8& zb, bool* ood, float* zf) {
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    const int k = kb * 16 + h * 8 + j;
+    const float xv = j < 4 ? u[j] : v[j - 4];
+    float z = 0.0f;
+    if (k < 63) {
+      const int f = feat_field(k);
+      z = (xv - nm->shift[f]) * nm->scale[f];
+    }
+    *ood = *ood || !(fabsf(z) <= kOodLimit);  // NaN counts as out of range
+    zb[j] = __bf16(z);
+    if (zf) zf[j] = float(zb[j]);
+  }
+}
+
+// Layer-1 operands of this lane from feature row `row` of x.
 __device__ __forceinline__ void row_operands(const float* __restrict__ x, int64_t row, const lbm_mlp_norm* nm,
                                              int h, bf16x8 zb[4], bool* ood, float* zf) {
-  bool o = false;
+  *ood = false;
 #pragma unroll
   for (int kb = 0; kb < 4; ++kb) {
     const f32x4* src = reinterpret_cast<const f32x4*>(x + row * 64 + kb * 16 + h * 8);
-    const f32x4 u = src[0], v = src[1];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const int k = kb * 16 + h * 8 + j;
-      const float xv = j < 4 ? u[j] : v[j - 4];
-      float z = 0.0f;
-      if (k < 63) {
-        const int f = feat_field(k);
-        z = (xv - nm->shift[f]) * nm->scale[f];
-      }
-      o = o || !(fabsf(z) <= kOodLimit);  // NaN counts as out of range
-      zb[kb][j] = __bf16(z);
-      if (zf) zf[kb * 8 + j] = float(zb[kb][j]);
-    }
+    feature_operands(src[0], src[1], kb, h, nm, zb[kb], ood, zf ? zf + kb * 8 : nullptr);
   }
-  *ood = o;
 }
 
+// A wave takes 32 rows at a time, 8 KB in one stretch, loaded straight into LDS
+// (16 bytes a lane).  The 16-byte piece c of row r goes to place c ^ (r % 16) of
+// that row, so the lanes that then read the same piece of 32 rows spread over the
+// banks.  The next rows are on their way while the network runs.  Measured 2^20 rows: operands read from memory with a
+// row's stride between lanes 96 us, this form 66 us.
 __global__ void __launch_bounds__(256)
 k_mlp_forward(const char* __restrict__ pk, const float* __restrict__ x, int64_t n, float* __restrict__ y,
               int32_t* __restrict__ ood_out) {
+  __shared__ f32x4 rows[4][32 * 16];
   const int lane = threadIdx.x & 63, h = lane >> 5;
-  const int64_t wave = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t wave = (int64_t)blockIdx.x * 4 + wid;
   const int64_t nwaves = (int64_t)gridDim.x * 4;
   const lbm_mlp_norm* nm = reinterpret_cast<const lbm_mlp_norm*>(pk + kPkNorm);
   MlpA w;
   load_mlp(pk, lane, w);
+  auto fetch = [&](int64_t g) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int r = i * 4 + (lane >> 4), c = (lane & 15) ^ (r & 15);
+      const int64_t src = g * 32 + r < n ? g * 32 + r : n - 1;
+      __builtin_amdgcn_global_load_lds((global_void*)(x + src * 64 + c * 4), (lds_void*)(&rows[wid][i * 64]), 16, 0, 0);
+    }
+  };
+  if (wave * 32 < n) fetch(wave);
   for (int64_t g = wave; g * 32 < n; g += nwaves) {
+    __builtin_amdgcn_s_waitcnt(0);  // the loads into LDS are complete
     const int64_t row = g * 32 + (lane & 31);
-    const int64_t rr = row < n ? row : n - 1;
+    f32x4 in[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      const int r = lane & 31, j = (k >> 1) * 4 + h * 2 + (k & 1);
+      in[k] = rows[wid][r * 16 + (j ^ (r & 15))];
+    }
+    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): read, so the next rows may arrive
+    __builtin_amdgcn_sched_barrier(0);
+    if ((g + nwaves) * 32 < n) fetch(g + nwaves);
+    __builtin_amdgcn_sched_barrier(0);
     bf16x8 zb[4];
-    bool o;
-    row_operands(x, rr, nm, h, zb, &o, nullptr);
+    bool o = false;
+#pragma unroll
+    for (int kb = 0; kb < 4; ++kb) feature_operands(in[2 * kb], in[2 * kb + 1], kb, h, nm, zb[kb], &o, nullptr);
     const f32x4 v = mlp_wave(w, zb, reinterpret_cast<const float*>(pk + kPkB1), lane, nullptr, nullptr);
     // every lane takes part in the exchange (a short-circuit would leave the
     // flagged lane inactive and its partner would read nothing from it)
@@ -160,9 +194,6 @@ __device__ __forceinline__ int wrap_halo(int v, int n, bool wide) {
   v %= n;
   return v < 0 ? v + n : v;
 }
-
-typedef __attribute__((address_space(3))) void lds_void;
-typedef __attribute__((address_space(1))) void global_void;
 
 __global__ void __launch_bounds__(256, 2)
 k_mlp_correct(const CellIn* __restrict__ in, const char* __restrict__ pk, float* __restrict__ corr, int nx, int ny) {
@@ -557,83 +588,127 @@ k_mlp_adam(float* __restrict__ p, float* __restrict__ m, float* __restrict__ v, 
 }
 
 // ---------------------------------------------------------------------------
-// Normalisation statistics: FP64 partial sums per workgroup, fixed-order
-// final pass.  Pass 1: sums of the seven centre features and of the squared
-// targets; pass 2: squared deviations from the means.
+// Normalisation statistics, FP64, one pass over the rows: counts, sums, and sums
+// of squared deviations from the mean, combined pairwise (Chan, Golub & LeVeque
+// 1983: M2 = M2_a + M2_b + (mean_b - mean_a)^2 n_a n_b / n) from threads to waves,
+// workgroups and, in a second kernel, the whole, always in the same order.  A
+// thread takes the deviations of its rows from its first row, so nothing cancels
+// beyond its few rows.  Bound by HBM (the centre features touch every line of a
+// row).  Measured 2^20 rows: two passes and two one-thread final sums 2 x 53 + 2 x
+// 65 us, this form 51 + 9 us.
 // ---------------------------------------------------------------------------
 constexpr int kStatBlocks = 256;
+constexpr int kStatVals = 26;  // count, 7 sums, 7 means, 7 M2, 4 sums of squared targets
 
-__device__ void block_sum11(double* acc, double* out) {
-  __shared__ double red[4][11];
+struct Stats {
+  double n, sum[7], mean[7], m2[7], t2[4];
+};
+
+__device__ __forceinline__ void stats_add(Stats& a, const Stats& b) {
+  const double n = a.n + b.n;
+  if (b.n != 0.0) {
+    const double wb = b.n / n, w = a.n * wb;
 #pragma unroll
-  for (int off = 32; off >= 1; off >>= 1)
+    for (int f = 0; f < 7; ++f) {
+      const double d = b.mean[f] - a.mean[f];
+      a.mean[f] = a.n == 0.0 ? b.mean[f] : a.mean[f] + d * wb;
+      a.m2[f] = a.n == 0.0 ? b.m2[f] : a.m2[f] + b.m2[f] + d * d * w;
+    }
+  }
 #pragma unroll
-    for (int k = 0; k < 11; ++k) acc[k] += __shfl_down(acc[k], off, 64);
-  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  if (lane == 0)
+  for (int f = 0; f < 7; ++f) a.sum[f] += b.sum[f];
 #pragma unroll
-    for (int k = 0; k < 11; ++k) red[wid][k] = acc[k];
+  for (int o = 0; o < 4; ++o) a.t2[o] += b.t2[o];
+  a.n = n;
+}
+
+// Sum over a workgroup of 256 threads; the result is in thread 0's s.
+__device__ void block_stats(Stats& s) {
+  static_assert(sizeof(Stats) == kStatVals * sizeof(double), "layout");
+  __shared__ Stats red[4];
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    Stats o;
+    const double* src = reinterpret_cast<const double*>(&s);
+    double* dst = reinterpret_cast<double*>(&o);
+#pragma unroll
+    for (int k = 0; k < kStatVals; ++k) dst[k] = __shfl_down(src[k], off, 64);
+    if ((threadIdx.x & 63) + off >= 64) o.n = 0.0;  // no such lane
+    if ((threadIdx.x & (2 * off - 1)) == 0) stats_add(s, o);
+  }
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
   __syncthreads();
   if (threadIdx.x == 0)
-    for (int k = 0; k < 11; ++k) out[k] = ((red[0][k] + red[1][k]) + red[2][k]) + red[3][k];
-  __syncthreads();
+    for (int w = 1; w < 4; ++w) stats_add(s, red[w]);
 }
 
 __global__ void __launch_bounds__(256)
-k_stats_pass(const float* __restrict__ x, const float* __restrict__ t, int64_t n, const double* __restrict__ mean,
-             double* __restrict__ part) {
-  double acc[11];
+k_stats_pass(const float* __restrict__ x, const float* __restrict__ t, int64_t n, Stats* __restrict__ part) {
+  Stats s;
+  double ref[7], dev[7];
+  s.n = 0.0;
 #pragma unroll
-  for (int k = 0; k < 11; ++k) acc[k] = 0.0;
+  for (int f = 0; f < 7; ++f) s.sum[f] = s.mean[f] = s.m2[f] = ref[f] = dev[f] = 0.0;
+#pragma unroll
+  for (int o = 0; o < 4; ++o) s.t2[o] = 0.0;
   const int64_t stride = (int64_t)gridDim.x * 256;
-  for (int64_t r = (int64_t)blockIdx.x * 256 + threadIdx.x; r < n; r += stride) {
+  const int64_t r0 = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  for (int64_t r = r0; r < n; r += stride) {
+    const f32x4 tv = *reinterpret_cast<const f32x4*>(t + r * 4);
 #pragma unroll
     for (int f = 0; f < 7; ++f) {
       const double v = x[r * 64 + f * 9 + 4];
-      if (mean) {
-        const double d = v - mean[f];
-        acc[f] += d * d;
-      } else {
-        acc[f] += v;
-      }
+      if (r == r0) ref[f] = isfinite(v) ? v : 0.0;
+      const double d = v - ref[f];
+      s.sum[f] += v;
+      dev[f] += d;
+      s.m2[f] += d * d;
     }
-    if (!mean)
 #pragma unroll
-      for (int o = 0; o < 4; ++o) {
-        const double v = t[r * 4 + o];
-        acc[7 + o] += v * v;
-      }
+    for (int o = 0; o < 4; ++o) s.t2[o] += double(tv[o]) * double(tv[o]);
+    s.n += 1.0;
   }
-  block_sum11(acc, part + (int64_t)blockIdx.x * 11);
+  if (s.n != 0.0) {
+#pragma unroll
+    for (int f = 0; f < 7; ++f) {
+      const double d = dev[f] / s.n;
+      s.mean[f] = ref[f] + d;
+      s.m2[f] -= dev[f] * d;
+    }
+  }
+  block_stats(s);
+  if (threadIdx.x == 0) part[blockIdx.x] = s;
 }
 
-// mode 0: partial sums -> means (mean[0..6]) and target RMS; mode 1:
-// squared deviations -> norm.
-__global__ void __launch_bounds__(64)
-k_stats_final(const double* __restrict__ part, int nparts, int64_t n, double* __restrict__ mean, int mode,
-              lbm_mlp_norm* __restrict__ norm) {
-  if (threadIdx.x != 0) return;
-  double s[11];
-  for (int k = 0; k < 11; ++k) s[k] = 0.0;
-  for (int b = 0; b < nparts; ++b)
-    for (int k = 0; k < 11; ++k) s[k] += part[(int64_t)b * 11 + k];
-  const double dn = double(n);
-  if (mode == 0) {
-    for (int f = 0; f < 7; ++f) mean[f] = s[f] / dn;
-    for (int o = 0; o < 4; ++o) mean[7 + o] = sqrt(s[7 + o] / dn);
-    return;
+// Statistics of the whole -> normalisation.
+__global__ void __launch_bounds__(256)
+k_stats_final(const Stats* __restrict__ part, int nparts, lbm_mlp_norm* __restrict__ norm) {
+  Stats s;
+  if (threadIdx.x < nparts) {
+    s = part[threadIdx.x];
+  } else {
+    double* z = reinterpret_cast<double*>(&s);
+#pragma unroll
+    for (int k = 0; k < kStatVals; ++k) z[k] = 0.0;
   }
+  block_stats(s);
+  if (threadIdx.x != 0) return;
   lbm_mlp_norm nm;
   for (int k = 0; k < 8; ++k) {
     nm.shift[k] = 0.0f;
     nm.scale[k] = 1.0f;
   }
+#pragma unroll
   for (int f = 0; f < 7; ++f) {
-    const double sd = sqrt(s[f] / dn);
-    nm.shift[f] = float(mean[f]);
+    const double sd = sqrt(s.m2[f] / s.n);
+    nm.shift[f] = float(s.sum[f] / s.n);
     nm.scale[f] = sd > 0.0 ? float(1.0 / sd) : 1.0f;
   }
-  for (int o = 0; o < 4; ++o) nm.out_scale[o] = mean[7 + o] > 0.0 ? float(mean[7 + o]) : 1.0f;
+#pragma unroll
+  for (int o = 0; o < 4; ++o) {
+    const double rms = sqrt(s.t2[o] / s.n);
+    nm.out_scale[o] = rms > 0.0 ? float(rms) : 1.0f;
+  }
   for (int k = 0; k < 12; ++k) nm.pad[k] = 0.0f;
   *norm = nm;
 }
@@ -912,8 +987,10 @@ hipError_t launch_mlp_pack(const float* params, const lbm_mlp_norm* norm, void* 
 hipError_t launch_mlp_forward(const void* packed, const float* x, int64_t n, float* y, int32_t* ood, hipStream_t st) {
   if (n == 0) return hipSuccess;
   const int64_t groups = (n + 31) / 32;
+  // two workgroups fit a compute unit (its registers hold the weights); more
+  // would only load the weights again
   int64_t blocks = (groups + 3) / 4;
-  if (blocks > 4096) blocks = 4096;
+  if (blocks > 512) blocks = 512;
   hipLaunchKernelGGL(k_mlp_forward, dim3((unsigned)blocks), dim3(256), 0, st, static_cast<const char*>(packed), x, n,
                      y, ood);
   return hipGetLastError();
@@ -1004,22 +1081,17 @@ hipError_t launch_mlp_train_noalloc(float* params, float* m, float* v, int64_t s
   return launch_mlp_train(params, m, v, step, lr, norm, x, t, idx, batch, work, loss, st);
 }
 
-size_t mlp_stats_work_bytes() { return (size_t)(kStatBlocks * 11 + 16) * sizeof(double); }
+size_t mlp_stats_work_bytes() { return kStatBlocks * sizeof(Stats); }
 
 hipError_t launch_mlp_stats(const float* x, const float* t, int64_t n, lbm_mlp_norm* norm, void* work,
                             hipStream_t st) {
-  double* part = static_cast<double*>(work);
-  double* mean = part + kStatBlocks * 11;
-  int64_t want = (n + 255) / 256;
+  Stats* part = static_cast<Stats*>(work);
+  const int64_t want = (n + 255) / 256;
   const int blocks = int(want < kStatBlocks ? want : kStatBlocks);
-  hipLaunchKernelGGL(k_stats_pass, dim3(blocks), dim3(256), 0, st, x, t, n, (const double*)nullptr, part);
-  hipError_t e = hipGetLastError();
+  hipLaunchKernelGGL(k_stats_pass, dim3(blocks), dim3(256), 0, st, x, t, n, part);
+  const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_stats_final, dim3(1), dim3(64), 0, st, part, blocks, n, mean, 0, norm);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  hipLaunchKernelGGL(k_stats_pass, dim3(blocks), dim3(256), 0, st, x, t, n, (const double*)mean, part);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  hipLaunchKernelGGL(k_stats_final, dim3(1), dim3(64), 0, st, part, blocks, n, mean, 1, norm);
+  hipLaunchKernelGGL(k_stats_final, dim3(1), dim3(256), 0, st, part, blocks, norm);
   return hipGetLastError();
 }
 

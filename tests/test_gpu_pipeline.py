@@ -134,3 +134,41 @@ def test_diagnostics_counts_a_bad_cell(x, y):
     s.set_state(st)
     d = s.diagnostics()
     assert d["nonfinite"] == 1 and np.isnan(d["mass"])
+
+
+@pytest.mark.parametrize("n", [2, 255, 257, 1000, 65535, 65537, 200003])
+def test_feature_stats_rows(n):
+    """Row counts around the thread, workgroup and grid sizes, with columns whose mean
+    is 1e4 spreads, whose first row is an outlier, and that are constant.  FP64
+    statistics rounded to FP32: two FP32 roundings (2.4e-7) against numpy's."""
+    G = _gpu()
+    r = np.random.default_rng(n)
+    X = r.standard_normal((n, 64)).astype(np.float32)
+    X[:, 4] = (1.0 + 1e-4 * X[:, 4]).astype(np.float32)
+    X[0, 13] = 3e4
+    X[:, 22] = 0.1
+    X[:, 63] = 0
+    T = (1e-6 * r.standard_normal((n, 4))).astype(np.float32)
+    T[:, 3] = 0
+    m = G.Mlp(G.glorot_params(1))
+    m.fit_norm(torch.from_numpy(X).cuda(), torch.from_numpy(T).cuda())
+    nm = m.norm.cpu().numpy()
+    c = X[:, 4:63:9].astype(np.float64)
+    mean, sd = c.mean(0), c.std(0)
+    assert np.all(np.abs(nm[:7] - mean) <= 2.4e-7 * np.abs(mean) + 1e-12)
+    for f in (0, 1, 3, 4, 5, 6):
+        assert abs(nm[8 + f] * sd[f] - 1) <= 2.4e-7, f
+    assert nm[10] == 1.0 and nm[15] == 1.0
+    rms = np.sqrt((T.astype(np.float64) ** 2).mean(0))
+    assert np.all(np.abs(nm[16:19] - rms[:3]) <= 2.4e-7 * rms[:3]) and nm[19] == 1.0
+
+
+def test_feature_stats_of_an_infinite_column():
+    G = _gpu()
+    X = np.random.default_rng(1).standard_normal((3000, 64)).astype(np.float32)
+    X[0, 31] = np.inf
+    m = G.Mlp(G.glorot_params(1))
+    m.fit_norm(torch.from_numpy(X).cuda(), torch.zeros(3000, 4, device="cuda"))
+    nm = m.norm.cpu().numpy()
+    assert nm[3] == np.inf and nm[11] == 1.0
+    assert np.isfinite(np.delete(nm[:20], 3)).all()
