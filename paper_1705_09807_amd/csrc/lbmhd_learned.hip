@@ -80,9 +80,9 @@ typedef __attribute__((address_space(1))) void global_void;
 
 // Layer-1 operand kb of lane half h from the eight features u, v at kb*16 + h*8
 // (FP32): z = (x - shift) * scale per field, pad 0, rounded to bfloat16.  Sets
-// *ood when any |z| exceeds the limit; zf (may be null) receives the rounded values.
+// *ood when any |z| exceeds the limit.
 __device__ __forceinline__ void feature_operands(const f32x4& u, const f32x4& v, int kb, int h, const lbm_mlp_norm* nm,
-                                                 bf16x8& zb, bool* ood, float* zf) {
+                                                 bf16x8& zb, bool* ood) {
 #pragma unroll
   for (int j = 0; j < 8; ++j) {
     const int k = kb * 16 + h * 8 + j;
@@ -94,18 +94,6 @@ __device__ __forceinline__ void feature_operands(const f32x4& u, const f32x4& v,
     }
     *ood = *ood || !(fabsf(z) <= kOodLimit);  // NaN counts as out of range
     zb[j] = __bf16(z);
-    if (zf) zf[j] = float(zb[j]);
-  }
-}
-
-// Layer-1 operands of this lane from feature row `row` of x.
-__device__ __forceinline__ void row_operands(const float* __restrict__ x, int64_t row, const lbm_mlp_norm* nm,
-                                             int h, bf16x8 zb[4], bool* ood, float* zf) {
-  *ood = false;
-#pragma unroll
-  for (int kb = 0; kb < 4; ++kb) {
-    const f32x4* src = reinterpret_cast<const f32x4*>(x + row * 64 + kb * 16 + h * 8);
-    feature_operands(src[0], src[1], kb, h, nm, zb[kb], ood, zf ? zf + kb * 8 : nullptr);
   }
 }
 
@@ -150,7 +138,7 @@ k_mlp_forward(const char* __restrict__ pk, const float* __restrict__ x, int64_t 
     bf16x8 zb[4];
     bool o = false;
 #pragma unroll
-    for (int kb = 0; kb < 4; ++kb) feature_operands(in[2 * kb], in[2 * kb + 1], kb, h, nm, zb[kb], &o, nullptr);
+    for (int kb = 0; kb < 4; ++kb) feature_operands(in[2 * kb], in[2 * kb + 1], kb, h, nm, zb[kb], &o);
     const f32x4 v = mlp_wave(w, zb, reinterpret_cast<const float*>(pk + kPkB1), lane, nullptr, nullptr);
     // every lane takes part in the exchange (a short-circuit would leave the
     // flagged lane inactive and its partner would read nothing from it)
@@ -254,8 +242,8 @@ k_mlp_correct(const CellIn* __restrict__ in, const char* __restrict__ pk, float*
 }
 
 // ---------------------------------------------------------------------------
-// Training: forward and backward on the matrix cores.  A workgroup of two
-// waves takes chunks of 64 batch rows (32 per wave in the forward).  With the
+// Training: forward and backward on the matrix cores.  A workgroup takes chunks
+// of 64 batch rows (32 per wave in the forward).  With the
 // batch row r, the loss L = sum (y - t)^2 / (4 batch) and straight-through
 // gradients of the bfloat16 roundings:
 //   d3 = dL/dy,  d2 = (d3 W3^T) [h2 > 0],  d1 = (d2 W2^T) [h1 > 0],
@@ -268,9 +256,9 @@ k_mlp_correct(const CellIn* __restrict__ in, const char* __restrict__ pk, float*
 // cores as three bfloat16 terms, d = hi + mid + lo + O(2^-25 |d|), so the
 // products carry the FP32 delta; activations and weights are bfloat16
 // already.  (Two terms, 16 bits, left 1e-4 relative errors in G1 over 5000
-// rows, where the row sums cancel.)  Each wave owns half of every weight gradient and accumulates it
-// over its workgroup's chunks in a fixed order; per-workgroup partials are
-// summed in a fixed order by k_mlp_reduce_groups and k_mlp_reduce.
+// rows, where the row sums cancel.)  Each wave owns half of a weight gradient and
+// accumulates it over its workgroup's chunks in a fixed order; per-workgroup
+// partials are summed in a fixed order by k_mlp_reduce.
 // ---------------------------------------------------------------------------
 constexpr int kTrainChunk = 64;
 constexpr int kTrainBlocksMax = 1024;
@@ -280,10 +268,12 @@ constexpr int kTs = 72;            // bfloat16 per feature row of an LDS tile (6
 struct TrainLds {
   __bf16 z[64][kTs], h1[64][kTs], h2[64][kTs];     // [feature][chunk row]
   __bf16 d2h[64][kTs], d2m[64][kTs], d2l[64][kTs], d1h[64][kTs], d1m[64][kTs], d1l[64][kTs];
+  bf16x8 a1[2][4][64], a2[2][4][64], a3[4][64];    // A operands of the forward
   bf16x8 a2b[2][4][64];                            // A operands of d1^T = W2 d2^T
   float d3[4][kTrainChunk];
   float w3[64 * 4];                                // bfloat16-rounded W3
-  double loss[128];
+  float bias[64 + 64 + 4];
+  double loss[64];
 };
 
 // hi + mid + lo bfloat16 split of eight floats (each remainder is exact in
@@ -332,53 +322,95 @@ __device__ __forceinline__ void activate_to_lds(const f32x16 acc[2], bf16x8 hb[4
     for (int j = 0; j < 8; ++j) dst[chained_k(kb, h, j)][sl] = hb[kb][j];
 }
 
-__global__ void __launch_bounds__(128)
-k_mlp_train(const char* __restrict__ pk, const float* __restrict__ p, const float* __restrict__ x,
+__device__ __forceinline__ void adam_update(int i, float g, float* __restrict__ p, float* __restrict__ m,
+                                            float* __restrict__ v, float lr, float bc1, float bc2) {
+  const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
+  const float mi = b1 * m[i] + (1.0f - b1) * g;
+  const float vi = b2 * v[i] + (1.0f - b2) * g * g;
+  m[i] = mi;
+  v[i] = vi;
+  p[i] -= lr * (mi / bc1) / (sqrtf(vi / bc2) + eps);
+}
+
+// Four waves per workgroup: all of them round the weights into operands (straight
+// from the FP32 parameters); waves 0 and 1 run the forward pass of 32 rows each
+// while 2 and 3 prepare the backward operands; in the backward pass wave w forms
+// half w / 2 of d1 for the rows of half w % 2, and then two 32 x 32 tiles of one weight
+// gradient.  A chain of dependent phases, too short for the chip to fill: bound by
+// their latencies.  Measured, batch 4096 (64 workgroups): two waves reading
+// operands packed by a launch of their own, 3.7 + 17.9 us; this form 16.1 us.
+__global__ void __launch_bounds__(256)
+k_mlp_train(const float* __restrict__ p, const lbm_mlp_norm* __restrict__ nm, const float* __restrict__ x,
             const float* __restrict__ t, const int32_t* __restrict__ idx, int batch, float* __restrict__ partial,
             double* __restrict__ loss_part) {
   __shared__ TrainLds s;
-  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6, h = lane >> 5;
-  const lbm_mlp_norm* nm = reinterpret_cast<const lbm_mlp_norm*>(pk + kPkNorm);
-  const float* b1 = reinterpret_cast<const float*>(pk + kPkB1);
-  const float* b2 = reinterpret_cast<const float*>(pk + kPkB2);
-  const float* b3 = reinterpret_cast<const float*>(pk + kPkB3);
-  const bf16x8* pa1 = reinterpret_cast<const bf16x8*>(pk + kPkA1);
-  const bf16x8* pa2 = reinterpret_cast<const bf16x8*>(pk + kPkA2);
-  const bf16x8* pa3 = reinterpret_cast<const bf16x8*>(pk + kPkA3);
-  // A operands of d1^T = W2 d2^T: row i = ot*32 + lane%32 of W2, contraction
-  // index j in the chained order of the accumulator layout
-  for (int e = tid; e < 2 * 4 * 64; e += 128) {
-    const int ot = e / 256, kb = (e / 64) % 4, l = e % 64;
-    bf16x8 v;
+  const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5;
+  const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const float *b1 = s.bias, *b2 = s.bias + 64, *b3 = s.bias + 128;
+  const int half = wid & 1, part = wid >> 1;       // rows and work of this wave
+  const int sl = half * 32 + (lane & 31);          // chunk row of this lane
+  const int chunks = (batch + kTrainChunk - 1) / kTrainChunk;
+  // this lane's eight 16-byte pieces of its row of a chunk and the row's targets,
+  // asked for before anything else needs them (the first chunk's during the weights)
+  f32x4 in[8], tv;
+  auto fetch = [&](int c) __attribute__((always_inline)) {
+    const int64_t row = idx[min(c * kTrainChunk + sl, batch - 1)];
 #pragma unroll
-    for (int j = 0; j < 8; ++j)
-      v[j] = __bf16(p[LBM_MLP_OFF_W2 + (ot * 32 + (l & 31)) * 64 + chained_k(kb, l >> 5, j)]);
-    s.a2b[ot][kb][l] = v;
+    for (int k = 0; k < 8; ++k)
+      in[k] = *reinterpret_cast<const f32x4*>(x + row * 64 + (k >> 1) * 16 + h * 8 + (k & 1) * 4);
+    tv = *reinterpret_cast<const f32x4*>(t + row * 4);
+  };
+  if (part == 0) fetch(blockIdx.x);
+  if (tid >= 128 && tid < 192) s.bias[tid - 128] = p[LBM_MLP_OFF_B1 + tid - 128];
+  if (tid >= 192) s.bias[tid - 128] = p[LBM_MLP_OFF_B2 + tid - 192];
+  if (tid >= 128 && tid < 132) s.bias[tid] = p[LBM_MLP_OFF_B3 + tid - 128];
+  // A operands of the forward (the order of lbm_mlp_pack): W1^T, W2^T in the chained
+  // contraction order, W3^T rows 0 .. 3
+  for (int e = wid; e < 20; e += 4) {
+    bf16x8 v;
+    if (e < 8) {
+      const int ot = e >> 2, kb = e & 3;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const int k = kb * 16 + h * 8 + j;
+        v[j] = __bf16(k < 63 ? p[LBM_MLP_OFF_W1 + k * 64 + ot * 32 + (lane & 31)] : 0.0f);
+      }
+      s.a1[ot][kb][lane] = v;
+    } else if (e < 16) {
+      const int ot = (e - 8) >> 2, kb = e & 3;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) v[j] = __bf16(p[LBM_MLP_OFF_W2 + chained_k(kb, h, j) * 64 + ot * 32 + (lane & 31)]);
+      s.a2[ot][kb][lane] = v;
+    } else {
+      const int kb = e - 16, o = lane & 31;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) v[j] = __bf16(o < 4 ? p[LBM_MLP_OFF_W3 + chained_k(kb, h, j) * 4 + (o & 3)] : 0.0f);
+      s.a3[kb][lane] = v;
+    }
   }
-  for (int e = tid; e < 256; e += 128) s.w3[e] = bf16_round(p[LBM_MLP_OFF_W3 + e]);
-  // gradient accumulators: wave wid owns rows [32 wid, 32 wid + 32) of G1 and
-  // G2 (two 32 x 32 tiles each, columns 0..31 and 32..63); thread tid owns two
-  // entries of G3 and one bias entry of b1 (tid >= 64) or b2 (tid < 64)
-  f32x16 g1[2], g2[2];
+  // gradient accumulators: waves 0 and 1 own rows [32 half, 32 half + 32) of G2,
+  // waves 2 and 3 those of G1 (two 32 x 32 tiles each, columns 0..31 and 32..63);
+  // thread tid owns an entry of G3, threads 0..63 one of b2's, 64..127 one of b1's
+  // and 128..131 one of b3's bias gradients
+  f32x16 gw[2];
 #pragma unroll
   for (int c = 0; c < 2; ++c)
 #pragma unroll
-    for (int e = 0; e < 16; ++e) g1[c][e] = g2[c][e] = 0.0f;
-  float g3a = 0.0f, g3b = 0.0f, gb = 0.0f, gb3 = 0.0f;
+    for (int e = 0; e < 16; ++e) gw[c][e] = 0.0f;
+  float g3 = 0.0f, gb = 0.0f;
   double loss = 0.0;
   const float inv = 2.0f / (float(batch) * 4.0f);
-  const int chunks = (batch + kTrainChunk - 1) / kTrainChunk;
-  const int sl = wid * 32 + (lane & 31);           // chunk row of this lane
+  __syncthreads();
   for (int c = blockIdx.x; c < chunks; c += gridDim.x) {
-    const int b = c * kTrainChunk + sl;
-    const bool valid = b < batch;
-    // forward (the operations of mlp_wave), activations to LDS
-    {
-      const int64_t row = idx[valid ? b : batch - 1];
+    if (part == 0) {
+      // forward (the operations of mlp_wave), activations to LDS
+      const bool valid = c * kTrainChunk + sl < batch;
       bf16x8 zb[4];
-      float zf[32];
-      bool o;
-      row_operands(x, row, nm, h, zb, &o, zf);
+      bool o = false;
+#pragma unroll
+      for (int kb = 0; kb < 4; ++kb) feature_operands(in[2 * kb], in[2 * kb + 1], kb, h, nm, zb[kb], &o);
+      const f32x4 target = tv;
+      if (c + int(gridDim.x) < chunks) fetch(c + gridDim.x);
 #pragma unroll
       for (int kb = 0; kb < 4; ++kb)
 #pragma unroll
@@ -390,7 +422,7 @@ k_mlp_train(const char* __restrict__ pk, const float* __restrict__ p, const floa
         acc[ot] = bias_tile(b1, ot, h);
 #pragma unroll
         for (int kb = 0; kb < 4; ++kb)
-          acc[ot] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pa1[(ot * 4 + kb) * 64 + lane], zb[kb], acc[ot], 0, 0, 0);
+          acc[ot] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(s.a1[ot][kb][lane], zb[kb], acc[ot], 0, 0, 0);
       }
       activate_to_lds(acc, hb, s.h1, h, sl);
 #pragma unroll
@@ -398,7 +430,7 @@ k_mlp_train(const char* __restrict__ pk, const float* __restrict__ p, const floa
         acc[ot] = bias_tile(b2, ot, h);
 #pragma unroll
         for (int kb = 0; kb < 4; ++kb)
-          acc[ot] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pa2[(ot * 4 + kb) * 64 + lane], hb[kb], acc[ot], 0, 0, 0);
+          acc[ot] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(s.a2[ot][kb][lane], hb[kb], acc[ot], 0, 0, 0);
       }
       activate_to_lds(acc, hb, s.h2, h, sl);
       f32x16 out;
@@ -410,19 +442,31 @@ k_mlp_train(const char* __restrict__ pk, const float* __restrict__ p, const floa
       }
 #pragma unroll
       for (int kb = 0; kb < 4; ++kb)
-        out = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pa3[kb * 64 + lane], hb[kb], out, 0, 0, 0);
+        out = __builtin_amdgcn_mfma_f32_32x32x16_bf16(s.a3[kb][lane], hb[kb], out, 0, 0, 0);
       if (h == 0) {
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-          const float r = out[q] - t[row * 4 + q] / nm->out_scale[q];
+          const float r = out[q] - target[q] / nm->out_scale[q];
           s.d3[q][sl] = valid ? inv * r : 0.0f;
           if (valid) loss += double(r) * double(r);
         }
       }
+    } else if (c == blockIdx.x) {
+      // A operands of d1^T = W2 d2^T: row i = ot*32 + lane%32 of W2, contraction
+      // index j in the chained order of the accumulator layout
+      for (int e = half; e < 8; e += 2) {
+        const int ot = e >> 2, kb = e & 3;
+        bf16x8 v;
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+          v[j] = __bf16(p[LBM_MLP_OFF_W2 + (ot * 32 + (lane & 31)) * 64 + chained_k(kb, h, j)]);
+        s.a2b[ot][kb][lane] = v;
+      }
+      for (int e = tid - 128; e < 256; e += 128) s.w3[e] = bf16_round(p[LBM_MLP_OFF_W3 + e]);
     }
     __syncthreads();
     // d2 in the accumulator layout of h2 (element kb*8 + j: hidden
-    // chained_k(kb, h, j)), then d1^T = W2 d2^T on the matrix cores
+    // chained_k(kb, h, j)), then half `part` of d1^T = W2 d2^T
     {
       float d3v[4];
 #pragma unroll
@@ -439,67 +483,83 @@ k_mlp_train(const char* __restrict__ pk, const float* __restrict__ p, const floa
           d2[j] = float(s.h2[ck][sl]) > 0.0f ? a : 0.0f;
         }
         split_bf16x8(d2, dh[kb], dm[kb], dl[kb]);
+        if ((kb >> 1) == part) {  // both waves of these rows have it: each stores half
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          const int ck = chained_k(kb, h, j);
-          s.d2h[ck][sl] = dh[kb][j];
-          s.d2m[ck][sl] = dm[kb][j];
-          s.d2l[ck][sl] = dl[kb][j];
+          for (int j = 0; j < 8; ++j) {
+            const int ck = chained_k(kb, h, j);
+            s.d2h[ck][sl] = dh[kb][j];
+            s.d2m[ck][sl] = dm[kb][j];
+            s.d2l[ck][sl] = dl[kb][j];
+          }
         }
       }
+      const int ot = part;
+      f32x16 acc;
 #pragma unroll
-      for (int ot = 0; ot < 2; ++ot) {
-        f32x16 acc;
+      for (int e = 0; e < 16; ++e) acc[e] = 0.0f;
 #pragma unroll
-        for (int e = 0; e < 16; ++e) acc[e] = 0.0f;
+      for (int kb = 0; kb < 4; ++kb) {
+        const bf16x8 a = s.a2b[ot][kb][lane];
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, dh[kb], acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, dm[kb], acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, dl[kb], acc, 0, 0, 0);
+      }
 #pragma unroll
-        for (int kb = 0; kb < 4; ++kb) {
-          const bf16x8 a = s.a2b[ot][kb][lane];
-          acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, dh[kb], acc, 0, 0, 0);
-          acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, dm[kb], acc, 0, 0, 0);
-          acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, dl[kb], acc, 0, 0, 0);
+      for (int q = 0; q < 2; ++q) {
+        float d1[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          const int hid = ot * 32 + acc_row(q * 8 + j, h);
+          d1[j] = float(s.h1[hid][sl]) > 0.0f ? acc[q * 8 + j] : 0.0f;
         }
+        bf16x8 hi, mi, lo;
+        split_bf16x8(d1, hi, mi, lo);
 #pragma unroll
-        for (int half = 0; half < 2; ++half) {
-          float d1[8];
-#pragma unroll
-          for (int j = 0; j < 8; ++j) {
-            const int hid = ot * 32 + acc_row(half * 8 + j, h);
-            d1[j] = float(s.h1[hid][sl]) > 0.0f ? acc[half * 8 + j] : 0.0f;
-          }
-          bf16x8 hi, mi, lo;
-          split_bf16x8(d1, hi, mi, lo);
-#pragma unroll
-          for (int j = 0; j < 8; ++j) {
-            const int hid = ot * 32 + acc_row(half * 8 + j, h);
-            s.d1h[hid][sl] = hi[j];
-            s.d1m[hid][sl] = mi[j];
-            s.d1l[hid][sl] = lo[j];
-          }
+        for (int j = 0; j < 8; ++j) {
+          const int hid = ot * 32 + acc_row(q * 8 + j, h);
+          s.d1h[hid][sl] = hi[j];
+          s.d1m[hid][sl] = mi[j];
+          s.d1l[hid][sl] = lo[j];
         }
       }
     }
     __syncthreads();
     // weight gradients over the chunk's rows
 #pragma unroll
-    for (int cn = 0; cn < 2; ++cn) {
-      g2[cn] = rows_product(g2[cn], s.h1, s.d2h, s.d2m, s.d2l, wid * 32, cn * 32, lane);
-      g1[cn] = rows_product(g1[cn], s.z, s.d1h, s.d1m, s.d1l, wid * 32, cn * 32, lane);
-    }
+    for (int cn = 0; cn < 2; ++cn)
+      gw[cn] = part == 0 ? rows_product(gw[cn], s.h1, s.d2h, s.d2m, s.d2l, half * 32, cn * 32, lane)
+                         : rows_product(gw[cn], s.z, s.d1h, s.d1m, s.d1l, half * 32, cn * 32, lane);
     {
-      // G3[j][o] for j = tid / 2, o = 2 (tid % 2) + {0, 1}; bias of d1 or d2
-      const int j = tid >> 1, o = (tid & 1) * 2, bh = tid & 63;
-      const __bf16(*dh)[kTs] = tid < 64 ? s.d2h : s.d1h;
-      const __bf16(*dm)[kTs] = tid < 64 ? s.d2m : s.d1m;
-      const __bf16(*dl)[kTs] = tid < 64 ? s.d2l : s.d1l;
-      for (int r = 0; r < kTrainChunk; ++r) {
-        const float hv = float(s.h2[j][r]);
-        g3a += hv * s.d3[o][r];
-        g3b += hv * s.d3[o + 1][r];
-        gb += (float(dh[bh][r]) + float(dm[bh][r])) + float(dl[bh][r]);
+      // G3[tid / 4][tid % 4]; biases
+      const bf16x8* hv = reinterpret_cast<const bf16x8*>(s.h2[tid >> 2]);
+      const f32x4* dv = reinterpret_cast<const f32x4*>(s.d3[tid & 3]);
+#pragma unroll
+      for (int r = 0; r < kTrainChunk / 8; ++r) {
+        const bf16x8 a = hv[r];
+        const f32x4 u = dv[2 * r], v = dv[2 * r + 1];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) g3 += float(a[j]) * (j < 4 ? u[j & 3] : v[j & 3]);
       }
-      if (tid < 4)
-        for (int r = 0; r < kTrainChunk; ++r) gb3 += s.d3[tid][r];
+    }
+    if (part == 0) {
+      const int bh = lane;
+      const bf16x8* ph = reinterpret_cast<const bf16x8*>(half == 0 ? s.d2h[bh] : s.d1h[bh]);
+      const bf16x8* pm = reinterpret_cast<const bf16x8*>(half == 0 ? s.d2m[bh] : s.d1m[bh]);
+      const bf16x8* pl = reinterpret_cast<const bf16x8*>(half == 0 ? s.d2l[bh] : s.d1l[bh]);
+#pragma unroll
+      for (int r = 0; r < kTrainChunk / 8; ++r) {
+        const bf16x8 a = ph[r], m = pm[r], l = pl[r];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) gb += (float(a[j]) + float(m[j])) + float(l[j]);
+      }
+    } else if (tid < 132) {
+      const f32x4* dv = reinterpret_cast<const f32x4*>(s.d3[tid - 128]);
+#pragma unroll
+      for (int r = 0; r < kTrainChunk / 4; ++r) {
+        const f32x4 v = dv[r];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) gb += v[j];
+      }
     }
     __syncthreads();
   }
@@ -508,83 +568,85 @@ k_mlp_train(const char* __restrict__ pk, const float* __restrict__ p, const floa
   for (int cn = 0; cn < 2; ++cn)
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
-      const int m = wid * 32 + acc_row(e, h), n = cn * 32 + (lane & 31);
-      out[LBM_MLP_OFF_W1 + m * 64 + n] = g1[cn][e];
-      out[LBM_MLP_OFF_W2 + m * 64 + n] = g2[cn][e];
+      const int m = half * 32 + acc_row(e, h), n = cn * 32 + (lane & 31);
+      out[(part == 0 ? LBM_MLP_OFF_W2 : LBM_MLP_OFF_W1) + m * 64 + n] = gw[cn][e];
     }
-  out[LBM_MLP_OFF_W3 + (tid >> 1) * 4 + (tid & 1) * 2] = g3a;
-  out[LBM_MLP_OFF_W3 + (tid >> 1) * 4 + (tid & 1) * 2 + 1] = g3b;
-  out[(tid < 64 ? LBM_MLP_OFF_B2 : LBM_MLP_OFF_B1) + (tid & 63)] = gb;
-  if (tid < 4) out[LBM_MLP_OFF_B3 + tid] = gb3;
+  out[LBM_MLP_OFF_W3 + tid] = g3;
+  if (part == 0)
+    out[(half == 0 ? LBM_MLP_OFF_B2 : LBM_MLP_OFF_B1) + lane] = gb;
+  else if (tid < 132)
+    out[LBM_MLP_OFF_B3 + tid - 128] = gb;
   // loss: fixed-order sum over the lanes that hold outputs
-  s.loss[tid] = loss;
+  if (part == 0 && h == 0) s.loss[sl] = loss;
   __syncthreads();
   if (tid == 0) {
     double a = 0.0;
-    for (int k = 0; k < 128; ++k) a += s.loss[k];
+    for (int k = 0; k < 64; ++k) a += s.loss[k];
     loss_part[blockIdx.x] = a;
   }
 }
 
-// Sum of the partial gradients (and of the loss partials) in a fixed order,
-// in two launches so that the loads of many partials are in flight at once:
-// each run of kReduceGroup consecutive partials is summed in order into its
-// first partial (k_mlp_reduce_groups), then those group sums in order
-// (k_mlp_reduce).  (One thread summing all partials in order, one launch,
-// waited on each batch of loads: 34 us for 128 partials.)
+// Sum of the partial gradients (and of the loss partials) in a fixed order: each
+// run of kReduceGroup consecutive partials in order, then the runs' sums in order;
+// with ADAM the update follows (Kingma & Ba 2015, bias corrections bc1 = 1 -
+// beta1^t, bc2 = 1 - beta2^t).  A workgroup takes 64 parameters, a wave a run at a
+// time, so the loads of many partials are in flight at once.  Measured, 64 partials: three
+// launches (runs, their sum, the update) 4.1 + 3.0 + 2.3 us, this one 3.9 us.
 constexpr int kReduceGroup = 16;
 
-__global__ void __launch_bounds__(256)
-k_mlp_reduce_groups(float* __restrict__ partial, int nparts, double* __restrict__ loss_part) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  const int b0 = blockIdx.y * kReduceGroup;
-  const int nb = min(kReduceGroup, nparts - b0);
-  if (i < LBM_MLP_PARAMS) {
-    float v[kReduceGroup];
-#pragma unroll
-    for (int k = 0; k < kReduceGroup; ++k) v[k] = k < nb ? partial[(int64_t)(b0 + k) * kGradStride + i] : 0.0f;
-    float g = v[0];
-#pragma unroll
-    for (int k = 1; k < kReduceGroup; ++k)
-      if (k < nb) g += v[k];
-    partial[(int64_t)b0 * kGradStride + i] = g;
-  }
-  if (blockIdx.x == 0 && threadIdx.x == 0 && loss_part) {
-    double a = loss_part[b0];
-    for (int k = 1; k < nb; ++k) a += loss_part[b0 + k];
-    loss_part[b0] = a;
-  }
-}
-
+template <bool ADAM>
 __global__ void __launch_bounds__(256)
 k_mlp_reduce(const float* __restrict__ partial, int nparts, float* __restrict__ grad,
-             const double* __restrict__ loss_part, float* __restrict__ loss_out, float loss_norm) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i < LBM_MLP_PARAMS) {
-    float g = 0.0f;
-    for (int b = 0; b < nparts; b += kReduceGroup) g += partial[(int64_t)b * kGradStride + i];
-    grad[i] = g;
+             const double* __restrict__ loss_part, float* __restrict__ loss_out, float loss_norm,
+             float* __restrict__ p, float* __restrict__ m, float* __restrict__ v, float lr, float bc1, float bc2) {
+  constexpr int kRuns = kTrainBlocksMax / kReduceGroup;
+  __shared__ float run[kRuns][64];
+  __shared__ double loss_run[kRuns];
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  const int i = blockIdx.x * 64 + lane;
+  const int runs = (nparts + kReduceGroup - 1) / kReduceGroup;
+  for (int g = wid; g < runs; g += 4) {
+    const int b0 = g * kReduceGroup, nb = min(kReduceGroup, nparts - b0);
+    if (i < LBM_MLP_PARAMS) {
+      float q[kReduceGroup];
+#pragma unroll
+      for (int k = 0; k < kReduceGroup; ++k) q[k] = k < nb ? partial[(int64_t)(b0 + k) * kGradStride + i] : 0.0f;
+      float a = q[0];
+#pragma unroll
+      for (int k = 1; k < kReduceGroup; ++k)
+        if (k < nb) a += q[k];
+      run[g][lane] = a;
+    }
   }
-  if (i == 0 && loss_out) {
+  const bool with_loss = blockIdx.x == 0 && loss_out;
+  if (with_loss && int(threadIdx.x) < runs) {
+    const int b0 = threadIdx.x * kReduceGroup, nb = min(kReduceGroup, nparts - b0);
+    double a = loss_part[b0];
+    for (int k = 1; k < nb; ++k) a += loss_part[b0 + k];
+    loss_run[threadIdx.x] = a;
+  }
+  __syncthreads();
+  if (wid == 0 && i < LBM_MLP_PARAMS) {
+    float g = 0.0f;
+    for (int k = 0; k < runs; ++k) g += run[k][lane];
+    if constexpr (ADAM) {
+      adam_update(i, g, p, m, v, lr, bc1, bc2);
+    } else {
+      grad[i] = g;
+    }
+  }
+  if (with_loss && threadIdx.x == 64) {
     double a = 0.0;
-    for (int b = 0; b < nparts; b += kReduceGroup) a += loss_part[b];
+    for (int k = 0; k < runs; ++k) a += loss_run[k];
     *loss_out = float(a * double(loss_norm));
   }
 }
 
-// Adam (Kingma & Ba 2015), bias corrections bc1 = 1 - beta1^t, bc2 = 1 - beta2^t.
 __global__ void __launch_bounds__(256)
 k_mlp_adam(float* __restrict__ p, float* __restrict__ m, float* __restrict__ v, const float* __restrict__ grad,
            float lr, float bc1, float bc2) {
   const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i >= LBM_MLP_PARAMS) return;
-  const float g = grad[i];
-  const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
-  const float mi = b1 * m[i] + (1.0f - b1) * g;
-  const float vi = b2 * v[i] + (1.0f - b2) * g * g;
-  m[i] = mi;
-  v[i] = vi;
-  p[i] -= lr * (mi / bc1) / (sqrtf(vi / bc2) + eps);
+  if (i < LBM_MLP_PARAMS) adam_update(i, grad[i], p, m, v, lr, bc1, bc2);
 }
 
 // ---------------------------------------------------------------------------
@@ -970,8 +1032,9 @@ static int train_blocks(int batch) {
   return chunks < kTrainBlocksMax ? chunks : kTrainBlocksMax;
 }
 
-// Work of a training step: packed network, per-workgroup partial gradients,
-// loss partials, the reduced gradient.
+// Work of a training step: per-workgroup partial gradients and loss partials (with
+// room for a packed network before and a reduced gradient after them, as callers
+// have sized it).
 size_t mlp_train_work_bytes(int batch) {
   const int blocks = train_blocks(batch);
   return (size_t)LBM_MLP_PACKED_BYTES + (size_t)blocks * kGradStride * sizeof(float) +
@@ -996,48 +1059,52 @@ hipError_t launch_mlp_forward(const void* packed, const float* x, int64_t n, flo
   return hipGetLastError();
 }
 
-hipError_t launch_mlp_gradient(const float* params, const lbm_mlp_norm* norm, const float* x, const float* t,
-                               const int32_t* idx, int batch, void* work, float* grad, float* loss, hipStream_t st) {
+struct AdamArgs {
+  float *p = nullptr, *m = nullptr, *v = nullptr;
+  float lr = 0, bc1 = 1, bc2 = 1;
+};
+static AdamArgs adam_args(float* params, float* m, float* v, int64_t step, double lr) {
+  return AdamArgs{params, m, v, float(lr), float(1.0 - pow(0.9, double(step))), float(1.0 - pow(0.999, double(step)))};
+}
+
+// Batch gradient into grad, or the Adam step with it.
+template <bool ADAM>
+static hipError_t launch_batch(const float* params, const lbm_mlp_norm* norm, const float* x, const float* t,
+                               const int32_t* idx, int batch, void* work, float* grad, float* loss, const AdamArgs& ad,
+                               hipStream_t st) {
   char* w = static_cast<char*>(work);
   const int blocks = train_blocks(batch);
   float* partial = reinterpret_cast<float*>(w + LBM_MLP_PACKED_BYTES);
   double* lpart = reinterpret_cast<double*>(w + LBM_MLP_PACKED_BYTES + (size_t)blocks * kGradStride * sizeof(float));
-  hipError_t e = launch_mlp_pack(params, norm, w, st);
+  hipLaunchKernelGGL(k_mlp_train, dim3(blocks), dim3(256), 0, st, params, norm, x, t, idx, batch, partial, lpart);
+  const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_mlp_train, dim3(blocks), dim3(128), 0, st, w, params, x, t, idx, batch, partial, lpart);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  hipLaunchKernelGGL(k_mlp_reduce_groups, dim3((LBM_MLP_PARAMS + 255) / 256, (blocks + kReduceGroup - 1) / kReduceGroup),
-                     dim3(256), 0, st, partial, blocks, lpart);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  hipLaunchKernelGGL(k_mlp_reduce, dim3((LBM_MLP_PARAMS + 255) / 256), dim3(256), 0, st, partial, blocks, grad, lpart,
-                     loss, float(1.0 / (double(batch) * 4.0)));
+  hipLaunchKernelGGL(k_mlp_reduce<ADAM>, dim3((LBM_MLP_PARAMS + 63) / 64), dim3(256), 0, st, partial, blocks, grad,
+                     lpart, loss, float(1.0 / (double(batch) * 4.0)), ad.p, ad.m, ad.v, ad.lr, ad.bc1, ad.bc2);
   return hipGetLastError();
+}
+
+hipError_t launch_mlp_gradient(const float* params, const lbm_mlp_norm* norm, const float* x, const float* t,
+                               const int32_t* idx, int batch, void* work, float* grad, float* loss, hipStream_t st) {
+  return launch_batch<false>(params, norm, x, t, idx, batch, work, grad, loss, AdamArgs{}, st);
 }
 
 hipError_t launch_mlp_adam(float* params, float* m, float* v, const float* grad, int64_t step, double lr,
                            hipStream_t st) {
-  const float bc1 = float(1.0 - pow(0.9, double(step)));
-  const float bc2 = float(1.0 - pow(0.999, double(step)));
-  hipLaunchKernelGGL(k_mlp_adam, dim3((LBM_MLP_PARAMS + 255) / 256), dim3(256), 0, st, params, m, v, grad, float(lr),
-                     bc1, bc2);
+  const AdamArgs ad = adam_args(params, m, v, step, lr);
+  hipLaunchKernelGGL(k_mlp_adam, dim3((LBM_MLP_PARAMS + 255) / 256), dim3(256), 0, st, params, m, v, grad, ad.lr,
+                     ad.bc1, ad.bc2);
   return hipGetLastError();
 }
 
 hipError_t launch_mlp_train(float* params, float* m, float* v, int64_t step, double lr, const lbm_mlp_norm* norm,
                             const float* x, const float* t, const int32_t* idx, int batch, void* work,
                             float* loss, hipStream_t st) {
-  const int blocks = train_blocks(batch);
-  float* grad = reinterpret_cast<float*>(static_cast<char*>(work) + LBM_MLP_PACKED_BYTES +
-                                         (size_t)blocks * kGradStride * sizeof(float) +
-                                         ((size_t)blocks * sizeof(double) + 255) / 256 * 256);
-  hipError_t e = launch_mlp_gradient(params, norm, x, t, idx, batch, work, grad, loss, st);
-  if (e != hipSuccess) return e;
-  return launch_mlp_adam(params, m, v, grad, step, lr, st);
+  return launch_batch<true>(params, norm, x, t, idx, batch, work, nullptr, loss, adam_args(params, m, v, step, lr), st);
 }
 
-// Training step without a caller-provided work buffer.  Its work (packed
-// network, per-workgroup partial gradients, loss partials, reduced gradient;
-// every byte the kernels read is written earlier in the same step, so nothing
+// Training step without a caller-provided work buffer.  Its work (per-workgroup
+// partial gradients, loss partials; every byte the kernels read is written earlier in the same step, so nothing
 // needs clearing) lives in this fixed device array, one copy per GPU that the
 // library runs on, held until the process ends.  In host code `scratch` names
 // a host-side stand-in, not device memory: kernels get the address that
