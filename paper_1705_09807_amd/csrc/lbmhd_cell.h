@@ -360,7 +360,7 @@ __device__ __forceinline__ void pull_pair(const S* __restrict__ src, int64_t pit
 
 template <typename S> using Vec4 = S __attribute__((ext_vector_type(4)));
 
-// Closure variants of the fused sweeps: see k_fused_les.
+// Closure variants of the fused sweeps: see k_fused_les_f.
 enum { kClosurePlain = 0, kClosureCorr = 1, kClosureFull = 2 };
 
 // A cell's populations as stored (16-bit values decoded where they are used).
@@ -382,7 +382,7 @@ __device__ __forceinline__ void decode_raw(const RawCell<S, QG>& c, C* v) {
 // lies inside it, except the stores of lanes that own no output column,
 // which take an offset past num_records: the hardware's range check drops
 // them, so the row body has no branch around its stores.  (nx <= 32768, as
-// lbm_create requires, keeps a lattice row below 27 * 32768 * 4 B = 3.5 MB
+// lbm_create requires, keeps a lattice row below 27 * 32768 * 8 B = 7 MB
 // and a row of input vectors at 512 KB, far below kDropOffset.)
 constexpr uint32_t kDropOffset = 0x80000000u;
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t row_rsrc(const void* base, uint32_t bytes) {

@@ -95,133 +95,6 @@ k_fused_dns(const S* __restrict__ src, S* __restrict__ dst, int nx, int ny, int6
   for (int q = 0; q < kPop<QG>; ++q) store<NT>(at(dst + q * pitch, rw.c, cl.c), encode<S>(v[q]));
 }
 
-// Closure on, FP64 (FP32 compute runs k_fused_les_f, the same schedule with
-// buffer addressing).  A workgroup of W + 64 lanes owns the column strip
-// x0 .. x0+W-1 and marches up rows y0 .. y0+ry-1.  The moments (m_x, m_y,
-// B_x - B_ref, B_y - B_ref) of the rows y-1 .. y+2 live in a 4-slot LDS ring
-// indexed by column - x0 + 1.  Lanes 0..W-1 gather, collide and store their
-// cells; one extra wave gathers the two halo columns (x0 - 1 and the column
-// after the strip's last cell), so no collision wave carries extra loads
-// (every wave of the workgroup waits at the per-row barrier for the slowest).
-// Rows are software-pipelined two deep: the loads of row y+2 are issued
-// before row y is collided.  A ring slot is rewritten only after the barrier
-// that follows its last read.
-//
-// MODE kClosureCorr: four FP32 planes (tau_xx, tau_xy, tau_yy, eps) of a
-// learned correction are added to the analytic subgrid terms of every cell.
-// MODE kClosureFull: the ring carries rho - rho0 as a fifth field and the
-// closure keeps the filtered-density gradient terms.
-
-template <typename S, typename C, int W, int STENCIL, bool NT, int MODE, int QG>
-__global__ void __launch_bounds__(W + 64)
-k_fused_les(const S* __restrict__ src, S* __restrict__ dst, int nx, int ny, int64_t pitch, int ry, Rates<C> r,
-            const float* __restrict__ corr) {
-  constexpr int NF = MODE == kClosureFull ? 5 : 4;
-  __shared__ C ring[4][NF][W + 2];
-  const int tid = threadIdx.x;
-  const bool halo_wave = tid >= W;
-  const int x0 = blockIdx.x * W;
-  const int last = min(x0 + W, nx) - 1;      // last column of this strip
-  const bool valid = !halo_wave && x0 + tid <= last;
-  const int hl = tid - W;                    // lane within the halo wave
-  const bool hlo = halo_wave && hl == 0;     // gathers the column left of the strip
-  const bool hhi = halo_wave && hl == 1;     // gathers the column right of the strip
-  const bool writer = valid || hlo || hhi;   // lanes that put moments into the ring
-  const bool loader = !halo_wave || hl < 2;
-  const int widx = hlo ? 0 : (hhi ? last - x0 + 2 : tid + 1);
-  const int xc = hlo ? (x0 == 0 ? nx - 1 : x0 - 1)
-                     : (hhi ? (last + 1 == nx ? 0 : last + 1) : (valid ? x0 + tid : last));
-  const Cols cx = cols_of<S>(xc, nx);        // idle lanes address a valid cell, never stored
-  const int y0 = blockIdx.y * ry;
-  const int y1 = min(y0 + ry, ny);
-
-  auto put = [&](int slot, const C* v) {
-    const Mom<C> m = moments_of<QG>(v);
-    ring[slot][0][widx] = m.mx;
-    ring[slot][1][widx] = m.my;
-    ring[slot][2][widx] = m.dbx;
-    ring[slot][3][widx] = m.dby;
-    if constexpr (NF == 5) ring[slot][4][widx] = m.drho;
-  };
-  auto wrapy = [&](int y) { return y < 0 ? y + ny : (y >= ny ? y - ny : y); };
-
-  C cur[kPop<QG>], nxt[kPop<QG>], nn[kPop<QG>];
-  if (loader) {
-    pull_cell<S, C, QG>(src, pitch, rows_of<S, QG>(wrapy(y0 - 1), ny, pitch), cx, nn);
-    if (writer) put(0, nn);
-    pull_cell<S, C, QG>(src, pitch, rows_of<S, QG>(y0, ny, pitch), cx, cur);
-    if (writer) put(1, cur);
-    pull_cell<S, C, QG>(src, pitch, rows_of<S, QG>(wrapy(y0 + 1), ny, pitch), cx, nxt);
-    if (writer) put(2, nxt);
-  }
-  __syncthreads();
-  {
-    // Rows rotated by copies.  The learned correction of row y + 1 is loaded
-    // with row y + 2's populations, a row ahead of its use.
-    const int64_t n = (int64_t)nx * ny;
-    float cc[4] = {0.0f, 0.0f, 0.0f, 0.0f}, cn[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-    auto load_corr = [&](int y, float (&c)[4]) __attribute__((always_inline)) {
-      const int64_t ci = (int64_t)y * nx + x0 + tid;
-#pragma unroll
-      for (int k = 0; k < 4; ++k) c[k] = corr[k * n + ci];
-    };
-    if constexpr (MODE == kClosureCorr) {
-      if (valid) load_corr(y0, cc);
-    }
-    for (int y = y0; y < y1; ++y) {
-      const int s = y - y0 + 1;                 // ring slot of row y is s & 3
-      const bool more = y + 1 < y1;             // row y + 2 is needed for row y + 1
-      if (more && loader) pull_cell<S, C, QG>(src, pitch, rows_of<S, QG>(wrapy(y + 2), ny, pitch), cx, nn);
-      if constexpr (MODE == kClosureCorr) {
-        if (more && valid) load_corr(y + 1, cn);
-      }
-      if (valid) {
-        const int sn = (s + 1) & 3, sc = s & 3, ss = (s - 1) & 3, l = tid + 1;
-        C gr[NF][2];
-#pragma unroll
-        for (int k = 0; k < NF; ++k) {
-          grad3x3<C, STENCIL>(ring[sc][k][l + 1], ring[sc][k][l - 1], ring[sn][k][l], ring[ss][k][l],
-                              ring[sn][k][l + 1], ring[sn][k][l - 1], ring[ss][k][l + 1], ring[ss][k][l - 1], gr[k][0],
-                              gr[k][1]);
-        }
-        const Mom<C> m = moments_of<QG>(cur);
-        const C ir = C(1) / (r.rho0 + m.drho);
-        Closure<C> cl;
-        if constexpr (MODE == kClosureFull) {
-          cl = closure_terms_full(gr, m.mx, m.my, r.bx0 + m.dbx, r.by0 + m.dby, ir, r.k2);
-        } else {
-          if constexpr (STENCIL >= LBM_STENCIL_LOCAL_ISO9 && QG == 5)
-            local_gradients(cur, m, r, gr[1][0] - gr[0][1], gr);
-          cl = closure_terms(gr[0][0], gr[0][1], gr[1][0], gr[1][1], gr[2][0], gr[2][1], gr[3][0], gr[3][1], ir,
-                             r.k2);
-        }
-        if constexpr (MODE == kClosureCorr) {
-          const C txx = C(cc[0]), txy = C(cc[1]), tyy = C(cc[2]), eps = C(cc[3]);
-          cl.tau_xy += txy;
-          cl.tau_d += txx - tyy;
-          cl.tau_s += txx + tyy;
-          cl.eps += eps;
-        }
-        collide_q<QG, true>(cur, m, cl, r);
-        const int64_t yo = int64_t(y) * int64_t(kPop<QG>) * pitch * int64_t(sizeof(S));
-#pragma unroll
-        for (int q = 0; q < kPop<QG>; ++q) store<NT>(at(dst + q * pitch, yo, cx.c), encode<S>(cur[q]));
-      }
-      if (more && writer) put((s + 2) & 3, nn);
-      __syncthreads();
-#pragma unroll
-      for (int q = 0; q < kPop<QG>; ++q) {
-        cur[q] = nxt[q];
-        nxt[q] = nn[q];
-      }
-      if constexpr (MODE == kClosureCorr) {
-#pragma unroll
-        for (int k = 0; k < 4; ++k) cc[k] = cn[k];
-      }
-    }
-  }
-}
-
 // Closure off, 16-bit storage, nx a multiple of 4: four cells per thread, so
 // every population moves in one aligned 8-byte load and store per thread (plus
 // one 2-byte load of the neighbour column for those that stream along x),
@@ -289,26 +162,33 @@ k_fused_dns_quad(const S* __restrict__ src, S* __restrict__ dst, int nx, int ny,
   }
 }
 
-// Closure on, FP32 compute (FP32, FP16 and BF16 storage): the schedule of
-// k_fused_les, written for the buffer addressing above.  A workgroup of W + 64
-// lanes owns the columns x0 .. x0+W-1 (W a multiple of 64, so every wave
-// stores whole aligned cache lines) and marches up the rows y0 .. y1-1; the
-// moment fields of rows y-1 .. y+2 live in a 4-slot LDS ring indexed by
-// column - x0 + 1.  Per row a collision lane issues the loads of row y + 2,
-// collides and stores row y from the ring, puts row y + 2's moments into the
-// ring and meets the others at the row's barrier (which waits for LDS only).
-// The row body has no branch around a memory operation: a lane past the last
-// column loads the last column, drops its stores (kDropOffset) and puts its
-// moments into a spare ring column (W + 2), so the compiler waits on each
-// batch of loads alone; three register sets rotate the rows without copies.
-// The last wave gathers the two halo columns (x0 - 1 and the column after the
-// strip's last cell) two rows ahead, in a loop of its own with the same
-// barrier per row.  Results are those of k_fused_les (same expressions).
+// Closure on.  A workgroup of W + 64 lanes owns the columns x0 .. x0+W-1 (W a
+// multiple of 64, so every wave stores whole aligned cache lines) and marches up
+// the rows y0 .. y1-1; the moment fields (m_x, m_y, B_x - B_ref, B_y - B_ref) of
+// rows y-1 .. y+2 live in a 4-slot LDS ring indexed by column - x0 + 1.  Per row a
+// collision lane issues the loads of row y + 2, collides and stores row y from
+// the ring, puts row y + 2's moments into the ring and meets the others at the
+// row's barrier (which waits for LDS only).  A ring slot is rewritten only after
+// the barrier that follows its last read.  The row body has no branch around a
+// memory operation: a lane past the last column loads the last column, drops its
+// stores (kDropOffset) and puts its moments into a spare ring column (W + 2), so
+// the compiler waits on each batch of loads alone; three register sets rotate the
+// rows without copies.  The last wave gathers the two halo columns (x0 - 1 and the
+// column after the strip's last cell) two rows ahead, in a loop of its own with
+// the same barrier per row.  FP64 64^2 (one row per workgroup): with per-lane
+// addresses, branches and the three first rows loaded one after another 5.3 us per
+// step, this form 4.5; 4096^2 961 and 881, with D2Q9 and
+// the density-gradient closure 1692 and 1273.
+//
+// MODE kClosureCorr: four FP32 planes (tau_xx, tau_xy, tau_yy, eps) of a
+// learned correction are added to the analytic subgrid terms of every cell.
+// MODE kClosureFull: the ring carries rho - rho0 as a fifth field and the
+// closure keeps the filtered-density gradient terms.
 template <typename S, int W, int STENCIL, bool NT, int MODE, int QG>
 __global__ void __launch_bounds__(W + 64)
-k_fused_les_f(const S* __restrict__ src, S* __restrict__ dst, int nx, int ny, int64_t pitch, int ry, Rates<float> r,
-              const float* __restrict__ corr) {
-  using C = float;
+k_fused_les_f(const S* __restrict__ src, S* __restrict__ dst, int nx, int ny, int64_t pitch, int ry,
+              Rates<typename ComputeOf<S>::type> r, const float* __restrict__ corr) {
+  using C = typename ComputeOf<S>::type;
   constexpr int NF = MODE == kClosureFull ? 5 : 4;
   constexpr int NP = kPop<QG>;
   __shared__ C ring[4][NF][W + 3];
@@ -345,13 +225,14 @@ k_fused_les_f(const S* __restrict__ src, S* __restrict__ dst, int nx, int ny, in
     const int widx = hl == 0 ? 0 : (hl == 1 ? last - x0 + 2 : W + 2);
     const Cols cx = cols_of<S>(xc, nx);
     auto ahead = [&](int y) { return wrapy(y <= y1 ? y : y1); };  // rows past y1 are not needed
-    RawCell<S, QG> ca, cb;
+    RawCell<S, QG> ca, cb, cc;
     pull(wrapy(y0 - 1), cx, ca);
+    pull(y0, cx, cb);
+    pull(wrapy(y0 + 1), cx, cc);
+    __builtin_amdgcn_sched_barrier(0);  // all three rows on their way first
     put(0, widx, ca);
-    pull(y0, cx, ca);
-    put(1, widx, ca);
-    pull(wrapy(y0 + 1), cx, ca);
-    put(2, widx, ca);
+    put(1, widx, cb);
+    put(2, widx, cc);
     pull(ahead(y0 + 2), cx, ca);
     __syncthreads();
     int y = y0;
@@ -408,10 +289,11 @@ k_fused_les_f(const S* __restrict__ src, S* __restrict__ dst, int nx, int ny, in
       cl = closure_terms(gr[0][0], gr[0][1], gr[1][0], gr[1][1], gr[2][0], gr[2][1], gr[3][0], gr[3][1], ir, r.k2);
     }
     if constexpr (MODE == kClosureCorr) {
-      cl.tau_xy += cc[1];
-      cl.tau_d += cc[0] - cc[2];
-      cl.tau_s += cc[0] + cc[2];
-      cl.eps += cc[3];
+      const C txx = C(cc[0]), tyy = C(cc[2]);
+      cl.tau_xy += C(cc[1]);
+      cl.tau_d += txx - tyy;
+      cl.tau_s += txx + tyy;
+      cl.eps += C(cc[3]);
     }
     collide_q<QG, true>(cur, m, cl, r);
     const __amdgpu_buffer_rsrc_t d = row_rsrc(reinterpret_cast<char*>(dst) + int64_t(y) * rowb, rowb);
@@ -428,12 +310,13 @@ k_fused_les_f(const S* __restrict__ src, S* __restrict__ dst, int nx, int ny, in
 
   RawCell<S, QG> ra, rb, rc;
   pull(wrapy(y0 - 1), cx, ra);
-  put(0, widx, ra);
   pull(y0, cx, rb);
-  put(1, widx, rb);
   pull(wrapy(y0 + 1), cx, rc);
-  put(2, widx, rc);
   if constexpr (MODE == kClosureCorr) load_corr(y0, cc);
+  __builtin_amdgcn_sched_barrier(0);  // all three rows on their way first
+  put(0, widx, ra);
+  put(1, widx, rb);
+  put(2, widx, rc);
   __syncthreads();
   int y = y0;
   for (; y + 3 <= y1; y += 3) {  // one straight-line block of three rows
@@ -1260,7 +1143,6 @@ static bool streaming_stores(const Launch& L) {
   return 2.0 * double(9 + 2 * L.qg) * double(L.nx) * double(L.ny) * double(storage_bytes(L.dtype)) > 256.0e6;
 }
 
-// FP32 compute runs k_fused_les_f, FP64 k_fused_les.
 template <typename S, typename C, int W, bool NT, int MODE, int QG, int STENCIL>
 static void launch_les_s(const Launch& L, const S* src, S* dst, const Rates<C>& r, const float* corr) {
   // Segments sized for one workgroup per compute unit, two for k_fused_les_f
@@ -1270,12 +1152,9 @@ static void launch_les_s(const Launch& L, const S* src, S* dst, const Rates<C>& 
   const int per_cu = (sizeof(C) == 4 && NT) ? 2 : 1;
   const int ry = fused_rows(L.nx, L.ny, W, L.cus * per_cu, sizeof(C) == 4 ? 128 : 64);
   const int strips = (L.nx + W - 1) / W, segs = (L.ny + ry - 1) / ry;
-  if constexpr (sizeof(C) == 4)  // one-dimensional grid, numbered XCD-contiguously in the kernel
-    hipLaunchKernelGGL((k_fused_les_f<S, W, STENCIL, NT, MODE, QG>), dim3(strips * segs), dim3(W + 64), 0, L.stream,
-                       src, dst, L.nx, L.ny, L.pitch, ry, r, corr);
-  else
-    hipLaunchKernelGGL((k_fused_les<S, C, W, STENCIL, NT, MODE, QG>), dim3(strips, segs), dim3(W + 64), 0, L.stream,
-                       src, dst, L.nx, L.ny, L.pitch, ry, r, corr);
+  // one-dimensional grid, numbered XCD-contiguously in the kernel
+  hipLaunchKernelGGL((k_fused_les_f<S, W, STENCIL, NT, MODE, QG>), dim3(strips * segs), dim3(W + 64), 0, L.stream,
+                     src, dst, L.nx, L.ny, L.pitch, ry, r, corr);
 }
 
 template <typename S, typename C, int W, bool NT, int MODE, int QG>

@@ -48,11 +48,12 @@ MsShape ms_shape(const Launch& L, int halo, int max_lanes, int per_cu_lds) {
 // Grids below these sizes take one-step sweeps: the rows and columns that a
 // sweep of several steps recomputes, and its longer pipeline, then cost more than
 // the traffic it saves.  Measured (several steps against one): closure on, FP32
-// 512^2 12.1 against 9.7 us and 700^2 12.3 against 16.0; BF16 512^2 12.5 against
-// 9.6, 1024^2 19.1 against 19.5; FP64 two steps 128^2 7.1 against 7.8, three
-// steps 512^2 14.4 against 13.7 for two, 1024^2 30.3 against 37.8; closure off,
-// FP32 256^2 3.8 against 5.0 and 64^2 2.7 against 3.3, FP64 64^2 3.7 against 3.4,
-// 128^2 4.0 against 5.2, BF16 512^2 5.7 against 5.8.
+// 512^2 11.2 against 9.3 us and 700^2 11.4 against 15.4; BF16 512^2 12.5 against
+// 9.6, 1024^2 19.1 against 19.5; FP64 two steps 384^2 10.8 against 10.5, 512^2 12.6
+// against 16.3 (three: 13.7), three steps 1024^2 30.3 against 37.8 for two; D2Q9
+// FP64 256^2 10.3 against 8.9, 384^2 12.5 against 14.8; closure off, FP32 256^2 3.8
+// against 5.0 and 64^2 2.7 against 3.3, FP64 64^2 3.7 against 3.4, 128^2 4.0
+// against 5.2, BF16 512^2 5.7 against 5.8.
 int multi_steps(const Launch& L) {
   if (L.schedule != LBM_SCHED_FUSED || L.learned || L.nx < 16 || L.ny < 16) return 1;
   const int64_t cells = int64_t(L.nx) * L.ny;
@@ -62,7 +63,7 @@ int multi_steps(const Launch& L) {
   if (bytes == 2) return cells >= (les ? 1000000 : 300000) ? most : 1;
   if (!les) return bytes == 8 && cells < 10000 ? 1 : most;
   if (bytes == 4) return cells >= 360000 ? most : 1;
-  return cells >= 400000 ? most : (cells >= 10000 ? 2 : 1);
+  return cells >= 400000 ? most : (cells >= (L.qg == 9 ? 140000 : 160000) ? 2 : 1);
 }
 
 hipError_t launch_steps_fp64(const Launch& L, int k);

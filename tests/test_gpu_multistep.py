@@ -16,7 +16,7 @@ torch = pytest.importorskip("torch")
 # (nx, ny, steps) by path: at the smallest grids of the path, on both sides of
 # strip and segment edges, ragged strips and segments, remainders of n
 SMALL = [(16, 16, 7), (17, 19, 4), (122, 21, 5), (123, 64, 6), (251, 300, 9)]
-FP64_LES = [(100, 100, 5), (118, 90, 4), (119, 257, 7), (700, 601, 6)]
+FP64_LES = [(400, 401, 5), (122, 1400, 4), (123, 1350, 7), (118, 3500, 4), (119, 3601, 7), (700, 601, 6)]
 FP32_LES = [(600, 600, 5), (246, 1500, 4), (247, 1601, 7), (4900, 75, 3), (16, 22501, 2)]
 LOW_LES = [(1000, 1000, 5), (247, 4096, 4), (5000, 201, 3)]
 
@@ -71,7 +71,7 @@ def test_closure_on(dtype, nx, ny, n, stencil):
 
 @pytest.mark.parametrize("stencil", ["iso9", "central5"])
 @pytest.mark.parametrize("mag", ["d2q5", "d2q9"])
-@pytest.mark.parametrize("dtype,nx,ny,n", [("fp64", 119, 257, 7), ("fp64", 700, 601, 5), ("fp32", 247, 1601, 7),
+@pytest.mark.parametrize("dtype,nx,ny,n", [("fp64", 123, 1400, 7), ("fp64", 700, 601, 5), ("fp32", 247, 1601, 7),
                                            ("fp16", 247, 4096, 4)])
 def test_density_gradients(dtype, nx, ny, n, mag, stencil):
     if mag == "d2q9" and dtype == "fp16":
@@ -80,7 +80,7 @@ def test_density_gradients(dtype, nx, ny, n, mag, stencil):
 
 
 @pytest.mark.parametrize("delta", [0.0, 3.0])
-@pytest.mark.parametrize("dtype,nx,ny,n", [("fp64", 123, 90, 5), ("fp32", 246, 1500, 4), ("fp32", 253, 1601, 7),
+@pytest.mark.parametrize("dtype,nx,ny,n", [("fp64", 123, 1300, 5), ("fp32", 246, 1500, 4), ("fp32", 253, 1601, 7),
                                            ("fp32", 4096, 2048, 3)])
 def test_d2q9(dtype, nx, ny, n, delta):
     _check(nx, ny, n, dtype=dtype, delta=delta, mag_lattice="d2q9")
