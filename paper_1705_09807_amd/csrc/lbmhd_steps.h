@@ -19,9 +19,10 @@
 // the results equal those of one-step sweeps bit for bit.
 //
 // Measured, us per step, one-step sweep -> K steps per launch: 4096^2 FP32
-// closure off 411 -> 140 (K = 4), on 442 -> 178 (K = 3); 8192^2 BF16 855 -> 368
-// and 940 -> 588; 4096^2 FP64 955 -> 341 and 873 -> 350; 1024^2 FP32 25.7 -> 11
-// and 27.7 -> 18; 4096^2 D2Q9 FP32 590 -> 240 and 627 -> 249.  What bounds it now:
+// closure off 411 -> 130 (K = 4), on 442 -> 173 (K = 3); 8192^2 BF16 855 -> 370
+// and 940 -> 597; 4096^2 FP64 955 -> 343 and 873 -> 350; 1024^2 FP32 25.7 -> 10.3
+// and 27.7 -> 17.8; 4096^2 D2Q9 FP32 590 -> 253 and 627 -> 249; 1500 x 1001 D2Q9
+// FP64 with density gradients 163 -> 52.  What bounds it now:
 // at 4096^2 FP32 a launch moves its 2.55 GB at 4.6-4.9 TB/s with the closure and
 // the vector ALUs busy about half the time; 16-bit storage is bound by the vector
 // ALUs (8192^2 BF16: about 230 instructions a cell and step, 410 of the 588 us).
@@ -44,7 +45,7 @@ namespace lbm {
 // Most steps per launch: what the LDS holds in groups of 256 columns (FP64 with the
 // closure: 128, whose registers allow no more).
 constexpr int ms_most_steps(size_t bytes, bool les, int qg) {
-  if (bytes == 8) return qg == 9 ? 2 : 3;  // D2Q9 with the closure, three steps: registers spill (111 against 70 us)
+  if (bytes == 8) return qg == 9 && !les ? 2 : 3;
   return les || qg == 9 ? 3 : 4;
 }
 
@@ -54,7 +55,153 @@ struct MsShape {
 };
 MsShape ms_shape(const Launch& L, int halo, int max_lanes, int per_cu_lds);
 
-constexpr int kClosureOff = 3;           // k_steps: a mode of its own beside the closure variants
+// Strip, segment and group of this thread (workgroups numbered XCD-contiguously: the
+// strips of a segment run side by side on one XCD and share the lines at their
+// edges in its L2).
+struct MsTile {
+  int step, lane;      // group, lane within it
+  int x0, x1, y0, y1;  // cells the workgroup stores
+};
+__device__ __forceinline__ MsTile ms_tile(int nx, int ny, int w, int ry, int k) {
+  MsTile t;
+  const int T = blockDim.x / k;
+  t.step = __builtin_amdgcn_readfirstlane(threadIdx.x / T);
+  t.lane = threadIdx.x - t.step * T;
+  const int nstrip = (nx + w - 1) / w;
+  const int vb = xcd_contiguous(blockIdx.x, gridDim.x);
+  t.x0 = (vb % nstrip) * w;
+  t.x1 = min(t.x0 + w, nx);
+  t.y0 = (vb / nstrip) * ry;
+  t.y1 = min(t.y0 + ry, ny);
+  return t;
+}
+// The lane's column, x0 - halo + lane (periodic; lanes past the right halo repeat its
+// last column).
+__device__ __forceinline__ int ms_column(const MsTile& t, int halo, int nx) {
+  const int x = min(t.x0 - halo + t.lane, t.x1 - 1 + halo);
+  return x < 0 ? x + nx : (x >= nx ? x - nx : x);
+}
+// Row y (within a grid height of the grid) of the state before the launch.
+template <typename S, int QG>
+__device__ __forceinline__ void ms_pull(const S* __restrict__ src, uint32_t pq, int y, int ny, const Cols& cx,
+                                        RawCell<S, QG>& c) {
+  auto wrapy = [&](int v) { return v < 0 ? v + ny : (v >= ny ? v - ny : v); };
+  pull_raw<S, QG>(src, pq, wrapy(y - 1), wrapy(y), wrapy(y + 1), cx, c);
+}
+// Store of row y, dropped outside the workgroup's rows and columns.  Ordinary
+// stores: the strips' edges share lines, which then meet in L2 (non-temporal
+// stores took 370 against 297 us per step at 4096^2).
+template <typename S, int QG>
+__device__ __forceinline__ void ms_store(S* __restrict__ dst, uint32_t pq, const MsTile& t, int y, bool owner,
+                                         const Cols& cx, const typename ComputeOf<S>::type* v) {
+  const bool mine = y >= t.y0 && y < t.y1;
+  const uint32_t rowb = uint32_t(kPop<QG>) * pq;
+  const __amdgpu_buffer_rsrc_t d = row_rsrc(reinterpret_cast<char*>(dst) + int64_t(mine ? y : t.y0) * rowb, rowb);
+  const uint32_t xo = owner && mine ? cx.c : kDropOffset;
+#pragma unroll
+  for (int q = 0; q < kPop<QG>; ++q) buf_store<S, false>(encode<S>(v[q]), d, xo, uint32_t(q) * pq);
+}
+
+// Closure off, K steps per launch.  A workgroup holds K groups of T = blockDim / K
+// lanes, one per step, and marches up the rows of its strip; the lanes of a group own
+// the same columns.  In iteration i group 0 collides row i (loaded an iteration
+// earlier) and hands it on; group s > 0 reads the row that group s - 1 handed on in
+// the iteration before, whose populations stream into the rows above, beside and
+// below it: the row below it, i - 2 s, is then complete in registers and is
+// collided and handed on or, in the last group, stored.  Rows are handed on
+// through two LDS slots by parity, one barrier per iteration.  One wave of every
+// group runs on every SIMD, so while one waits for its loads, LDS or the barrier the
+// others' arithmetic fills in.  (Gathering a row from three LDS slots behind a second
+// barrier: 512^2 FP32 5.5 against 4.5 us per step, 1024^2 11.7 against 9.7; the same
+// at 4096^2, where HBM sets the pace.)
+template <typename S, int QG, int K, int LN>
+struct DnsLds {
+  S pop[K - 1][2][kPop<QG>][LN + 2];  // step, parity, population, lane + 1
+};
+
+template <typename S, int QG, int K, int LN>
+__global__ void __launch_bounds__(LN* K)
+k_dns_steps(const S* __restrict__ src, S* __restrict__ dst, int nx, int ny, int64_t pitch, int w, int ry,
+            Rates<typename ComputeOf<S>::type> r) {
+  using C = typename ComputeOf<S>::type;
+  constexpr int NP = kPop<QG>, H = K - 1;  // H: recomputed columns at each side, rows at each end
+  extern __shared__ __attribute__((aligned(16))) char ms_lds[];
+  DnsLds<S, QG, K, LN>& lds = *reinterpret_cast<DnsLds<S, QG, K, LN>*>(ms_lds);
+  const MsTile t = ms_tile(nx, ny, w, ry, K);
+  const int l = t.lane + 1;
+  const int first = t.y0 - H, last = t.y1 - 1 + H;  // rows of the first step
+  const int end = t.y1 + 2 * (K - 1);               // iterations first .. end - 1
+  const Cols cx = cols_of<S>(ms_column(t, H, nx), nx);
+  const uint32_t pq = uint32_t(pitch) * uint32_t(sizeof(S));
+  const Closure<C> off = {C(0), C(0), C(0), C(0)};
+  auto collide = [&](C* v) __attribute__((always_inline)) {
+    const Mom<C> m = moments_of<QG>(v);
+    collide_q<QG, false>(v, m, off, r);
+  };
+  auto hand_on = [&](int s, int par, const C* v) __attribute__((always_inline)) {
+#pragma unroll
+    for (int q = 0; q < NP; ++q) lds.pop[s][par][q][l] = encode<S>(v[q]);
+  };
+  using N0 = std::integral_constant<int, 0>;
+  using N1 = std::integral_constant<int, 1>;
+  using N2 = std::integral_constant<int, 2>;
+  using N3 = std::integral_constant<int, 3>;
+
+  if (t.step == 0) {
+    RawCell<S, QG> raw[2];
+    auto iter = [&](int i, auto uc) __attribute__((always_inline)) {
+      constexpr int u = decltype(uc)::value;
+      ms_pull<S, QG>(src, pq, min(i + 1, last), ny, cx, raw[u ^ 1]);
+      __builtin_amdgcn_sched_barrier(0);
+      C v[NP];
+      decode_raw<S, C, QG>(raw[u], v);
+      collide(v);
+      hand_on(0, u, v);
+      __syncthreads();
+    };
+    ms_pull<S, QG>(src, pq, first, ny, cx, raw[0]);
+    for (int i = first; i < end; i += 4) {  // past `end`: nothing is stored
+      iter(i, N0{});
+      iter(i + 1, N1{});
+      iter(i + 2, N0{});
+      iter(i + 3, N1{});
+    }
+  } else {
+    const bool owner = t.lane >= H && t.lane < H + (t.x1 - t.x0);
+    C row[4][NP];  // rows being completed, by the iteration (mod 4) that completes them
+    auto iter = [&](int i, auto uc, auto sc) __attribute__((always_inline)) {
+      constexpr int u = decltype(uc)::value, st = decltype(sc)::value;
+#pragma unroll
+      for (int q = 0; q < NP; ++q)
+        row[(u + 1 + qcy<QG>(q)) & 3][q] = decode<C>(lds.pop[st - 1][(u & 1) ^ 1][q][l - qcx<QG>(q)]);
+      if constexpr (sizeof(S) == 8) __builtin_amdgcn_sched_barrier(0);  // registers: the reads before the collision
+      C v[NP];
+#pragma unroll
+      for (int q = 0; q < NP; ++q) v[q] = row[u][q];
+      collide(v);
+      if constexpr (st + 1 < K)
+        hand_on(st, u & 1, v);
+      else
+        ms_store<S, QG>(dst, pq, t, i - 2 * st, owner, cx, v);
+      __syncthreads();
+    };
+    auto loop = [&](auto sc) __attribute__((always_inline)) {
+      for (int i = first; i < end; i += 4) {
+        iter(i, N0{}, sc);
+        iter(i + 1, N1{}, sc);
+        iter(i + 2, N2{}, sc);
+        iter(i + 3, N3{}, sc);
+      }
+    };
+    if (t.step == 1) loop(N1{});
+    if constexpr (K > 2) {
+      if (t.step == 2) loop(N2{});
+    }
+    if constexpr (K > 3) {
+      if (t.step == 3) loop(N3{});
+    }
+  }
+}
 
 // LDS rows that hand population q from one step to the next: a row written in
 // iteration j is read in j + 1 by the populations that move down, j + 2 by those
@@ -71,172 +218,128 @@ constexpr int ms_row(int q) {
 template <int QG>
 constexpr int kMsRows = ms_row<QG>(kPop<QG>);
 
-// LDS of k_steps for at most LN columns (and one pad column at each side).
+// LDS of k_les_steps for at most LN columns (and one pad column at each side).
 template <typename S, int MODE, int QG, int K, int LN>
-struct MsLds {
-  static constexpr int kMsStride = LN + 2;
+struct LesLds {
   using C = typename ComputeOf<S>::type;
-  static constexpr bool LES = MODE != kClosureOff, FULL = MODE == kClosureFull;
+  static constexpr bool FULL = MODE == kClosureFull;
   struct alignas(4 * sizeof(C)) Quad {
     C v[4];
   };
-  Quad mom[LES ? K : 1][LES ? 3 : 1][LES ? kMsStride : 1];  // m, B - B_ref by step, row slot, lane + 1
-  C rho[FULL ? K : 1][FULL ? 3 : 1][FULL ? kMsStride : 1];
-  S pop[K - 1][kMsRows<QG>][kMsStride];                     // handed-on populations
+  Quad mom[K][3][LN + 2];  // m_x, m_y, B_x - B_ref, B_y - B_ref by step, row slot, lane + 1
+  C rho[FULL ? K : 1][FULL ? 3 : 1][FULL ? LN + 2 : 1];
+  S pop[K - 1][kMsRows<QG>][LN + 2];  // handed-on populations
 };
 
-// K steps per launch.  A workgroup holds K groups of T = blockDim / K lanes, one
-// per step, and marches up the rows of its strip; the lanes of a group own the
-// same columns.  In iteration i
-//  first half:  group 0 has row i (loaded an iteration earlier), group s > 0
-//               gathers row i - LAG s of its step from the populations that
-//               group s - 1 handed on; with the closure each puts the row's
-//               moments into its ring (three row slots);
-//  second half: each group collides that row (closure off), or the row before it
-//               with the gradients from its ring, and hands it on or, in the
-//               last group, stores it.
-// A barrier after each half.  One wave of every group runs on every SIMD, so
-// while one waits for its loads, LDS or the barrier's slowest wave the others'
-// arithmetic fills in; a group needs the registers of a single step.
+// Closure on, K steps per launch, groups as in k_dns_steps.  In iteration i
+//  first half:  group 0 has row i (loaded an iteration earlier), group s > 0 gathers
+//               row i - 3 s of its step from the populations that group s - 1 handed
+//               on; each puts the row's moments into its ring (three row slots);
+//  second half: each group collides the row before it with the gradients from its
+//               ring, and hands it on or, in the last group, stores it.
+// A barrier after each half.  (One barrier per iteration, as in k_dns_steps, takes
+// two more rows of registers and spills: 4096^2 FP32 201 against 178 us per step.)
 template <typename S, int STENCIL, int MODE, int QG, int K, int LN>
 __global__ void __launch_bounds__(LN* K)
-k_steps(const S* __restrict__ src, S* __restrict__ dst, int nx, int ny, int64_t pitch, int w, int ry,
-        Rates<typename ComputeOf<S>::type> r) {
+k_les_steps(const S* __restrict__ src, S* __restrict__ dst, int nx, int ny, int64_t pitch, int w, int ry,
+            Rates<typename ComputeOf<S>::type> r) {
   using C = typename ComputeOf<S>::type;
-  using Lds = MsLds<S, MODE, QG, K, LN>;
+  using Lds = LesLds<S, MODE, QG, K, LN>;
   using Quad = typename Lds::Quad;
-  constexpr bool LES = Lds::LES;
   constexpr int NP = kPop<QG>, NF = Lds::FULL ? 5 : 4;
-  constexpr int H = LES ? 2 * K - 1 : K - 1;  // recomputed columns at each side, rows at each end
-  constexpr int LAG = LES ? 3 : 2, COL = LES ? 1 : 0;
+  constexpr int H = 2 * K - 1;  // recomputed columns at each side, rows at each end
   extern __shared__ __attribute__((aligned(16))) char ms_lds[];
   Lds& lds = *reinterpret_cast<Lds*>(ms_lds);
-
-  const int T = blockDim.x / K;
-  const int step = __builtin_amdgcn_readfirstlane(threadIdx.x / T);
-  const int tid = threadIdx.x - step * T, l = tid + 1;
-  // numbered XCD-contiguously: the strips of a segment run side by side on one
-  // XCD and share the lines at their edges in its L2
-  const int nstrip = (nx + w - 1) / w;
-  const int vb = xcd_contiguous(blockIdx.x, gridDim.x);
-  const int x0 = (vb % nstrip) * w, x1 = min(x0 + w, nx);
-  const int y0 = (vb / nstrip) * ry, y1 = min(y0 + ry, ny);
-  const int first = y0 - H, last = y1 - 1 + H;  // rows of the first step's moments
-  const int end = y1 + LAG * (K - 1) + COL;     // iterations first .. end - 1
-  // columns of the lanes: x0 - H + tid, periodic; lanes past the right halo
-  // repeat its last column
-  int x = min(x0 - H + tid, x1 - 1 + H);
-  x = x < 0 ? x + nx : (x >= nx ? x - nx : x);
-  const Cols cx = cols_of<S>(x, nx);
+  const MsTile t = ms_tile(nx, ny, w, ry, K);
+  const int l = t.lane + 1;
+  const int first = t.y0 - H, last = t.y1 - 1 + H;  // rows of the first step's moments
+  const int end = t.y1 + 3 * (K - 1) + 1;           // iterations first .. end - 1
+  const Cols cx = cols_of<S>(ms_column(t, H, nx), nx);
   const uint32_t pq = uint32_t(pitch) * uint32_t(sizeof(S));
-  auto wrapy = [&](int y) { return y < 0 ? y + ny : (y >= ny ? y - ny : y); };
 
   auto put = [&](int s, int sl, const C* v) __attribute__((always_inline)) {
-    if constexpr (LES) {
-      const Mom<C> m = moments_of<QG>(v);
-      lds.mom[s][sl][l] = Quad{m.mx, m.my, m.dbx, m.dby};
-      if constexpr (NF == 5) lds.rho[s][sl][l] = m.drho;
-    }
+    const Mom<C> m = moments_of<QG>(v);
+    lds.mom[s][sl][l] = Quad{m.mx, m.my, m.dbx, m.dby};
+    if constexpr (NF == 5) lds.rho[s][sl][l] = m.drho;
   };
-  // collision of a cell whose row sits in slot sc of step s's ring, its southern
-  // and northern neighbours' rows in ss and sn
+  // closure and collision of a cell whose row sits in slot sc of step s's ring, its
+  // southern and northern neighbours' rows in ss and sn
   auto collide = [&](int s, int ss, int sc, int sn, C* v) __attribute__((always_inline)) {
     const Mom<C> m = moments_of<QG>(v);
-    Closure<C> cl = {C(0), C(0), C(0), C(0)};
-    if constexpr (LES) {
-      const auto& q = lds.mom[s];
-      const Quad e = q[sc][l + 1], o = q[sc][l - 1], n = q[sn][l], so = q[ss][l], ne = q[sn][l + 1],
-                 nw = q[sn][l - 1], se = q[ss][l + 1], sw = q[ss][l - 1];
-      C gr[NF][2];
+    const auto& q = lds.mom[s];
+    C gr[NF][2];
+    // FP64: two fields at a time, which the registers have room for
+    constexpr int kAtOnce = sizeof(C) == 8 ? 2 : 4;
 #pragma unroll
-      for (int k = 0; k < 4; ++k)
-        grad3x3<C, STENCIL>(e.v[k], o.v[k], n.v[k], so.v[k], ne.v[k], nw.v[k], se.v[k], sw.v[k], gr[k][0], gr[k][1]);
-      const C ir = C(1) / (r.rho0 + m.drho);
-      if constexpr (Lds::FULL) {
-        const auto& p = lds.rho[s];
-        grad3x3<C, STENCIL>(p[sc][l + 1], p[sc][l - 1], p[sn][l], p[ss][l], p[sn][l + 1], p[sn][l - 1], p[ss][l + 1],
-                            p[ss][l - 1], gr[4][0], gr[4][1]);
-        cl = closure_terms_full(gr, m.mx, m.my, r.bx0 + m.dbx, r.by0 + m.dby, ir, r.k2);
-      } else {
-        if constexpr (STENCIL >= LBM_STENCIL_LOCAL_ISO9 && QG == 5)
-          local_gradients(v, m, r, gr[1][0] - gr[0][1], gr);
-        cl = closure_terms(gr[0][0], gr[0][1], gr[1][0], gr[1][1], gr[2][0], gr[2][1], gr[3][0], gr[3][1], ir, r.k2);
-      }
+    for (int k0 = 0; k0 < 4; k0 += kAtOnce) {
+#pragma unroll
+      for (int k = k0; k < k0 + kAtOnce; ++k)
+        grad3x3<C, STENCIL>(q[sc][l + 1].v[k], q[sc][l - 1].v[k], q[sn][l].v[k], q[ss][l].v[k], q[sn][l + 1].v[k],
+                            q[sn][l - 1].v[k], q[ss][l + 1].v[k], q[ss][l - 1].v[k], gr[k][0], gr[k][1]);
+      if constexpr (kAtOnce < 4) __builtin_amdgcn_sched_barrier(0);
     }
-    collide_q<QG, LES>(v, m, cl, r);
+    const C ir = C(1) / (r.rho0 + m.drho);
+    Closure<C> cl;
+    if constexpr (Lds::FULL) {
+      const auto& p = lds.rho[s];
+      grad3x3<C, STENCIL>(p[sc][l + 1], p[sc][l - 1], p[sn][l], p[ss][l], p[sn][l + 1], p[sn][l - 1], p[ss][l + 1],
+                          p[ss][l - 1], gr[4][0], gr[4][1]);
+      cl = closure_terms_full(gr, m.mx, m.my, r.bx0 + m.dbx, r.by0 + m.dby, ir, r.k2);
+    } else {
+      if constexpr (STENCIL >= LBM_STENCIL_LOCAL_ISO9 && QG == 5)
+        local_gradients(v, m, r, gr[1][0] - gr[0][1], gr);
+      cl = closure_terms(gr[0][0], gr[0][1], gr[1][0], gr[1][1], gr[2][0], gr[2][1], gr[3][0], gr[3][1], ir, r.k2);
+    }
+    collide_q<QG, true>(v, m, cl, r);
   };
-  // parity of the iteration: which of two slots
+  // slot of population q in iteration i: u = i mod 3, par = i mod 2
+  auto slot = [](int q, int u, int par) { return ms_row<QG>(q) + (qcy<QG>(q) > 0 ? u : (qcy<QG>(q) == 0 ? par : 0)); };
   auto hand_on = [&](int s, int u, int par, const C* v) __attribute__((always_inline)) {
 #pragma unroll
-    for (int q = 0; q < NP; ++q) {
-      const int sl = qcy<QG>(q) > 0 ? u : (qcy<QG>(q) == 0 ? par : 0);
-      lds.pop[s][ms_row<QG>(q) + sl][l] = encode<S>(v[q]);
-    }
-  };
-  auto gather = [&](int s, int u, int par, C* v) __attribute__((always_inline)) {
-#pragma unroll
-    for (int q = 0; q < NP; ++q) {
-      const int sl = qcy<QG>(q) > 0 ? u : (qcy<QG>(q) == 0 ? par : 0);
-      v[q] = decode<C>(lds.pop[s - 1][ms_row<QG>(q) + sl][l - qcx<QG>(q)]);
-    }
+    for (int q = 0; q < NP; ++q) lds.pop[s][slot(q, u, par)][l] = encode<S>(v[q]);
   };
   using N0 = std::integral_constant<int, 0>;
   using N1 = std::integral_constant<int, 1>;
   using N2 = std::integral_constant<int, 2>;
 
-  if (step == 0) {
+  if (t.step == 0) {
     RawCell<S, QG> raw[3];
-    auto pull = [&](int row, RawCell<S, QG>& c) __attribute__((always_inline)) {
-      const int y = min(row, last);
-      pull_raw<S, QG>(src, pq, wrapy(y - 1), wrapy(y), wrapy(y + 1), cx, c);
-    };
     auto iter = [&](int i, int par, auto uc) __attribute__((always_inline)) {
       constexpr int u0 = decltype(uc)::value, u1 = (u0 + 2) % 3, u2 = (u0 + 1) % 3;  // rows i, i - 1, i - 2
-      pull(i + 1, raw[u2]);
+      ms_pull<S, QG>(src, pq, min(i + 1, last), ny, cx, raw[u2]);
       __builtin_amdgcn_sched_barrier(0);
       C v[NP];
-      if constexpr (LES) {
-        decode_raw<S, C, QG>(raw[u0], v);
-        put(0, u0, v);
-      }
+      decode_raw<S, C, QG>(raw[u0], v);
+      put(0, u0, v);
       __syncthreads();
-      decode_raw<S, C, QG>(raw[LES ? u1 : u0], v);
+      decode_raw<S, C, QG>(raw[u1], v);
       collide(0, u2, u1, u0, v);
       hand_on(0, u0, par, v);
       __syncthreads();
     };
-    pull(first, raw[0]);
+    ms_pull<S, QG>(src, pq, first, ny, cx, raw[0]);
     for (int i = first, par = 0; i < end; i += 3, par ^= 1) {  // past `end`: nothing is stored
       iter(i, par, N0{});
       iter(i + 1, par ^ 1, N1{});
       iter(i + 2, par, N2{});
     }
   } else {
-    // s > 0; the last group stores
-    const int s = step;
+    const bool owner = t.lane >= H && t.lane < H + (t.x1 - t.x0);
     C vs[3][NP];  // rows gathered and not yet collided
-    const bool owner = tid >= H && tid < H + (x1 - x0);
     auto iter = [&](int i, int par, auto uc, auto sc) __attribute__((always_inline)) {
       constexpr int u0 = decltype(uc)::value, u1 = (u0 + 2) % 3, u2 = (u0 + 1) % 3, st = decltype(sc)::value;
-      gather(st, u0, par, vs[u0]);
+#pragma unroll
+      for (int q = 0; q < NP; ++q) vs[u0][q] = decode<C>(lds.pop[st - 1][slot(q, u0, par)][l - qcx<QG>(q)]);
       put(st, u0, vs[u0]);
       __syncthreads();
       C v[NP];
 #pragma unroll
-      for (int q = 0; q < NP; ++q) v[q] = vs[LES ? u1 : u0][q];
+      for (int q = 0; q < NP; ++q) v[q] = vs[u1][q];
       collide(st, u2, u1, u0, v);
-      if constexpr (st + 1 < K) {
+      if constexpr (st + 1 < K)
         hand_on(st, u0, par, v);
-      } else {
-        const int y = i - LAG * st - COL;
-        const bool mine = y >= y0 && y < y1;
-        const uint32_t rowb = uint32_t(NP) * pq;
-        const __amdgpu_buffer_rsrc_t d =
-            row_rsrc(reinterpret_cast<char*>(dst) + int64_t(mine ? y : y0) * rowb, rowb);
-        const uint32_t xo = owner && mine ? cx.c : kDropOffset;
-#pragma unroll
-        for (int q = 0; q < NP; ++q) buf_store<S, false>(encode<S>(v[q]), d, xo, uint32_t(q) * pq);
-      }
+      else
+        ms_store<S, QG>(dst, pq, t, i - 3 * st - 1, owner, cx, v);
       __syncthreads();
     };
     auto loop = [&](auto sc) __attribute__((always_inline)) {
@@ -246,12 +349,9 @@ k_steps(const S* __restrict__ src, S* __restrict__ dst, int nx, int ny, int64_t 
         iter(i + 2, par, N2{}, sc);
       }
     };
-    if (s == 1) loop(N1{});
+    if (t.step == 1) loop(N1{});
     if constexpr (K > 2) {
-      if (s == 2) loop(N2{});
-    }
-    if constexpr (K > 3) {
-      if (s == 3) loop(std::integral_constant<int, 3>{});
+      if (t.step == 2) loop(N2{});
     }
   }
 }
@@ -259,13 +359,20 @@ k_steps(const S* __restrict__ src, S* __restrict__ dst, int nx, int ny, int64_t 
 // ---------------------------------------------------------------------------
 // Host side
 // ---------------------------------------------------------------------------
+constexpr int kClosureOff = 3;  // beside the closure variants
+
 template <typename S, int STENCIL, int MODE, int QG, int K, int LN>
 static hipError_t launch_k_steps(const Launch& L) {
   using C = typename ComputeOf<S>::type;
-  using Lds = MsLds<S, MODE, QG, K, LN>;
+  using Lds = std::conditional_t<MODE == kClosureOff, DnsLds<S, QG, K, LN>, LesLds<S, MODE, QG, K, LN>>;
   static_assert(sizeof(Lds) <= 160 * 1024, "LDS of a compute unit");
   const MsShape sh = ms_shape(L, MODE != kClosureOff ? 2 * K - 1 : K - 1, LN, 160 * 1024 / sizeof(Lds));
-  const auto kernel = &k_steps<S, STENCIL, MODE, QG, K, LN>;
+  const auto kernel = [] {
+    if constexpr (MODE == kClosureOff)
+      return &k_dns_steps<S, QG, K, LN>;
+    else
+      return &k_les_steps<S, STENCIL, MODE, QG, K, LN>;
+  }();
   if (sizeof(Lds) > 64 * 1024) {
     const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(Lds));

@@ -8,8 +8,8 @@ namespace lbm {
 
 // Measured on MI355X, 256^2 .. 8192^2, microseconds per step:
 //  * groups of 256 columns, of 128 with the closure off on small grids, where
-//    more and narrower strips fill the chip (512^2 FP32 5.4 against 7.2, 1024^2
-//    10.6 against 11.8, 2048^2 36.8 against 34.1);
+//    more and narrower strips fill the chip (512^2 FP32 5.4 against 7.2, 2048^2 36.8
+//    against 34.1);
 //  * one workgroup per compute unit: few, tall segments keep few rows of the
 //    state open and recompute least (4096^2 FP32 closure on 175 against 180 with
 //    two, 2048^2 51 against 59); two for 16-bit storage on tall segments, where
