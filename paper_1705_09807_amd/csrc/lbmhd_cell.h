@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "lbmhd_device.h"
 #include "lbmhd_internal.h"
 
@@ -157,9 +159,12 @@ __device__ __forceinline__ Mom<C> moments19(const C v[kQ]) {
 //     moment-space SRT of MagTMatrix / MagMomentEq: with one rate for every
 //     moment, relaxing T_m g towards N^eq and mapping back is relaxing g
 //     towards T_m^-1 N^eq, the D2Q9 geq.
-// LES false: the closure is off (cl is not read).
-template <int QG, bool LES, typename C>
-__device__ __forceinline__ void collide_q(C* v, const Mom<C>& m, const Closure<C>& cl, const Rates<C>& r) {
+// LES false: the closure is off (cl is not read).  LOCAL: after local_gradients, whose
+// unfused equilibria are shared.  swapped: the rest population sums its two products
+// in the other order (see swapped_rest).
+template <int QG, bool LES, bool LOCAL = false, typename C>
+__device__ __forceinline__ void collide_q(C* v, const Mom<C>& m, const Closure<C>& cl, const Rates<C>& r,
+                                          bool swapped = false) {
 #pragma clang fp contract(off)
   const C rho = r.rho0 + m.drho;
   const C ir = C(1) / rho;
@@ -175,9 +180,10 @@ __device__ __forceinline__ void collide_q(C* v, const Mom<C>& m, const Closure<C
   const C M7 = fmadd(C(4), s58, fmadd(C(4), v[0], C(-5) * s14));
   const C M8 = fmadd(C(4), v[0], -s58);
   // filtered equilibrium moments (deviation form for M8)
-  const C q2 = fmadd(mx, mx, my * my) * ir;
-  C e3 = fmadd(mx * my, ir, -(bx * by));
-  C e4 = fmadd(fmadd(mx, mx, -(my * my)), ir, -fmadd(bx, bx, -(by * by)));
+  const C q2 = (LOCAL ? mx * mx + my * my : fmadd(mx, mx, my * my)) * ir;
+  C e3 = LOCAL ? mx * my * ir - bx * by : fmadd(mx * my, ir, -(bx * by));
+  C e4 = LOCAL ? (mx * mx - my * my) * ir - (bx * bx - by * by)
+               : fmadd(fmadd(mx, mx, -(my * my)), ir, -fmadd(bx, bx, -(by * by)));
   if constexpr (LES) {
     e3 += cl.tau_xy;
     e4 += cl.tau_d;
@@ -188,7 +194,7 @@ __device__ __forceinline__ void collide_q(C* v, const Mom<C>& m, const Closure<C
   const C m8 = M8 - fmadd(C(5.0 / 3.0), m.drho, e7);
   const C d4 = r.s4q * (M4 - e4), d5 = r.s5q * m5, d6 = r.s6q * m6, d7 = r.s7q * m7, d8 = r.s8q * m8;
   const C h = fmadd(C(4), d7, -d8);
-  v[0] = fmadd(C(-4), fmadd(r.s8q, m8, d7), v[0]);
+  v[0] = fmadd(C(-4), swapped ? fmadd(r.s7q, m7, d8) : fmadd(r.s8q, m8, d7), v[0]);
   v[1] -= fmadd(C(-5), d7, fmadd(C(-2), d5, d4));
   v[2] -= fmadd(C(-5), d7, fmadd(C(-2), d6, -d4));
   v[3] -= fmadd(C(-5), d7, fmadd(C(2), d5, d4));
@@ -199,8 +205,8 @@ __device__ __forceinline__ void collide_q(C* v, const Mom<C>& m, const Closure<C
   v[8] -= fmadd(-r.s6q, m6, fmadd(-r.s3q, m3, d5)) + h;
   // vector distribution, SRT; the w'_i B_ref part of the stored deviation
   // cancels against that of g_eq
-  const C n = fmadd(mx, by, -(my * bx));
-  const C E = LES ? fmadd(n, ir, cl.eps) : n * ir;
+  const C n = LOCAL ? mx * by - my * bx : fmadd(mx, by, -(my * bx));
+  const C E = !LES ? n * ir : (LOCAL ? n * ir + cl.eps : fmadd(n, ir, cl.eps));
   const C bxp = fmadd(C(3), E, m.dbx), bxm = fmadd(C(-3), E, m.dbx);
   const C byp = fmadd(C(3), E, m.dby), bym = fmadd(C(-3), E, m.dby);
 #pragma unroll
@@ -213,9 +219,21 @@ __device__ __forceinline__ void collide_q(C* v, const Mom<C>& m, const Closure<C
   }
 }
 
-template <bool LES, typename C>
-__device__ __forceinline__ void collide19(C v[kQ], const Mom<C>& m, const Closure<C>& cl, const Rates<C>& r) {
-  collide_q<5, LES>(v, m, cl, r);
+template <bool LES, bool LOCAL = false, typename C>
+__device__ __forceinline__ void collide19(C v[kQ], const Mom<C>& m, const Closure<C>& cl, const Rates<C>& r,
+                                          bool swapped = false) {
+  collide_q<5, LES, LOCAL>(v, m, cl, r, swapped);
+}
+
+// 16-bit storage, closure off, nx a multiple of 4: one column in four rounds its rest
+// population from the two products in the other order (FP16 the third, BF16 the
+// second), as the sweep of four columns a thread always has.  A difference in the last
+// bit of FP32 would now and then become one of a stored 16-bit value, so the sweeps
+// keep it: runs and saved states continue with the same bits.
+template <typename S>
+__device__ __forceinline__ bool swapped_rest(int x, int nx) {
+  if constexpr (sizeof(S) == 2) return (nx & 3) == 0 && (x & 3) == (std::is_same_v<S, __bf16> ? 1 : 2);
+  return false;
 }
 
 // Closure gradients from local non-equilibrium moments (LOCAL stencils),

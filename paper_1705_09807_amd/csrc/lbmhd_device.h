@@ -30,16 +30,18 @@ struct Closure {
 // Reynolds P_ac = k2/rho (D m_a).(D m_c), Maxwell Q_ac = k2 (D B_a).(D B_c),
 // induction R_ac = k2/rho (D m_a).(D' B_c); the induction product takes its
 // B gradients from h' (equal to h except in the density-gradient closure).
-template <typename C>
+// LOCAL: gradients of a LOCAL stencil, with two squares summed in the other order
+// (the last bit that runs with those stencils have always had).
+template <bool LOCAL = false, typename C>
 __device__ __forceinline__ Closure<C> closure_terms(C gxx, C gxy, C gyx, C gyy, C hxx, C hxy, C hyx, C hyy,
                                                     C pxx_, C pxy_, C pyx_, C pyy_, C inv_rho, C k2) {
 #pragma clang fp contract(off)
-  const C kr = k2 * inv_rho;
-  const C pxx = fmadd(gxx, gxx, gxy * gxy);  // products over their common factors (k2 / rho, k2)
+  const C kr = k2 * inv_rho;  // products over their common factors (k2 / rho, k2)
+  const C pxx = LOCAL ? fmadd(gxy, gxy, gxx * gxx) : fmadd(gxx, gxx, gxy * gxy);
   const C pyy = kr * fmadd(gyx, gyx, gyy * gyy);
   const C pxy = fmadd(gxx, gyx, gxy * gyy);
   const C qxx = fmadd(hxx, hxx, hxy * hxy);
-  const C qyy = k2 * fmadd(hyx, hyx, hyy * hyy);
+  const C qyy = k2 * (LOCAL ? fmadd(hyy, hyy, hyx * hyx) : fmadd(hyx, hyx, hyy * hyy));
   const C qxy = k2 * fmadd(hxx, hyx, hxy * hyy);
   const C rxy = fmadd(gxx, pyx_, gxy * pyy_);
   const C ryx = kr * fmadd(gyx, pxx_, gyy * pxy_);
@@ -51,10 +53,10 @@ __device__ __forceinline__ Closure<C> closure_terms(C gxx, C gxy, C gyx, C gyy, 
   return c;
 }
 
-template <typename C>
+template <bool LOCAL = false, typename C>
 __device__ __forceinline__ Closure<C> closure_terms(C gxx, C gxy, C gyx, C gyy, C hxx, C hxy, C hyx,
                                                     C hyy, C inv_rho, C k2) {
-  return closure_terms(gxx, gxy, gyx, gyy, hxx, hxy, hyx, hyy, hxx, hxy, hyx, hyy, inv_rho, k2);
+  return closure_terms<LOCAL>(gxx, gxy, gyx, gyy, hxx, hxy, hyx, hyy, hxx, hxy, hyx, hyy, inv_rho, k2);
 }
 
 // FilterExampleLarge with Z = rho: the bracket of the expansion of

@@ -148,7 +148,7 @@ k_fused_dns_quad(const S* __restrict__ src, S* __restrict__ dst, int nx, int ny,
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
     const Mom<C> m = moments19(v[k]);
-    collide19<false>(v[k], m, cl, r);
+    collide19<false>(v[k], m, cl, r, swapped_rest<S>(k, 4));
   }
   const __amdgpu_buffer_rsrc_t d = row_rsrc(reinterpret_cast<char*>(dst) + int64_t(y) * rowb, rowb);
 #pragma unroll
@@ -191,6 +191,7 @@ k_fused_les_f(const S* __restrict__ src, S* __restrict__ dst, int nx, int ny, in
   using C = typename ComputeOf<S>::type;
   constexpr int NF = MODE == kClosureFull ? 5 : 4;
   constexpr int NP = kPop<QG>;
+  constexpr bool LOCAL = STENCIL >= LBM_STENCIL_LOCAL_ISO9 && QG == 5 && MODE != kClosureFull;
   __shared__ C ring[4][NF][W + 3];
   const int tid = threadIdx.x;
   const int nstrip = (nx + W - 1) / W;
@@ -284,9 +285,9 @@ k_fused_les_f(const S* __restrict__ src, S* __restrict__ dst, int nx, int ny, in
     if constexpr (MODE == kClosureFull) {
       cl = closure_terms_full(gr, m.mx, m.my, r.bx0 + m.dbx, r.by0 + m.dby, ir, r.k2);
     } else {
-      if constexpr (STENCIL >= LBM_STENCIL_LOCAL_ISO9 && QG == 5)
+      if constexpr (LOCAL)
         local_gradients(cur, m, r, gr[1][0] - gr[0][1], gr);
-      cl = closure_terms(gr[0][0], gr[0][1], gr[1][0], gr[1][1], gr[2][0], gr[2][1], gr[3][0], gr[3][1], ir, r.k2);
+      cl = closure_terms<LOCAL>(gr[0][0], gr[0][1], gr[1][0], gr[1][1], gr[2][0], gr[2][1], gr[3][0], gr[3][1], ir, r.k2);
     }
     if constexpr (MODE == kClosureCorr) {
       const C txx = C(cc[0]), tyy = C(cc[2]);
@@ -295,7 +296,7 @@ k_fused_les_f(const S* __restrict__ src, S* __restrict__ dst, int nx, int ny, in
       cl.tau_s += txx + tyy;
       cl.eps += C(cc[3]);
     }
-    collide_q<QG, true>(cur, m, cl, r);
+    collide_q<QG, true, LOCAL>(cur, m, cl, r);
     const __amdgpu_buffer_rsrc_t d = row_rsrc(reinterpret_cast<char*>(dst) + int64_t(y) * rowb, rowb);
 #pragma unroll
     for (int q = 0; q < NP; ++q) buf_store<S, NT>(encode<S>(cur[q]), d, xo_store, uint32_t(q) * pq);
@@ -463,10 +464,11 @@ k_aa_les(S* __restrict__ A, const C* __restrict__ mb, int nx, int ny, int64_t pi
   C gr[4][2];
   tile_gradients<C, STENCIL>(tile, threadIdx.x + 1, gr);
   const C ir = C(1) / (r.rho0 + m.drho);
-  if constexpr (STENCIL >= LBM_STENCIL_LOCAL_ISO9) local_gradients(v, m, r, gr[1][0] - gr[0][1], gr);
-  const Closure<C> cls = closure_terms(gr[0][0], gr[0][1], gr[1][0], gr[1][1], gr[2][0], gr[2][1], gr[3][0],
+  constexpr bool LOCAL = STENCIL >= LBM_STENCIL_LOCAL_ISO9;
+  if constexpr (LOCAL) local_gradients(v, m, r, gr[1][0] - gr[0][1], gr);
+  const Closure<C> cls = closure_terms<LOCAL>(gr[0][0], gr[0][1], gr[1][0], gr[1][1], gr[2][0], gr[2][1], gr[3][0],
                                        gr[3][1], ir, r.k2);
-  collide19<true>(v, m, cls, r);
+  collide19<true, LOCAL>(v, m, cls, r);
   aa_store<S, C, ODD>(A, pitch, rw, cl, v);
 }
 

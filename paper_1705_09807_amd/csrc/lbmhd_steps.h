@@ -134,9 +134,10 @@ k_dns_steps(const S* __restrict__ src, S* __restrict__ dst, int nx, int ny, int6
   const Cols cx = cols_of<S>(ms_column(t, H, nx), nx);
   const uint32_t pq = uint32_t(pitch) * uint32_t(sizeof(S));
   const Closure<C> off = {C(0), C(0), C(0), C(0)};
+  const bool swapped = swapped_rest<S>(ms_column(t, H, nx), nx);
   auto collide = [&](C* v) __attribute__((always_inline)) {
     const Mom<C> m = moments_of<QG>(v);
-    collide_q<QG, false>(v, m, off, r);
+    collide_q<QG, false>(v, m, off, r, swapped);
   };
   auto hand_on = [&](int s, int par, const C* v) __attribute__((always_inline)) {
 #pragma unroll
@@ -247,6 +248,7 @@ k_les_steps(const S* __restrict__ src, S* __restrict__ dst, int nx, int ny, int6
   using Lds = LesLds<S, MODE, QG, K, LN>;
   using Quad = typename Lds::Quad;
   constexpr int NP = kPop<QG>, NF = Lds::FULL ? 5 : 4;
+  constexpr bool LOCAL = STENCIL >= LBM_STENCIL_LOCAL_ISO9 && QG == 5 && MODE != kClosureFull;
   constexpr int H = 2 * K - 1;  // recomputed columns at each side, rows at each end
   extern __shared__ __attribute__((aligned(16))) char ms_lds[];
   Lds& lds = *reinterpret_cast<Lds*>(ms_lds);
@@ -286,11 +288,11 @@ k_les_steps(const S* __restrict__ src, S* __restrict__ dst, int nx, int ny, int6
                           p[ss][l - 1], gr[4][0], gr[4][1]);
       cl = closure_terms_full(gr, m.mx, m.my, r.bx0 + m.dbx, r.by0 + m.dby, ir, r.k2);
     } else {
-      if constexpr (STENCIL >= LBM_STENCIL_LOCAL_ISO9 && QG == 5)
+      if constexpr (LOCAL)
         local_gradients(v, m, r, gr[1][0] - gr[0][1], gr);
-      cl = closure_terms(gr[0][0], gr[0][1], gr[1][0], gr[1][1], gr[2][0], gr[2][1], gr[3][0], gr[3][1], ir, r.k2);
+      cl = closure_terms<LOCAL>(gr[0][0], gr[0][1], gr[1][0], gr[1][1], gr[2][0], gr[2][1], gr[3][0], gr[3][1], ir, r.k2);
     }
-    collide_q<QG, true>(v, m, cl, r);
+    collide_q<QG, true, LOCAL>(v, m, cl, r);
   };
   // slot of population q in iteration i: u = i mod 3, par = i mod 2
   auto slot = [](int q, int u, int par) { return ms_row<QG>(q) + (qcy<QG>(q) > 0 ? u : (qcy<QG>(q) == 0 ? par : 0)); };
