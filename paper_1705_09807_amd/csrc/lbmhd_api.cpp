@@ -21,6 +21,7 @@ struct lbm_ctx {
   int64_t t = 0;
   bool initialized = false;
   bool mlp_set = false;  // learned closure: a network has been installed
+  bool recorded = false;  // a graph may hold calls of this context (see note_recording)
   bool cus_known = false;  // compute-unit count queried
   bool lag_ready = false;  // lagged schedule: moment set t & 1 holds step t - 1
   int32_t corr_every = 1;  // learned closure: correction evaluated every corr_every steps
@@ -117,9 +118,7 @@ int check_ctx(const lbm_ctx* ctx, bool need_state) {
   return LBM_OK;
 }
 
-// Whether work on this stream is being recorded into a graph.  A recorded run of
-// n steps must leave the state in the buffer that n one-step sweeps leave it in,
-// so that an even number of steps can be replayed.
+// Whether work on this stream is being recorded into a graph.
 bool capturing(hipStream_t st) {
   if (!st) return false;  // the null stream cannot be captured
   hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
@@ -128,6 +127,21 @@ bool capturing(hipStream_t st) {
     return true;
   }
   return s != hipStreamCaptureStatusNone;
+}
+
+// A recorded call reads or writes a fixed one of the two buffers and is replayed at
+// times of the same parity, so from the first recording on the buffer that holds the
+// state follows the parity of t.
+void note_recording(lbm_ctx* ctx) {
+  if (!ctx->recorded) ctx->recorded = capturing(ctx->L.stream);
+}
+
+// The launch for a state placed at time t.
+lbm::Launch at_time(lbm_ctx* ctx, int64_t t) {
+  note_recording(ctx);
+  lbm::Launch L = ctx->L;
+  L.cur ^= int((ctx->t ^ t) & 1);
+  return L;
 }
 
 }  // namespace
@@ -174,9 +188,11 @@ int lbm_init_kh_jet(lbm_ctx* ctx, const lbm_kh_params* kh) {
     if (!std::isfinite(v)) return fail(LBM_EINVAL, "kh params must be finite");
   if (!(kh->delta_over_L > 0.0) || !(kh->rho0 > 0.0))
     return fail(LBM_EINVAL, "delta_over_L and rho0 must be > 0");
-  hipError_t e = lbm::launch_init_kh(ctx->L, *kh);
+  const lbm::Launch L = at_time(ctx, 0);
+  hipError_t e = lbm::launch_init_kh(L, *kh);
   if (e != hipSuccess) return hip_fail(e, "lbm_init_kh_jet");
   ctx->t = 0;
+  ctx->L.cur = L.cur;
   ctx->initialized = true;
   ctx->lag_ready = false;
   ctx->corr_ready = false;
@@ -192,9 +208,11 @@ int lbm_init_sech2_jet(lbm_ctx* ctx, const lbm_sech2_params* jet) {
     if (!std::isfinite(v)) return fail(LBM_EINVAL, "jet params must be finite");
   if (!(jet->rho0 > 0.0) || jet->k < 1 || jet->reserved != 0)
     return fail(LBM_EINVAL, "rho0 must be > 0, k >= 1 and reserved 0");
-  hipError_t e = lbm::launch_init_sech2(ctx->L, *jet);
+  const lbm::Launch L = at_time(ctx, 0);
+  hipError_t e = lbm::launch_init_sech2(L, *jet);
   if (e != hipSuccess) return hip_fail(e, "lbm_init_sech2_jet");
   ctx->t = 0;
+  ctx->L.cur = L.cur;
   ctx->initialized = true;
   ctx->lag_ready = false;
   ctx->corr_ready = false;
@@ -206,9 +224,11 @@ int lbm_init_from_moments(lbm_ctx* ctx, const double* mom_dev, int64_t t) {
   if (rc != LBM_OK) return rc;
   if (!mom_dev || !aligned(mom_dev)) return fail(LBM_EINVAL, "mom_dev must be a non-NULL 256-byte aligned pointer");
   if (t < 0) return fail(LBM_EINVAL, "t must be >= 0");
-  hipError_t e = lbm::launch_init_moments(ctx->L, t, mom_dev);
+  const lbm::Launch L = at_time(ctx, t);
+  hipError_t e = lbm::launch_init_moments(L, t, mom_dev);
   if (e != hipSuccess) return hip_fail(e, "lbm_init_from_moments");
   ctx->t = t;
+  ctx->L.cur = L.cur;
   ctx->initialized = true;
   ctx->lag_ready = false;
   ctx->corr_ready = false;
@@ -234,10 +254,13 @@ int lbm_step(lbm_ctx* ctx, int64_t n) {
     if (e != hipSuccess) return hip_fail(e, "lbm_step");
     ctx->lag_ready = true;
   }
-  const int most = n > 1 && !capturing(ctx->L.stream) ? lbm::multi_steps(ctx->L) : 1;
-  for (int64_t k = 0; k < n;) {
-    // as few sweeps as possible, of nearly equal numbers of steps
-    const int64_t left = n - k, sweeps = (left + most - 1) / most;
+  if (n > 0) note_recording(ctx);
+  const int most = n > 1 ? lbm::multi_steps(ctx->L) : 1;
+  // as few sweeps as possible, of nearly equal numbers of steps; as many as steps in
+  // parity once a graph holds steps (4096^2 FP32 closure off, 10 steps: 4 sweeps for 3)
+  int64_t sweeps = (n + most - 1) / most;
+  if (ctx->recorded) sweeps += (n - sweeps) & 1;
+  for (int64_t left = n; sweeps > 0; --sweeps) {
     const int adv = int((left + sweeps - 1) / sweeps);
     hipError_t e;
     if (adv > 1) {
@@ -250,7 +273,7 @@ int lbm_step(lbm_ctx* ctx, int64_t n) {
     ctx->corr_ready = ctx->L.learned;
     ctx->L.cur ^= 1;
     ctx->t += adv;
-    k += adv;
+    left -= adv;
   }
   return LBM_OK;
 }
@@ -267,6 +290,7 @@ int lbm_moments(lbm_ctx* ctx, double* out_dev) {
   int rc = check_ctx(ctx, true);
   if (rc != LBM_OK) return rc;
   if (!out_dev || !aligned(out_dev)) return fail(LBM_EINVAL, "out_dev must be a non-NULL 256-byte aligned pointer");
+  note_recording(ctx);
   hipError_t e = lbm::launch_moments(ctx->L, ctx->t, out_dev);
   return e == hipSuccess ? LBM_OK : hip_fail(e, "lbm_moments");
 }
@@ -275,6 +299,7 @@ int lbm_get_state(lbm_ctx* ctx, double* out_dev) {
   int rc = check_ctx(ctx, true);
   if (rc != LBM_OK) return rc;
   if (!out_dev || !aligned(out_dev)) return fail(LBM_EINVAL, "out_dev must be a non-NULL 256-byte aligned pointer");
+  note_recording(ctx);
   hipError_t e = lbm::launch_get_state(ctx->L, ctx->t, out_dev);
   return e == hipSuccess ? LBM_OK : hip_fail(e, "lbm_get_state");
 }
@@ -284,9 +309,11 @@ int lbm_set_state(lbm_ctx* ctx, const double* in_dev, int64_t t) {
   if (rc != LBM_OK) return rc;
   if (!in_dev || !aligned(in_dev)) return fail(LBM_EINVAL, "in_dev must be a non-NULL 256-byte aligned pointer");
   if (t < 0) return fail(LBM_EINVAL, "t must be >= 0");
-  hipError_t e = lbm::launch_set_state(ctx->L, t, in_dev);
+  const lbm::Launch L = at_time(ctx, t);
+  hipError_t e = lbm::launch_set_state(L, t, in_dev);
   if (e != hipSuccess) return hip_fail(e, "lbm_set_state");
   ctx->t = t;
+  ctx->L.cur = L.cur;
   ctx->initialized = true;
   ctx->lag_ready = false;
   ctx->corr_ready = false;
@@ -348,6 +375,7 @@ int lbm_closure_correction(lbm_ctx* ctx, float* out_dev) {
   if (!ctx->L.learned || !ctx->mlp_set)
     return fail(LBM_ESTATE, "needs closure = LBM_CLOSURE_LEARNED and an installed network");
   if (!out_dev || !aligned(out_dev)) return fail(LBM_EINVAL, "out_dev must be a non-NULL 256-byte aligned pointer");
+  note_recording(ctx);
   hipError_t e = lbm::launch_correction(ctx->L, ctx->t, out_dev);
   return e == hipSuccess ? LBM_OK : hip_fail(e, "lbm_closure_correction");
 }

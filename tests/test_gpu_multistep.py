@@ -115,3 +115,36 @@ def test_captured_steps_replay(dtype, delta, n):
             x, y = a.get_state(), b.get_state()
         st.synchronize()
         assert torch.equal(x, y), k
+
+
+@pytest.mark.parametrize("dtype,delta,between", [("fp32", 0.0, (4, 5, 1)), ("fp32", 4.0, (3, 2, 1)),
+                                                 ("fp16", 0.0, (7, 3)), ("fp64", 2.0, (6, 2))])
+def test_replay_after_further_steps(dtype, delta, between):
+    """Steps taken and states placed between the recording and a replay leave the graph valid at even times."""
+    _require_gpu()
+    st = torch.cuda.Stream()
+    with torch.cuda.stream(st):
+        a = _start(640, 600, dtype=dtype, delta=delta)
+        b = _start(640, 600, dtype=dtype, delta=delta)
+        a.step(4)
+        b.step(4)
+    st.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=st):
+        a.step(2)
+    for k in range(3):
+        with torch.cuda.stream(st):
+            for n in between:  # an even number together
+                a.step(n)
+                b.step(n)
+            if k == 1:
+                x = b.get_state()
+                a.set_state(x, t=7)
+                b.set_state(x, t=7)
+                a.step(1)
+                b.step(1)
+            graph.replay()
+            b.step(2)
+            x, y = a.get_state(), b.get_state()
+        st.synchronize()
+        assert torch.equal(x, y), k
