@@ -11,8 +11,8 @@ timed region.  Inputs are synthetic (analytic initial state), resident in HBM
 before timing starts.
 
 Prints one JSON line: MLUPS (lattice updates of both runs per second), the
-HBM roofline of the dominant kernel (the 4096^2 sweep) from HIP events on the
-stream the kernels run on, and the FP64 CPU oracle timed on a bounded sample
+HBM roofline of the dominant kernel (the 4096^2 sweep; a launch moves the state once
+and advances several timesteps) from HIP events on the stream the kernels run on, and the FP64 CPU oracle timed on a bounded sample
 of the same workload.
 """
 
@@ -41,7 +41,13 @@ NU = ETA = 2e-4
 GHOST = 1.6
 LES_N, LES_DELTA = 1024, 4.0
 DNS_N = 4096
-KERNEL_SRC = os.path.join(ROOT, "paper_1705_09807_amd", "csrc", "lbmhd_kernels.hip")
+# sources of the kernels that the counter summaries in profiles/ were taken on
+KERNEL_SRC = [os.path.join(ROOT, "paper_1705_09807_amd", "csrc", f)
+              for f in ("lbmhd_kernels.hip", "lbmhd_steps.h", "lbmhd_steps_16bit.hip", "lbmhd_cell.h", "lbmhd_device.h")]
+# Most timesteps per launch of the fused schedule on the large grids here (the
+# library's ms_most_steps), by closure off / on; the in-place schedule and the
+# learned closure take one.
+STEPS_PER_LAUNCH = {False: 4, True: 3}
 
 
 def log(*a):
@@ -52,12 +58,19 @@ def kernel_source_hash() -> str:
     """SHA-256 (16 hex digits) of the kernel source with comments and blank
     space removed, so an edit of comments alone keeps a counter summary valid
     while any change of code invalidates it."""
-    with open(KERNEL_SRC) as fh:
-        text = fh.read()
+    text = ""
+    for src in [KERNEL_SRC] if isinstance(KERNEL_SRC, str) else KERNEL_SRC:
+        with open(src) as fh:
+            text += fh.read()
     text = re.sub(r"/\*.*?\*/", "", text, flags=re.S)
     text = re.sub(r"//[^\n]*", "", text)
     text = re.sub(r"\s+", " ", text).strip()
     return hashlib.sha256(text.encode()).hexdigest()[:16]
+
+
+def launches(steps: int, most: int) -> int:
+    """Launches of a run of `steps` steps, at most `most` of them per launch."""
+    return -(-steps // most)
 
 
 def measured_traffic(kernel: str, lups: int):
@@ -905,23 +918,29 @@ def main() -> int:
     lups_step = LES_N * LES_N + DNS_N * DNS_N
     value = K * lups_step / T / 1e6
     dns_lups = DNS_N * DNS_N
-    achieved = BYTES_PER_LUP_FP32 * dns_lups / (dns_ms * 1e-3) / 1e9
+    # a launch reads and writes the state once and advances it by several steps
+    dns_launches = sum(launches(c, STEPS_PER_LAUNCH[False]) for c, *_ in chunks)
+    dns_launch_ms = dns_ms * K / dns_launches
+    achieved = BYTES_PER_LUP_FP32 * dns_lups / (dns_launch_ms * 1e-3) / 1e9
     traffic = measured_traffic("fused_dns_fp32", dns_lups)
     roofline = {
         "bound": "hbm",
-        "kernel": "k_fused_dns_pair<float, float, true, 5> (4096^2 DNS sweep)",
+        "kernel": "k_dns_steps<float, 5, 4, 256> (4096^2 DNS, up to four timesteps per launch)",
         "achieved": round(achieved, 1),
         "peak": HBM_PEAK_GBS,
         "unit": "GB/s",
         "frac": round(achieved / HBM_PEAK_GBS, 4),
         "traffic": traffic,
         "algorithmic_bytes_per_launch": BYTES_PER_LUP_FP32 * dns_lups,
-        "avg_launch_us": round(dns_ms * 1e3, 2),
+        "avg_launch_us": round(dns_launch_ms * 1e3, 2),
+        "steps_per_launch": round(K / dns_launches, 3),
+        "avg_step_us": round(dns_ms * 1e3, 2),
     }
-    les_bw = BYTES_PER_LUP_FP32 * LES_N * LES_N / (les_ms * 1e-3) / 1e9
+    les_launches = sum(launches(c, STEPS_PER_LAUNCH[True]) for c, *_ in chunks)
+    les_bw = BYTES_PER_LUP_FP32 * LES_N * LES_N * les_launches / (les_ms * K * 1e-3) / 1e9
     extra = {
-        "les1024": {"mlups": round(LES_N * LES_N / (les_ms * 1e-3) / 1e6, 1), "avg_launch_us": round(les_ms * 1e3, 2),
-                    "algorithmic_GBps": round(les_bw, 1),
+        "les1024": {"mlups": round(LES_N * LES_N / (les_ms * 1e-3) / 1e6, 1), "avg_step_us": round(les_ms * 1e3, 2),
+                    "steps_per_launch": round(K / les_launches, 3), "algorithmic_GBps": round(les_bw, 1),
                     "note": "state (160 MB) is Infinity-Cache resident: not an HBM figure"},
         "dns4096": {"mlups": round(dns_lups / (dns_ms * 1e-3) / 1e6, 1)},
     }
@@ -933,19 +952,20 @@ def main() -> int:
         # timed over the same steps from the same state; the end states are
         # compared with the synchronous fused run (relative L2 of m and of
         # B - mean B), beside the closure's own effect (sync LES vs Delta = 0).
-        # values per update: fused 19 + 19; in place synchronous 19 + 4 then
-        # 19 + 4 + 19; in place lagged 19 + 4 + 19 + 4.
+        # values per update and launch: fused 19 + 19; in place synchronous 19 + 4 then
+        # 19 + 4 + 19; in place lagged 19 + 4 + 19 + 4.  Steps per launch (of a pair of
+        # launches, in place synchronous): most.
         variants = [
-            ("les4096", "fused", {}, 38, "k_fused_les_f<float> (plain closure, Delta=4)"),
-            ("les4096_full", "fused", dict(closure="full"), 38, "k_fused_les_f<float, ..., full> (density-gradient terms)"),
-            ("les4096_local_iso9", "fused", dict(grad_stencil="local_iso9"), 38,
-             "k_fused_les_f<float, LOCAL_ISO9> (gradients from non-equilibrium moments)"),
-            ("les4096_aa", "aa", {}, 65, "k_aa_moments + k_aa_les (in place, synchronous)"),
-            ("les4096_aa_lagged", "aa_lagged", {}, 46, "k_aa_les_lagged (in place, lagged gradients)"),
+            ("les4096", "fused", {}, 38, 3, "k_les_steps<float> (plain closure, Delta=4)"),
+            ("les4096_full", "fused", dict(closure="full"), 38, 3, "k_les_steps<float, ..., full> (density-gradient terms)"),
+            ("les4096_local_iso9", "fused", dict(grad_stencil="local_iso9"), 38, 3,
+             "k_les_steps<float, LOCAL_ISO9> (gradients from non-equilibrium moments)"),
+            ("les4096_aa", "aa", {}, 65, 1, "k_aa_moments + k_aa_les (in place, synchronous)"),
+            ("les4096_aa_lagged", "aa_lagged", {}, 46, 1, "k_aa_les_lagged (in place, lagged gradients)"),
             # D2Q9 vector distribution (27 populations): compared with the D2Q5 run
-            ("les4096_d2q9", "fused", dict(mag_lattice="d2q9"), 54, "k_fused_les_f<float, ..., QG=9> (D2Q9 g)"),
-            ("dns4096_d2q9", "fused", dict(mag_lattice="d2q9", delta=0.0), 54,
-             "k_fused_dns_pair<float, QG=9> (D2Q9 g, closure off)"),
+            ("les4096_d2q9", "fused", dict(mag_lattice="d2q9"), 54, 3, "k_les_steps<float, ..., QG=9> (D2Q9 g)"),
+            ("dns4096_d2q9", "fused", dict(mag_lattice="d2q9", delta=0.0), 54, 3,
+             "k_dns_steps<float, QG=9> (D2Q9 g, closure off)"),
         ]
         nsteps = 20 + args.les4096_steps
 
@@ -961,7 +981,7 @@ def main() -> int:
         mom_off = sd.moments()
         del sd
         mom_sync = None
-        for key, sched, kw, vals, kname in variants:
+        for key, sched, kw, vals, most, kname in variants:
             args_v = dict(nx=DNS_N, ny=DNS_N, nu=NU, eta=ETA, delta=LES_DELTA, dtype="fp32", schedule=sched,
                           b_ref=bref, device=dev, stream=stream, **ghost)
             args_v.update(kw)
@@ -974,9 +994,11 @@ def main() -> int:
             b.record(stream)
             torch.cuda.synchronize(dev)
             ms = a.elapsed_time(b) / args.les4096_steps
-            bw = vals * 4 * dns_lups / (ms * 1e-3) / 1e9
+            nl = launches(args.les4096_steps, most)
+            launch_ms = ms * args.les4096_steps / nl
+            bw = vals * 4 * dns_lups / (launch_ms * 1e-3) / 1e9
             rec = {"mlups": round(dns_lups / (ms * 1e-3) / 1e6, 1), "avg_step_us": round(ms * 1e3, 2),
-                   "bytes_per_lup": vals * 4, "achieved_GBps": round(bw, 1), "frac": round(bw / HBM_PEAK_GBS, 4),
+                   "steps_per_launch": round(args.les4096_steps / nl, 3), "bytes_per_lup_and_launch": vals * 4, "achieved_GBps": round(bw, 1), "frac": round(bw / HBM_PEAK_GBS, 4),
                    "kernel": kname}
             mom = sv.moments()
             if mom_sync is None:
@@ -989,17 +1011,19 @@ def main() -> int:
                 del mom
             extra[key] = rec
             if key == "les4096":
-                # the plain closure beyond the caches: one k_fused_les_f launch per step
+                # the plain closure beyond the caches: three steps per launch
                 roofline_plain = {
                     "bound": "hbm",
-                    "kernel": "k_fused_les_f<float, 512, 0, true, 0, 5> (4096^2 LES sweep, plain closure)",
+                    "kernel": "k_les_steps<float, 0, 0, 5, 3, 256> (4096^2 LES, plain closure, up to three timesteps per launch)",
                     "achieved": round(bw, 1),
                     "peak": HBM_PEAK_GBS,
                     "unit": "GB/s",
                     "frac": round(bw / HBM_PEAK_GBS, 4),
                     "traffic": measured_traffic("fused_les4096_fp32", dns_lups),
                     "algorithmic_bytes_per_launch": BYTES_PER_LUP_FP32 * dns_lups,
-                    "avg_launch_us": round(ms * 1e3, 2),
+                    "avg_launch_us": round(launch_ms * 1e3, 2),
+                    "steps_per_launch": round(args.les4096_steps / nl, 3),
+                    "avg_step_us": round(ms * 1e3, 2),
                     "target_frac": 0.70,
                 }
             log(f"{key}: {ms * 1e3:.1f} us/step, {bw:.0f} GB/s algorithmic")
@@ -1074,7 +1098,7 @@ def main() -> int:
         tflop = 8192 * (16768 + 2 * 64 * 64 + 16768) / (ms * 1e-3) / 1e12
         extra["mlp_train_step_8192"] = {"avg_step_us": round(ms * 1e3, 1), "rows": 8192,
                                         "tflops_fwd_bwd": round(tflop, 2),
-                                        "kernels": "k_mlp_pack + k_mlp_train (matrix cores) + k_mlp_reduce_groups + k_mlp_reduce + k_mlp_adam"}
+                                        "kernels": "k_mlp_train (matrix cores) + k_mlp_reduce<true>"}
         log(f"mlp train step (8192 rows): {ms * 1e3:.1f} us")
         del mlp, packed, Xt, Tt
 
@@ -1095,10 +1119,12 @@ def main() -> int:
                 b.record(stream)
                 torch.cuda.synchronize(dev)
                 ms = a.elapsed_time(b) / args.lowprec_steps
-                bw = 38 * width * lups8 / (ms * 1e-3) / 1e9
+                nl = launches(args.lowprec_steps, STEPS_PER_LAUNCH[delta8 != 0.0])
+                bw = 38 * width * lups8 * nl / (ms * args.lowprec_steps * 1e-3) / 1e9
                 key = f"{'les' if delta8 else 'dns'}8192_{dt}"
-                extra[key] = {"mlups": round(lups8 / (ms * 1e-3) / 1e6, 1), "avg_launch_us": round(ms * 1e3, 2),
-                              "bytes_per_lup": 38 * width, "achieved_GBps": round(bw, 1),
+                extra[key] = {"mlups": round(lups8 / (ms * 1e-3) / 1e6, 1), "avg_step_us": round(ms * 1e3, 2),
+                              "steps_per_launch": round(args.lowprec_steps / nl, 3),
+                              "bytes_per_lup_and_launch": 38 * width, "achieved_GBps": round(bw, 1),
                               "frac": round(bw / HBM_PEAK_GBS, 4)}
                 log(f"{key}: {ms * 1e3:.1f} us/step, {lups8 / (ms * 1e-3) / 1e6:.0f} MLUPS, {bw:.0f} GB/s")
                 del sim8
@@ -1159,8 +1185,7 @@ def main() -> int:
                     "nonfinite": int(d16["nonfinite"]), "e_kin": d16["e_kin"], "e_mag": d16["e_mag"],
                     # Parseval: the magnetic spectrum sums to the domain mean <|B|^2 / 2>
                     "parseval_em_rel": float(abs(em.sum().item() - d16["e_mag"]) / d16["e_mag"]),
-                    "spectra_kernels": "k_moments_out + k_fft_rows_big + k_fft_cols_big + k_bin_cols + "
-                                       "k_spectra_final"})
+                    "spectra_kernels": "k_moments_out + k_fft_rows + k_fft_cols + k_spectra_final"})
                 log(f"production 16384^2 spectra {ms_spec:.1f} ms")
                 del mom16, ek, em
             else:
