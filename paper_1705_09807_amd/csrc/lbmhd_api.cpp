@@ -4,6 +4,7 @@
 // lbmhd_kernels.hip and lbmhd_learned.hip.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdint>
 #include <cstdio>
@@ -255,16 +256,24 @@ int lbm_step(lbm_ctx* ctx, int64_t n) {
     ctx->lag_ready = true;
   }
   if (n > 0) note_recording(ctx);
-  const int most = n > 1 ? lbm::multi_steps(ctx->L) : 1;
-  // as few sweeps as possible, of nearly equal numbers of steps; as many as steps in
-  // parity once a graph holds steps (4096^2 FP32 closure off, 10 steps: 4 sweeps for 3)
+  const bool fused = ctx->L.schedule == LBM_SCHED_FUSED;
+  const int most = n > 1 ? (fused ? lbm::multi_steps(ctx->L) : lbm::multi_steps_inplace(ctx->L)) : 1;
+  // fused: as few sweeps as possible, of nearly equal numbers of steps; as many as steps
+  // in parity once a graph holds steps (4096^2 FP32 closure off, 10 steps: 4 sweeps for 3).
+  // In place: an even number of steps from even times.
   int64_t sweeps = (n + most - 1) / most;
   if (ctx->recorded) sweeps += (n - sweeps) & 1;
-  for (int64_t left = n; sweeps > 0; --sweeps) {
-    const int adv = int((left + sweeps - 1) / sweeps);
+  for (int64_t left = n; left > 0; --sweeps) {
+    int adv;
     hipError_t e;
+    if (fused) {
+      adv = int((left + sweeps - 1) / sweeps);
+    } else {
+      adv = ctx->t % 2 ? 1 : int(std::min<int64_t>(left, most));
+      if (adv > 1) adv &= ~1;
+    }
     if (adv > 1) {
-      e = lbm::launch_steps(ctx->L, adv);
+      e = fused ? lbm::launch_steps(ctx->L, adv) : lbm::launch_steps_inplace(ctx->L, adv);
     } else {
       const bool refresh = !ctx->corr_ready || ctx->t % ctx->corr_every == 0;
       e = lbm::launch_step(ctx->L, ctx->t, refresh);

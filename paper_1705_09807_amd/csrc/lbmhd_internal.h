@@ -37,7 +37,7 @@ struct Launch {
   size_t off_mb = 0;              // moment planes for the in-place closure sweep
                                   // (two sets for the lagged schedule, set t & 1
                                   // holding the moments of step t - 1)
-  size_t off_diag = 0;            // 5 FP64 moment planes for the diagnostics
+  size_t off_edges = 0;           // room of 5 FP64 planes: copied cells of the in-place sweeps of several steps
   size_t off_part = 0;            // per-block reduction partials
   size_t off_final = 0;           // final reduction values
   int diag_blocks = 0;
@@ -69,6 +69,10 @@ hipError_t launch_init_moments(const Launch& L, int64_t t, const double* mom);
 // only), and k > 1 steps in one launch, from buffer cur into the other one.
 int multi_steps(const Launch& L);
 hipError_t launch_steps(const Launch& L, int k);
+// In-place schedule: the most timesteps (1, 2 or 4) one sweep can advance from an even
+// time, and k = 2 or 4 steps in one.
+int multi_steps_inplace(const Launch& L);
+hipError_t launch_steps_inplace(const Launch& L, int k);
 // State at time t -> t + 1 (fused schedule: from buffer cur into the other
 // one); with the learned closure, corr_refresh = false
 // reuses the correction planes of an earlier step instead of evaluating the

@@ -81,6 +81,10 @@ __device__ __forceinline__ int ms_column(const MsTile& t, int halo, int nx) {
   const int x = min(t.x0 - halo + t.lane, t.x1 - 1 + halo);
   return x < 0 ? x + nx : (x >= nx ? x - nx : x);
 }
+// Whether the lane stores its column.
+__device__ __forceinline__ bool ms_owner(const MsTile& t, int halo) {
+  return t.lane >= halo && t.lane < halo + (t.x1 - t.x0);
+}
 // Row y (within a grid height of the grid) of the state before the launch.
 template <typename S, int QG>
 __device__ __forceinline__ void ms_pull(const S* __restrict__ src, uint32_t pq, int y, int ny, const Cols& cx,
@@ -119,22 +123,16 @@ struct DnsLds {
   S pop[K - 1][2][kPop<QG>][LN + 2];  // step, parity, population, lane + 1
 };
 
-template <typename S, int QG, int K, int LN>
-__global__ void __launch_bounds__(LN* K)
-k_dns_steps(const S* __restrict__ src, S* __restrict__ dst, int nx, int ny, int64_t pitch, int w, int ry,
-            Rates<typename ComputeOf<S>::type> r) {
+// `load` gets a row of the state before the launch, `store` takes one of that after it.
+template <typename S, int QG, int K, int LN, typename Load, typename Store>
+__device__ __forceinline__ void dns_march(DnsLds<S, QG, K, LN>& lds, const MsTile& t, bool swapped,
+                                          const Rates<typename ComputeOf<S>::type>& r, Load&& load, Store&& store) {
   using C = typename ComputeOf<S>::type;
   constexpr int NP = kPop<QG>, H = K - 1;  // H: recomputed columns at each side, rows at each end
-  extern __shared__ __attribute__((aligned(16))) char ms_lds[];
-  DnsLds<S, QG, K, LN>& lds = *reinterpret_cast<DnsLds<S, QG, K, LN>*>(ms_lds);
-  const MsTile t = ms_tile(nx, ny, w, ry, K);
   const int l = t.lane + 1;
   const int first = t.y0 - H, last = t.y1 - 1 + H;  // rows of the first step
   const int end = t.y1 + 2 * (K - 1);               // iterations first .. end - 1
-  const Cols cx = cols_of<S>(ms_column(t, H, nx), nx);
-  const uint32_t pq = uint32_t(pitch) * uint32_t(sizeof(S));
   const Closure<C> off = {C(0), C(0), C(0), C(0)};
-  const bool swapped = swapped_rest<S>(ms_column(t, H, nx), nx);
   auto collide = [&](C* v) __attribute__((always_inline)) {
     const Mom<C> m = moments_of<QG>(v);
     collide_q<QG, false>(v, m, off, r, swapped);
@@ -152,7 +150,7 @@ k_dns_steps(const S* __restrict__ src, S* __restrict__ dst, int nx, int ny, int6
     RawCell<S, QG> raw[2];
     auto iter = [&](int i, auto uc) __attribute__((always_inline)) {
       constexpr int u = decltype(uc)::value;
-      ms_pull<S, QG>(src, pq, min(i + 1, last), ny, cx, raw[u ^ 1]);
+      load(min(i + 1, last), raw[u ^ 1]);
       __builtin_amdgcn_sched_barrier(0);
       C v[NP];
       decode_raw<S, C, QG>(raw[u], v);
@@ -160,7 +158,7 @@ k_dns_steps(const S* __restrict__ src, S* __restrict__ dst, int nx, int ny, int6
       hand_on(0, u, v);
       __syncthreads();
     };
-    ms_pull<S, QG>(src, pq, first, ny, cx, raw[0]);
+    load(first, raw[0]);
     for (int i = first; i < end; i += 4) {  // past `end`: nothing is stored
       iter(i, N0{});
       iter(i + 1, N1{});
@@ -168,7 +166,6 @@ k_dns_steps(const S* __restrict__ src, S* __restrict__ dst, int nx, int ny, int6
       iter(i + 3, N1{});
     }
   } else {
-    const bool owner = t.lane >= H && t.lane < H + (t.x1 - t.x0);
     C row[4][NP];  // rows being completed, by the iteration (mod 4) that completes them
     auto iter = [&](int i, auto uc, auto sc) __attribute__((always_inline)) {
       constexpr int u = decltype(uc)::value, st = decltype(sc)::value;
@@ -183,7 +180,7 @@ k_dns_steps(const S* __restrict__ src, S* __restrict__ dst, int nx, int ny, int6
       if constexpr (st + 1 < K)
         hand_on(st, u & 1, v);
       else
-        ms_store<S, QG>(dst, pq, t, i - 2 * st, owner, cx, v);
+        store(i - 2 * st, v);
       __syncthreads();
     };
     auto loop = [&](auto sc) __attribute__((always_inline)) {
@@ -202,6 +199,24 @@ k_dns_steps(const S* __restrict__ src, S* __restrict__ dst, int nx, int ny, int6
       if (t.step == 3) loop(N3{});
     }
   }
+}
+
+template <typename S, int QG, int K, int LN>
+__global__ void __launch_bounds__(LN* K)
+k_dns_steps(const S* __restrict__ src, S* __restrict__ dst, int nx, int ny, int64_t pitch, int w, int ry,
+            Rates<typename ComputeOf<S>::type> r) {
+  using C = typename ComputeOf<S>::type;
+  constexpr int H = K - 1;
+  extern __shared__ __attribute__((aligned(16))) char ms_lds[];
+  const MsTile t = ms_tile(nx, ny, w, ry, K);
+  const int x = ms_column(t, H, nx);
+  const Cols cx = cols_of<S>(x, nx);
+  const bool owner = ms_owner(t, H);
+  const uint32_t pq = uint32_t(pitch) * uint32_t(sizeof(S));
+  dns_march(
+      *reinterpret_cast<DnsLds<S, QG, K, LN>*>(ms_lds), t, swapped_rest<S>(x, nx), r,
+      [&](int y, RawCell<S, QG>& c) __attribute__((always_inline)) { ms_pull<S, QG>(src, pq, y, ny, cx, c); },
+      [&](int y, const C* v) __attribute__((always_inline)) { ms_store<S, QG>(dst, pq, t, y, owner, cx, v); });
 }
 
 // LDS rows that hand population q from one step to the next: a row written in
@@ -240,24 +255,18 @@ struct LesLds {
 //               ring, and hands it on or, in the last group, stores it.
 // A barrier after each half.  (One barrier per iteration, as in k_dns_steps, takes
 // two more rows of registers and spills: 4096^2 FP32 201 against 178 us per step.)
-template <typename S, int STENCIL, int MODE, int QG, int K, int LN>
-__global__ void __launch_bounds__(LN* K)
-k_les_steps(const S* __restrict__ src, S* __restrict__ dst, int nx, int ny, int64_t pitch, int w, int ry,
-            Rates<typename ComputeOf<S>::type> r) {
+template <typename S, int STENCIL, int MODE, int QG, int K, int LN, typename Load, typename Store>
+__device__ __forceinline__ void les_march(LesLds<S, MODE, QG, K, LN>& lds, const MsTile& t,
+                                          const Rates<typename ComputeOf<S>::type>& r, Load&& load, Store&& store) {
   using C = typename ComputeOf<S>::type;
   using Lds = LesLds<S, MODE, QG, K, LN>;
   using Quad = typename Lds::Quad;
   constexpr int NP = kPop<QG>, NF = Lds::FULL ? 5 : 4;
   constexpr bool LOCAL = STENCIL >= LBM_STENCIL_LOCAL_ISO9 && QG == 5 && MODE != kClosureFull;
   constexpr int H = 2 * K - 1;  // recomputed columns at each side, rows at each end
-  extern __shared__ __attribute__((aligned(16))) char ms_lds[];
-  Lds& lds = *reinterpret_cast<Lds*>(ms_lds);
-  const MsTile t = ms_tile(nx, ny, w, ry, K);
   const int l = t.lane + 1;
   const int first = t.y0 - H, last = t.y1 - 1 + H;  // rows of the first step's moments
   const int end = t.y1 + 3 * (K - 1) + 1;           // iterations first .. end - 1
-  const Cols cx = cols_of<S>(ms_column(t, H, nx), nx);
-  const uint32_t pq = uint32_t(pitch) * uint32_t(sizeof(S));
 
   auto put = [&](int s, int sl, const C* v) __attribute__((always_inline)) {
     const Mom<C> m = moments_of<QG>(v);
@@ -308,7 +317,7 @@ k_les_steps(const S* __restrict__ src, S* __restrict__ dst, int nx, int ny, int6
     RawCell<S, QG> raw[3];
     auto iter = [&](int i, int par, auto uc) __attribute__((always_inline)) {
       constexpr int u0 = decltype(uc)::value, u1 = (u0 + 2) % 3, u2 = (u0 + 1) % 3;  // rows i, i - 1, i - 2
-      ms_pull<S, QG>(src, pq, min(i + 1, last), ny, cx, raw[u2]);
+      load(min(i + 1, last), raw[u2]);
       __builtin_amdgcn_sched_barrier(0);
       C v[NP];
       decode_raw<S, C, QG>(raw[u0], v);
@@ -319,14 +328,13 @@ k_les_steps(const S* __restrict__ src, S* __restrict__ dst, int nx, int ny, int6
       hand_on(0, u0, par, v);
       __syncthreads();
     };
-    ms_pull<S, QG>(src, pq, first, ny, cx, raw[0]);
+    load(first, raw[0]);
     for (int i = first, par = 0; i < end; i += 3, par ^= 1) {  // past `end`: nothing is stored
       iter(i, par, N0{});
       iter(i + 1, par ^ 1, N1{});
       iter(i + 2, par, N2{});
     }
   } else {
-    const bool owner = t.lane >= H && t.lane < H + (t.x1 - t.x0);
     C vs[3][NP];  // rows gathered and not yet collided
     auto iter = [&](int i, int par, auto uc, auto sc) __attribute__((always_inline)) {
       constexpr int u0 = decltype(uc)::value, u1 = (u0 + 2) % 3, u2 = (u0 + 1) % 3, st = decltype(sc)::value;
@@ -341,7 +349,7 @@ k_les_steps(const S* __restrict__ src, S* __restrict__ dst, int nx, int ny, int6
       if constexpr (st + 1 < K)
         hand_on(st, u0, par, v);
       else
-        ms_store<S, QG>(dst, pq, t, i - 3 * st - 1, owner, cx, v);
+        store(i - 3 * st - 1, v);
       __syncthreads();
     };
     auto loop = [&](auto sc) __attribute__((always_inline)) {
@@ -356,6 +364,23 @@ k_les_steps(const S* __restrict__ src, S* __restrict__ dst, int nx, int ny, int6
       if (t.step == 2) loop(N2{});
     }
   }
+}
+
+template <typename S, int STENCIL, int MODE, int QG, int K, int LN>
+__global__ void __launch_bounds__(LN* K)
+k_les_steps(const S* __restrict__ src, S* __restrict__ dst, int nx, int ny, int64_t pitch, int w, int ry,
+            Rates<typename ComputeOf<S>::type> r) {
+  using C = typename ComputeOf<S>::type;
+  constexpr int H = 2 * K - 1;
+  extern __shared__ __attribute__((aligned(16))) char ms_lds[];
+  const MsTile t = ms_tile(nx, ny, w, ry, K);
+  const Cols cx = cols_of<S>(ms_column(t, H, nx), nx);
+  const bool owner = ms_owner(t, H);
+  const uint32_t pq = uint32_t(pitch) * uint32_t(sizeof(S));
+  les_march<S, STENCIL, MODE, QG, K, LN>(
+      *reinterpret_cast<LesLds<S, MODE, QG, K, LN>*>(ms_lds), t, r,
+      [&](int y, RawCell<S, QG>& c) __attribute__((always_inline)) { ms_pull<S, QG>(src, pq, y, ny, cx, c); },
+      [&](int y, const C* v) __attribute__((always_inline)) { ms_store<S, QG>(dst, pq, t, y, owner, cx, v); });
 }
 
 // ---------------------------------------------------------------------------

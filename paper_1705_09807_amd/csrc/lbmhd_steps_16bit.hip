@@ -56,7 +56,10 @@ MsShape ms_shape(const Launch& L, int halo, int max_lanes, int per_cu_lds) {
 // against 3.7, 256^2 4.9 against 6.3.  16-bit storage with the closure off pays on
 // small grids, whose steps are bound by the launch (128^2 3.4 against 4.4, 180^2
 // 3.1 against 3.8), not where the one-step sweep keeps the state in L2 (256^2 4.7
-// against 4.2, 512^2 6.2 against 5.8), and again above (724^2 7.0 against 9.6).
+// against 4.2, 512^2 6.2 against 5.8), and again above (724^2 7.0 against 9.6).  Flat
+// grids of 16-bit storage, whose few rows per segment are mostly recomputed, stay
+// too (8000 x 64 closure on 14.3 against 12.1, 32768 x 20 off 14.0 against 10.7;
+// FP32 8000 x 64 13.7 against 15.6).
 int multi_steps(const Launch& L) {
   if (L.schedule != LBM_SCHED_FUSED || L.learned || L.nx < 16 || L.ny < 16) return 1;
   const int64_t cells = int64_t(L.nx) * L.ny;
@@ -64,10 +67,10 @@ int multi_steps(const Launch& L) {
   const bool les = L.k2 != 0.0;
   const int most = ms_most_steps(bytes, les, L.qg);
   if (!les) {
-    if (bytes == 2) return cells <= 40000 ? 3 : (cells >= 300000 ? most : 1);
+    if (bytes == 2) return cells <= 40000 ? 3 : (cells >= 300000 && L.ny >= 64 ? most : 1);
     return bytes == 8 && cells < 10000 ? 1 : most;
   }
-  if (bytes <= 4) return cells >= 360000 ? most : 1;
+  if (bytes <= 4) return cells >= 360000 && (bytes == 4 || L.ny >= 128) ? most : 1;
   return cells >= 400000 ? most : (cells >= (L.qg == 9 ? 140000 : 160000) ? 2 : 1);
 }
 

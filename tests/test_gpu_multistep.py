@@ -1,7 +1,7 @@
 """Sweeps of several timesteps per launch against one-step sweeps.
 
-lbm_step(n) of the fused schedule takes several steps per launch where the grid
-is large enough; lbm_step(1) always takes the one-step sweep, which the oracle
+lbm_step(n) takes several steps per launch where the grid is large enough (in
+place: two or four, from even times); lbm_step(1) always takes the one-step sweep, which the oracle
 tests pin.  Both evaluate the same per-cell arithmetic as written and round the
 states between the steps to the storage type, so the states must be equal bit
 for bit (tolerance 0).
@@ -145,6 +145,55 @@ def test_replay_after_further_steps(dtype, delta, between):
                 b.step(1)
             graph.replay()
             b.step(2)
+            x, y = a.get_state(), b.get_state()
+        st.synchronize()
+        assert torch.equal(x, y), k
+
+
+# in place: strips and segments of every remainder, one and several of each, and the
+# smallest numbers of rows and columns; smaller grids (the last two) take one-step sweeps
+IN_PLACE = [(4100, 2051, 9), (1999, 4100, 6), (249, 32768, 4), (32768, 250, 5), (40, 130, 6), (700, 601, 7)]
+
+
+@pytest.mark.parametrize("dtype", ["fp64", "fp32", "fp16", "bf16"])
+@pytest.mark.parametrize("schedule,delta,stencil", [("aa", 0.0, "iso9"), ("aa", 4.0, "iso9"), ("aa", 4.0, "local_iso9"),
+                                                    ("aa_lagged", 4.0, "iso9"), ("aa_lagged", 4.0, "central5")])
+@pytest.mark.parametrize("nx,ny,n", IN_PLACE)
+def test_in_place(nx, ny, n, schedule, delta, stencil, dtype):
+    _check(nx, ny, n, dtype=dtype, delta=delta, schedule=schedule, grad_stencil=stencil)
+
+
+@pytest.mark.parametrize("schedule,delta", [("aa", 0.0), ("aa", 4.0), ("aa_lagged", 4.0)])
+@pytest.mark.parametrize("stencil", ["central5", "local_central5"])
+def test_in_place_flat(schedule, delta, stencil):
+    """Few rows: every row of a block is one of its edges."""
+    if schedule == "aa_lagged" and stencil.startswith("local"):
+        pytest.skip("local gradients need the current populations")
+    _check(32768, 62, 6, dtype="fp32", delta=delta, schedule=schedule, grad_stencil=stencil)
+    _check(62, 32768, 6, dtype="fp32", delta=delta, schedule=schedule, grad_stencil=stencil)
+
+
+@pytest.mark.parametrize("schedule,delta", [("aa", 0.0), ("aa", 4.0), ("aa_lagged", 4.0)])
+def test_in_place_recorded(schedule, delta):
+    """Recorded at an even time, replayed after further eager steps."""
+    _require_gpu()
+    st = torch.cuda.Stream()
+    with torch.cuda.stream(st):
+        a = _start(1500, 1400, dtype="fp32", schedule=schedule, delta=delta)
+        b = _start(1500, 1400, dtype="fp32", schedule=schedule, delta=delta)
+        a.step(2)
+        b.step(2)
+    st.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=st):
+        a.step(4)
+    for k in range(3):
+        with torch.cuda.stream(st):
+            graph.replay()
+            a.step(5)
+            a.step(3)
+            for _ in range(12):
+                b.step(1)
             x, y = a.get_state(), b.get_state()
         st.synchronize()
         assert torch.equal(x, y), k
