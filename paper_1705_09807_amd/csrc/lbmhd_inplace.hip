@@ -188,7 +188,11 @@ struct LaggedLds {
   S pop[kMsRows<5>][LN + 2];
 };
 
-template <typename S, int STENCIL, int LN>
+//
+// LATE: row i + 2 is loaded after the collision of row i - 1, into its registers,
+// not row i + 1 at the start of iteration i, so that the loads run beside the
+// other group's stores of populations and not of planes.
+template <typename S, int STENCIL, bool LATE, int LN>
 __global__ void __launch_bounds__(LN * 2)
 k_aa_lagged_steps(S* A, typename ComputeOf<S>::type* mb, const S* rows, const S* cols,
                   const typename ComputeOf<S>::type* mrows, const typename ComputeOf<S>::type* mcols, EdgeShape e,
@@ -239,8 +243,10 @@ k_aa_lagged_steps(S* A, typename ComputeOf<S>::type* mb, const S* rows, const S*
     };
     auto iter = [&](int i, int par, auto uc) __attribute__((always_inline)) {
       constexpr int u0 = decltype(uc)::value, u1 = (u0 + 2) % 3, u2 = (u0 + 1) % 3;  // rows i, i - 1, i - 2
-      load(min(i + 1, last), raw[u2], pm[u2]);
-      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (!LATE) {
+        load(min(i + 1, last), raw[u2], pm[u2]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
       C v[kQ];
       decode_raw<S, C, 5>(raw[u0], v);
       const Mom<C> m = moments_of<5>(v);
@@ -249,11 +255,17 @@ k_aa_lagged_steps(S* A, typename ComputeOf<S>::type* mb, const S* rows, const S*
       __syncthreads();
       decode_raw<S, C, 5>(raw[u1], v);
       collide(lds.prev[u2], lds.prev[u1], lds.prev[u0], v);
+      if constexpr (LATE) {
+        __builtin_amdgcn_sched_barrier(0);
+        load(min(i + 2, last), raw[u1], pm[u1]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
 #pragma unroll
       for (int q = 0; q < kQ; ++q) lds.pop[slot(q, u0, par)][l] = encode<S>(v[q]);
       __syncthreads();
     };
     load(first, raw[0], pm[0]);
+    if constexpr (LATE) load(first + 1, raw[1], pm[1]);
     for (int i = first, par = 0; i < end; i += 3, par ^= 1) {  // past `end`: nothing is stored
       iter(i, par, N0{});
       iter(i + 1, par ^ 1, N1{});
@@ -338,9 +350,9 @@ static bool inplace_plan(const Launch& L, int k, InplacePlan& p) {
 // workgroups march and the copies are a launch of their own.  Measured, us per step,
 // several steps against one (closure off / synchronous / lagged gradients): FP32
 // 1024^2 20.0/38.9/27.9 against 24.3/40.9/29.7, 1448^2 26.3/51.1/44.5 against
-// 46.3/79.3/56.8, 4096^2 157/301/405 against 449/768/556; FP64 512^2 16.4/50.9/40.6
+// 46.3/79.3/56.8, 4096^2 157/301/368 against 449/768/556; FP64 512^2 16.4/50.9/40.6
 // against 12.8/23.0/16.7, 1024^2 32.0/52.6/43.7 against 45.7/78.6/57.1, 4096^2
-// 555/617/857 against 898/1527/1111; BF16 2048^2 47.1/80.7/69.2 against
+// 555/617/787 against 898/1527/1111; BF16 2048^2 47.1/80.7/69.2 against
 // 45.7/88.4/107.9, 4096^2 151/237/242 against 232/472/452.
 int multi_steps_inplace(const Launch& L) {
   InplacePlan p;
@@ -397,9 +409,19 @@ static hipError_t launch_inplace_typed(const Launch& L, int k) {
   if (L.schedule == LBM_SCHED_AA_LAGGED) {
     constexpr size_t lds = sizeof(LaggedLds<S, LN>);
     static_assert(lds <= 160 * 1024, "LDS of a compute unit");
-    if (L.stencil == LBM_STENCIL_ISO9)
-      return launch_inplace<S, true, 2, LN>(L, &k_aa_lagged_steps<S, LBM_STENCIL_ISO9, LN>, lds);
-    return launch_inplace<S, true, 2, LN>(L, &k_aa_lagged_steps<S, LBM_STENCIL_CENTRAL5, LN>, lds);
+    // late loads beyond the caches, with storage of 4 and 8 bytes (4096^2 FP32 368 us per step
+    // against 404, FP64 787 against 854, 3000^2 FP32 201 against 206; 2048^2 FP32 96
+    // against 88, 4096^2 BF16 262 against 239)
+    auto go = [&](auto late) {
+      constexpr bool LATE = decltype(late)::value;
+      if (L.stencil == LBM_STENCIL_ISO9)
+        return launch_inplace<S, true, 2, LN>(L, &k_aa_lagged_steps<S, LBM_STENCIL_ISO9, LATE, LN>, lds);
+      return launch_inplace<S, true, 2, LN>(L, &k_aa_lagged_steps<S, LBM_STENCIL_CENTRAL5, LATE, LN>, lds);
+    };
+    if constexpr (sizeof(S) >= 4) {
+      if (int64_t(L.nx) * L.ny * kQ * int(sizeof(S)) >= (512 << 20)) return go(std::true_type{});
+    }
+    return go(std::false_type{});
   }
   constexpr size_t lds = sizeof(LesLds<S, kClosurePlain, 5, 2, LN>);
   switch (L.stencil) {
