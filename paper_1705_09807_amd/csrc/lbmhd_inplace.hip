@@ -144,7 +144,7 @@ k_aa_dns_steps(S* A, const S* rows, const S* cols, EdgeShape e, int pitch, Rates
   const Cols cx = cols_of<S>(ms_column(t, H, e.nx), e.nx);
   const bool owner = ms_owner(t, H);
   const uint32_t pq = uint32_t(pitch) * uint32_t(sizeof(S));
-  dns_march(
+  dns_march<S, 5, K, LN, 1>(
       *reinterpret_cast<DnsLds<S, 5, K, LN>*>(ms_lds), t, false, r,
       [&](int y, RawCell<S, 5>& c) __attribute__((always_inline)) { f.load(y, [&](int q, S v) { c.v[q] = v; }); },
       [&](int y, const C* v) __attribute__((always_inline)) { aa_scatter<S>(A, pq, t, y, e.ny, owner, cx, v); });

@@ -123,8 +123,9 @@ struct DnsLds {
   S pop[K - 1][2][kPop<QG>][LN + 2];  // step, parity, population, lane + 1
 };
 
-// `load` gets a row of the state before the launch, `store` takes one of that after it.
-template <typename S, int QG, int K, int LN, typename Load, typename Store>
+// `load` gets a row of the state before the launch, AHEAD (1 or 3) iterations before it is
+// collided, `store` takes a row of the state after it.
+template <typename S, int QG, int K, int LN, int AHEAD, typename Load, typename Store>
 __device__ __forceinline__ void dns_march(DnsLds<S, QG, K, LN>& lds, const MsTile& t, bool swapped,
                                           const Rates<typename ComputeOf<S>::type>& r, Load&& load, Store&& store) {
   using C = typename ComputeOf<S>::type;
@@ -147,23 +148,30 @@ __device__ __forceinline__ void dns_march(DnsLds<S, QG, K, LN>& lds, const MsTil
   using N3 = std::integral_constant<int, 3>;
 
   if (t.step == 0) {
-    RawCell<S, QG> raw[2];
+    constexpr int NR = AHEAD + 1;  // rows in flight and the current one
+    static_assert(4 % NR == 0, "the loop is unrolled by four");
+    RawCell<S, QG> raw[NR];
     auto iter = [&](int i, auto uc) __attribute__((always_inline)) {
       constexpr int u = decltype(uc)::value;
-      load(min(i + 1, last), raw[u ^ 1]);
+      load(min(i + AHEAD, last), raw[(u + AHEAD) % NR]);
       __builtin_amdgcn_sched_barrier(0);
       C v[NP];
-      decode_raw<S, C, QG>(raw[u], v);
+      decode_raw<S, C, QG>(raw[u % NR], v);
       collide(v);
-      hand_on(0, u, v);
+      hand_on(0, u & 1, v);
       __syncthreads();
     };
-    load(first, raw[0]);
-    for (int i = first; i < end; i += 4) {  // past `end`: nothing is stored
+#pragma unroll
+    for (int k = 0; k < AHEAD; ++k) load(min(first + k, last), raw[k]);
+    // small grids, of few iterations, leave at `end`; past it nothing is stored
+    for (int i = first; i < end; i += 4) {
       iter(i, N0{});
+      if (AHEAD > 1 && i + 1 >= end) break;
       iter(i + 1, N1{});
-      iter(i + 2, N0{});
-      iter(i + 3, N1{});
+      if (AHEAD > 1 && i + 2 >= end) break;
+      iter(i + 2, N2{});
+      if (AHEAD > 1 && i + 3 >= end) break;
+      iter(i + 3, N3{});
     }
   } else {
     C row[4][NP];  // rows being completed, by the iteration (mod 4) that completes them
@@ -186,8 +194,11 @@ __device__ __forceinline__ void dns_march(DnsLds<S, QG, K, LN>& lds, const MsTil
     auto loop = [&](auto sc) __attribute__((always_inline)) {
       for (int i = first; i < end; i += 4) {
         iter(i, N0{}, sc);
+        if (AHEAD > 1 && i + 1 >= end) break;
         iter(i + 1, N1{}, sc);
+        if (AHEAD > 1 && i + 2 >= end) break;
         iter(i + 2, N2{}, sc);
+        if (AHEAD > 1 && i + 3 >= end) break;
         iter(i + 3, N3{}, sc);
       }
     };
@@ -201,7 +212,7 @@ __device__ __forceinline__ void dns_march(DnsLds<S, QG, K, LN>& lds, const MsTil
   }
 }
 
-template <typename S, int QG, int K, int LN>
+template <typename S, int QG, int K, int LN, int AHEAD>
 __global__ void __launch_bounds__(LN* K)
 k_dns_steps(const S* __restrict__ src, S* __restrict__ dst, int nx, int ny, int64_t pitch, int w, int ry,
             Rates<typename ComputeOf<S>::type> r) {
@@ -213,7 +224,7 @@ k_dns_steps(const S* __restrict__ src, S* __restrict__ dst, int nx, int ny, int6
   const Cols cx = cols_of<S>(x, nx);
   const bool owner = ms_owner(t, H);
   const uint32_t pq = uint32_t(pitch) * uint32_t(sizeof(S));
-  dns_march(
+  dns_march<S, QG, K, LN, AHEAD>(
       *reinterpret_cast<DnsLds<S, QG, K, LN>*>(ms_lds), t, swapped_rest<S>(x, nx), r,
       [&](int y, RawCell<S, QG>& c) __attribute__((always_inline)) { ms_pull<S, QG>(src, pq, y, ny, cx, c); },
       [&](int y, const C* v) __attribute__((always_inline)) { ms_store<S, QG>(dst, pq, t, y, owner, cx, v); });
@@ -396,7 +407,7 @@ static hipError_t launch_k_steps(const Launch& L) {
   const MsShape sh = ms_shape(L, MODE != kClosureOff ? 2 * K - 1 : K - 1, LN, 160 * 1024 / sizeof(Lds));
   const auto kernel = [] {
     if constexpr (MODE == kClosureOff)
-      return &k_dns_steps<S, QG, K, LN>;
+      return &k_dns_steps<S, QG, K, LN, LN < 256 ? 3 : 1>;
     else
       return &k_les_steps<S, STENCIL, MODE, QG, K, LN>;
   }();
@@ -440,16 +451,29 @@ static hipError_t launch_k(const Launch& L, int k) {
   return k == 2 ? launch_k_stencil<S, MODE, QG, 2, LN>(L) : hipErrorInvalidValue;
 }
 
+// Closure off: rows loaded three ahead, by groups of 64 (FP64) or 128 columns whose
+// waves have the registers for it, on small grids, where a few rows per workgroup wait
+// for their loads (128^2 FP64 3.75 -> 2.8 us per step, 256^2 5.06 -> 3.98, 512^2
+// 7.96 -> 6.9, FP32 256^2 3.6 -> 3.3, BF16 384^2 4.8 -> 4.25; 512^2 FP32 4.61
+// against 4.88, 724^2 BF16 6.92 against 7.11).  The closure's rows wait for its arithmetic
+// instead (64^2 FP32, three steps 6.0 us each either way).
+template <typename S, int QG>
+static hipError_t launch_dns(const Launch& L, int k) {
+  const int64_t deep = sizeof(S) == 8 ? 400000 : (sizeof(S) == 4 ? 100000 : 300000);
+  if (int64_t(L.nx) * L.ny < deep) return launch_k<S, kClosureOff, QG, sizeof(S) == 8 ? 64 : 128>(L, k);
+  return launch_k<S, kClosureOff, QG, 256>(L, k);
+}
+
 template <typename S>
 static hipError_t launch_steps_typed(const Launch& L, int k) {
   constexpr int LN = sizeof(S) == 8 ? 128 : 256;  // closure on
   if constexpr (sizeof(S) >= 4) {
     if (L.qg == 9) {
-      if (L.k2 == 0.0) return launch_k<S, kClosureOff, 9, 256>(L, k);
+      if (L.k2 == 0.0) return launch_dns<S, 9>(L, k);
       return L.full ? launch_k<S, kClosureFull, 9, LN>(L, k) : launch_k<S, kClosurePlain, 9, LN>(L, k);
     }
   }
-  if (L.k2 == 0.0) return launch_k<S, kClosureOff, 5, 256>(L, k);
+  if (L.k2 == 0.0) return launch_dns<S, 5>(L, k);
   return L.full ? launch_k<S, kClosureFull, 5, LN>(L, k) : launch_k<S, kClosurePlain, 5, LN>(L, k);
 }
 

@@ -24,7 +24,7 @@ MsShape ms_shape(const Launch& L, int halo, int max_lanes, int per_cu_lds) {
   const int64_t cells = int64_t(L.nx) * L.ny;
   const int bytes = int(storage_bytes(L.dtype));
   MsShape s;
-  s.lanes = L.k2 == 0.0 && cells < 800000 ? 128 : max_lanes;
+  s.lanes = std::min(L.k2 == 0.0 && cells < 800000 ? 128 : max_lanes, max_lanes);
   s.lanes = std::min(s.lanes, (L.nx + 2 * halo + 63) / 64 * 64);
   const int most = s.lanes - 2 * halo;
   int strips = (L.nx + most - 1) / most;
@@ -51,12 +51,9 @@ MsShape ms_shape(const Launch& L, int halo, int max_lanes, int per_cu_lds) {
 // 512^2 11.2 against 9.3 us and 700^2 11.4 against 15.4; BF16 512^2 12.7 against
 // 9.6, 600^2 12.8 against 14.5; FP64 two steps 384^2 10.8 against 10.5, 512^2 12.6
 // against 16.3 (three: 13.7), three steps 1024^2 30.3 against 37.8 for two; D2Q9
-// FP64 256^2 10.3 against 8.9, 384^2 12.5 against 14.8; closure off, FP32 256^2 3.4
-// against 4.6 and 64^2 2.6 against 3.3, FP64 64^2 3.3-3.7 against 3.5, 128^2 3.5
-// against 3.7, 256^2 4.9 against 6.3.  16-bit storage with the closure off pays on
-// small grids, whose steps are bound by the launch (128^2 3.4 against 4.4, 180^2
-// 3.1 against 3.8), not where the one-step sweep keeps the state in L2 (256^2 4.7
-// against 4.2, 512^2 6.2 against 5.8), and again above (724^2 7.0 against 9.6).  Flat
+// FP64 256^2 10.3 against 8.9, 384^2 12.5 against 14.8; closure off, FP32 256^2 3.3
+// against 4.6 and 64^2 2.5 against 3.3, FP64 64^2 2.5 against 3.5, 256^2 4.0 against
+// 6.3, BF16 64^2 2.9 against 4.4, 256^2 3.7 against 4.1, 512^2 5.4 against 5.8.  Flat
 // grids of 16-bit storage, whose few rows per segment are mostly recomputed, stay
 // too (8000 x 64 closure on 14.3 against 12.1, 32768 x 20 off 14.0 against 10.7;
 // FP32 8000 x 64 13.7 against 15.6).
@@ -66,10 +63,7 @@ int multi_steps(const Launch& L) {
   const size_t bytes = storage_bytes(L.dtype);
   const bool les = L.k2 != 0.0;
   const int most = ms_most_steps(bytes, les, L.qg);
-  if (!les) {
-    if (bytes == 2) return cells <= 40000 ? 3 : (cells >= 300000 && L.ny >= 64 ? most : 1);
-    return bytes == 8 && cells < 10000 ? 1 : most;
-  }
+  if (!les) return bytes == 2 && cells >= 300000 && L.ny < 64 ? 1 : most;
   if (bytes <= 4) return cells >= 360000 && (bytes == 4 || L.ny >= 128) ? most : 1;
   return cells >= 400000 ? most : (cells >= (L.qg == 9 ? 140000 : 160000) ? 2 : 1);
 }
