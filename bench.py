@@ -45,8 +45,7 @@ DNS_N = 4096
 KERNEL_SRC = [os.path.join(ROOT, "paper_1705_09807_amd", "csrc", f)
               for f in ("lbmhd_kernels.hip", "lbmhd_steps.h", "lbmhd_steps_16bit.hip", "lbmhd_cell.h", "lbmhd_device.h")]
 # Most timesteps per launch of the fused schedule on the large grids here (the
-# library's ms_most_steps), by closure off / on; the in-place schedule and the
-# learned closure take one.
+# library's ms_most_steps), by closure off / on; the learned closure takes one.
 STEPS_PER_LAUNCH = {False: 4, True: 3}
 
 
@@ -925,7 +924,7 @@ def main() -> int:
     traffic = measured_traffic("fused_dns_fp32", dns_lups)
     roofline = {
         "bound": "hbm",
-        "kernel": "k_dns_steps<float, 5, 4, 256> (4096^2 DNS, up to four timesteps per launch)",
+        "kernel": "k_dns_steps<float, 5, 4, 256, 1> (4096^2 DNS, up to four timesteps per launch)",
         "achieved": round(achieved, 1),
         "peak": HBM_PEAK_GBS,
         "unit": "GB/s",
@@ -952,16 +951,15 @@ def main() -> int:
         # timed over the same steps from the same state; the end states are
         # compared with the synchronous fused run (relative L2 of m and of
         # B - mean B), beside the closure's own effect (sync LES vs Delta = 0).
-        # values per update and launch: fused 19 + 19; in place synchronous 19 + 4 then
-        # 19 + 4 + 19; in place lagged 19 + 4 + 19 + 4.  Steps per launch (of a pair of
-        # launches, in place synchronous): most.
+        # values per cell and sweep of up to `most` steps: fused 19 + 19; in place the
+        # same, lagged with the 4 moments read and written besides.
         variants = [
             ("les4096", "fused", {}, 38, 3, "k_les_steps<float> (plain closure, Delta=4)"),
             ("les4096_full", "fused", dict(closure="full"), 38, 3, "k_les_steps<float, ..., full> (density-gradient terms)"),
             ("les4096_local_iso9", "fused", dict(grad_stencil="local_iso9"), 38, 3,
              "k_les_steps<float, LOCAL_ISO9> (gradients from non-equilibrium moments)"),
-            ("les4096_aa", "aa", {}, 65, 1, "k_aa_moments + k_aa_les (in place, synchronous)"),
-            ("les4096_aa_lagged", "aa_lagged", {}, 46, 1, "k_aa_les_lagged (in place, lagged gradients)"),
+            ("les4096_aa", "aa", {}, 38, 2, "k_aa_edges + k_aa_les_steps (in place, synchronous)"),
+            ("les4096_aa_lagged", "aa_lagged", {}, 46, 2, "k_aa_edges + k_aa_lagged_steps (in place, lagged gradients)"),
             # D2Q9 vector distribution (27 populations): compared with the D2Q5 run
             ("les4096_d2q9", "fused", dict(mag_lattice="d2q9"), 54, 3, "k_les_steps<float, ..., QG=9> (D2Q9 g)"),
             ("dns4096_d2q9", "fused", dict(mag_lattice="d2q9", delta=0.0), 54, 3,
