@@ -6,10 +6,12 @@ Usage: ``python -m paper_1705_09807_amd.build`` or ``build()``.
 
 from __future__ import annotations
 
+import concurrent.futures
 import os
 import shutil
 import subprocess
 import sys
+import tempfile
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
@@ -27,7 +29,6 @@ FLAGS = [
     "-std=c++17",
     "--offload-arch=gfx950",
     "-fPIC",
-    "-shared",
     "-Wall",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
 ]
@@ -40,10 +41,7 @@ def hipcc() -> str:
     return path
 
 
-def build(verbose: bool = False) -> str:
-    """Compile csrc/ into liblbmhd.so (always recompiles).  Returns its path."""
-    tmp = LIB + ".tmp"
-    cmd = [hipcc(), *FLAGS, "-I", INCLUDE, "-I", CSRC, "-o", tmp] + [os.path.join(CSRC, s) for s in SOURCES]
+def _run(cmd, verbose: bool):
     if verbose:
         print(" ".join(cmd), flush=True)
     res = subprocess.run(cmd, capture_output=True, text=True)
@@ -52,6 +50,21 @@ def build(verbose: bool = False) -> str:
         raise RuntimeError("hipcc failed building liblbmhd.so")
     if verbose and res.stderr.strip():
         sys.stderr.write(res.stderr)
+
+
+def build(verbose: bool = False) -> str:
+    """Compile csrc/ into liblbmhd.so (always recompiles; the sources side by side).
+    Returns its path."""
+    tmp = LIB + ".tmp"
+    cc = hipcc()
+    with tempfile.TemporaryDirectory() as work:
+        objs = [os.path.join(work, s + ".o") for s in SOURCES]
+        with concurrent.futures.ThreadPoolExecutor(max_workers=min(8, os.cpu_count() or 1)) as pool:
+            jobs = [pool.submit(_run, [cc, *FLAGS, "-I", INCLUDE, "-I", CSRC, "-c", os.path.join(CSRC, s), "-o", o],
+                                verbose) for s, o in zip(SOURCES, objs)]
+            for job in jobs:
+                job.result()
+        _run([cc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp, *objs], verbose)
     os.replace(tmp, LIB)
     return LIB
 
