@@ -18,6 +18,8 @@
 // which hold hidden rows (2 b + j/4) * 8 + (l/32) * 4 + j % 4; the packed A
 // operands use the same permutation of the contraction index.
 #include <hip/hip_runtime.h>
+
+#include <algorithm>
 #include <math.h>
 #include <stdint.h>
 
@@ -802,44 +804,31 @@ __global__ void __launch_bounds__(256) k_gauss_taps(double sigma2, int R, double
 // serves up to B of them.  A fine cell x of the segment sits at [x % (B FACTOR)][x /
 // (B FACTOR)], so the lanes of a wave, B FACTOR cells apart, read consecutive
 // doubles.  Taps are uniform (scalar loads).  Bound by HBM (40 B read, 96 B /
-// FACTOR written per fine cell) and the LDS reads.  Measured 4096^2, FACTOR 4, R = 24:
-// one thread per output forming its own products (and three divisions) per tap
-// 1502 us, this form 441 us.
-template <int FACTOR>
+// FACTOR written per fine cell) and the LDS reads.  A workgroup takes several rows, the
+// next one's cells on their way during the filter, and SMALL (2 R at most 6 P) lets
+// three workgroups share a compute unit.  Measured 4096^2, FACTOR 4, R = 24: one
+// thread per output forming its own products (and three divisions) per tap 1502 us,
+// one row per workgroup 441 us; the whole filter with that 685 us, in this form 580
+// (FACTOR 8, R = 35: 545 and 510; FACTOR 16, R = 70: 667 and 552).
+template <int FACTOR, bool SMALL>
 struct FilterX {
   static constexpr int B = FACTOR <= 4 ? 2 : 1;       // outputs per lane
   static constexpr int P = B * FACTOR;                // fine cells between lanes
-  static constexpr int NI = 64 + (2 * 127 + P - 1) / P + 1;
+  static constexpr int E = SMALL ? 6 * P : 2 * 127;   // most fine cells past the lanes' own
+  static constexpr int N0 = 64 + (E + P - 1) / P;
+  static constexpr int NI = N0 + (N0 % 16 == 0);       // neighbouring cells in different banks
+  static constexpr int NE = (64 * P + E + 255) / 256;  // fine cells per thread
 };
 
-template <int FACTOR>
-__global__ void __launch_bounds__(256)
-k_filter_x(const double* __restrict__ mom, int nx, int ny, int R, const double* __restrict__ taps,
-           double* __restrict__ tmp) {
-  constexpr int B = FilterX<FACTOR>::B, P = FilterX<FACTOR>::P, NI = FilterX<FACTOR>::NI;
-  extern __shared__ double prod[];  // [12][P][NI]
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int k0 = 3 * __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int cx = nx / FACTOR;
-  const int X0 = blockIdx.x * 64 * B, y = blockIdx.y;
-  const int64_t n = (int64_t)nx * ny;
-  const double* row = mom + (int64_t)y * nx;
-  for (int e = tid; e < 64 * P + 2 * R; e += 256) {
-    int xx = (X0 * FACTOR - R + e) % nx;
-    if (xx < 0) xx += nx;
-    const double rho = row[xx], mx = row[n + xx], my = row[2 * n + xx], bx = row[3 * n + xx], by = row[4 * n + xx];
-    const double p[12] = {rho, mx, my, bx, by, mx * mx / rho, mx * my / rho, my * my / rho,
-                          bx * bx, bx * by, by * by, (mx * by - my * bx) / rho};
-#pragma unroll
-    for (int k = 0; k < 12; ++k) prod[(k * P + e % P) * NI + e / P] = p[k];
-  }
-  __syncthreads();
+// The three products at `v` of one row at the lane's outputs: out(product, output, value).
+template <int FACTOR, bool SMALL, typename Out>
+__device__ __forceinline__ void filter_row(const double* v, int R, const double* __restrict__ taps, Out&& out) {
+  constexpr int B = FilterX<FACTOR, SMALL>::B, P = FilterX<FACTOR, SMALL>::P, NI = FilterX<FACTOR, SMALL>::NI;
   double acc[3][B];
 #pragma unroll
   for (int k = 0; k < 3; ++k)
 #pragma unroll
     for (int b = 0; b < B; ++b) acc[k][b] = 0.0;
-  const double* v = prod + k0 * P * NI + lane;
   // position t of a lane's window is tap t - b FACTOR of its output b
   const int end = 2 * R + (B - 1) * FACTOR;
   for (int t0 = 0; t0 <= end; t0 += P) {
@@ -865,14 +854,59 @@ k_filter_x(const double* __restrict__ mom, int nx, int ny, int R, const double* 
         }
     }
   }
-  const int64_t cn = (int64_t)cx * ny;
-  const int X = X0 + lane * B;
 #pragma unroll
-  for (int k = 0; k < 3; ++k) {
-    double* out = tmp + (k0 + k) * cn + (int64_t)y * cx + X;
+  for (int k = 0; k < 3; ++k)
 #pragma unroll
-    for (int b = 0; b < B; ++b)
-      if (X + b < cx) out[b] = acc[k][b];
+    for (int b = 0; b < B; ++b) out(k, b, acc[k][b]);
+}
+
+template <int FACTOR, bool SMALL>
+__global__ void __launch_bounds__(256)
+k_filter_x(const double* __restrict__ mom, int nx, int ny, int R, int rows, const double* __restrict__ taps,
+           double* __restrict__ tmp) {
+  using F = FilterX<FACTOR, SMALL>;
+  constexpr int B = F::B, P = F::P, NI = F::NI, NE = F::NE;
+  extern __shared__ double prod[];  // [12][P][NI]
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int k0 = 3 * __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int cx = nx / FACTOR;
+  const int X0 = blockIdx.x * 64 * B, count = 64 * P + 2 * R;
+  const int y0 = blockIdx.y * rows, y1 = min(y0 + rows, ny);
+  const int64_t n = (int64_t)nx * ny, cn = (int64_t)cx * ny;
+  const double* v = prod + k0 * P * NI + lane;
+  int xs[NE];
+  double f[NE][5];
+#pragma unroll
+  for (int i = 0; i < NE; ++i) {
+    int xx = (X0 * FACTOR - R + min(tid + 256 * i, count - 1)) % nx;
+    xs[i] = xx < 0 ? xx + nx : xx;
+  }
+  auto load = [&](int y) __attribute__((always_inline)) {
+    const double* row = mom + (int64_t)y * nx;
+#pragma unroll
+    for (int i = 0; i < NE; ++i)
+#pragma unroll
+      for (int k = 0; k < 5; ++k) f[i][k] = row[k * n + xs[i]];
+  };
+  load(y0);
+  for (int y = y0; y < y1; ++y) {
+#pragma unroll
+    for (int i = 0; i < NE; ++i) {
+      const int e = tid + 256 * i;
+      if (e >= count) break;
+      const double rho = f[i][0], mx = f[i][1], my = f[i][2], bx = f[i][3], by = f[i][4];
+      const double p[12] = {rho, mx, my, bx, by, mx * mx / rho, mx * my / rho, my * my / rho,
+                            bx * bx, bx * by, by * by, (mx * by - my * bx) / rho};
+#pragma unroll
+      for (int k = 0; k < 12; ++k) prod[(k * P + e % P) * NI + e / P] = p[k];
+    }
+    __syncthreads();
+    if (y + 1 < y1) load(y + 1);
+    filter_row<FACTOR, SMALL>(v, R, taps, [&](int k, int b, double a) __attribute__((always_inline)) {
+      const int X = X0 + lane * B + b;
+      if (X < cx) tmp[(k0 + k) * cn + (int64_t)y * cx + X] = a;
+    });
+    __syncthreads();  // the row's products are read
   }
 }
 
@@ -1168,19 +1202,25 @@ size_t filter_work_bytes(int nx, int ny, int factor) {
   return 256 * sizeof(double) + (size_t)12 * (size_t)(nx / factor) * (size_t)ny * sizeof(double);
 }
 
-template <int FACTOR>
+template <int FACTOR, bool SMALL>
 static hipError_t launch_filter_x(const double* mom, int nx, int ny, int R, const double* taps, double* tmp,
                                   hipStream_t st) {
-  using F = FilterX<FACTOR>;
+  using F = FilterX<FACTOR, SMALL>;
+  if constexpr (!SMALL) {
+    if (2 * R <= 6 * F::P) return launch_filter_x<FACTOR, true>(mom, nx, ny, R, taps, tmp, st);
+  }
   const size_t lds = (size_t)12 * F::P * F::NI * sizeof(double);
+  const auto kernel = &k_filter_x<FACTOR, SMALL>;
   if (lds > 64 * 1024) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_filter_x<FACTOR>),
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
   }
-  const int per = 64 * F::B;
-  hipLaunchKernelGGL((k_filter_x<FACTOR>), dim3((nx / FACTOR + per - 1) / per, ny), dim3(256), lds, st, mom, nx, ny, R,
-                     taps, tmp);
+  const int per = 64 * F::B, across = (nx / FACTOR + per - 1) / per;
+  // rows per workgroup: up to 8, while there are 1024 workgroups
+  const int rows = (int)std::min<int64_t>(8, std::max<int64_t>(1, (int64_t)across * ny / 1024));
+  hipLaunchKernelGGL(kernel, dim3(across, (ny + rows - 1) / rows), dim3(256), lds, st, mom, nx, ny, R, rows, taps,
+                     tmp);
   return hipGetLastError();
 }
 
@@ -1194,11 +1234,11 @@ hipError_t launch_filter(const double* mom, int nx, int ny, int factor, double d
   if (e != hipSuccess) return e;
   const int cx = nx / factor, cy = ny / factor;
   switch (factor) {
-    case 1: e = launch_filter_x<1>(mom, nx, ny, R, taps, tmp, st); break;
-    case 2: e = launch_filter_x<2>(mom, nx, ny, R, taps, tmp, st); break;
-    case 4: e = launch_filter_x<4>(mom, nx, ny, R, taps, tmp, st); break;
-    case 8: e = launch_filter_x<8>(mom, nx, ny, R, taps, tmp, st); break;
-    default: e = launch_filter_x<16>(mom, nx, ny, R, taps, tmp, st);
+    case 1: e = launch_filter_x<1, false>(mom, nx, ny, R, taps, tmp, st); break;
+    case 2: e = launch_filter_x<2, false>(mom, nx, ny, R, taps, tmp, st); break;
+    case 4: e = launch_filter_x<4, false>(mom, nx, ny, R, taps, tmp, st); break;
+    case 8: e = launch_filter_x<8, false>(mom, nx, ny, R, taps, tmp, st); break;
+    default: e = launch_filter_x<16, false>(mom, nx, ny, R, taps, tmp, st);
   }
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_filter_y, dim3((cx + 63) / 64, (cy + kFilterYB - 1) / kFilterYB, 12), dim3(64), 0, st, tmp, nx,

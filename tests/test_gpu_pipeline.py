@@ -34,7 +34,9 @@ def _fields(nx, ny, seed):
 @pytest.mark.parametrize("nx,ny,factor,delta", [
     (4, 4, 1, 0.7), (16, 16, 16, 3.0), (127, 9, 1, 3.0), (129, 140, 1, 80.0), (254, 12, 2, 5.0), (258, 34, 2, 9.0),
     (508, 28, 4, 2.0), (516, 60, 4, 16.0), (512, 136, 4, 87.0), (520, 48, 8, 24.0), (1040, 272, 16, 64.0),
-    (48, 160, 16, 7.0)])
+    (48, 160, 16, 7.0),
+    # several rows per workgroup, the last one's fewer; both sides of 2 R = 6 P
+    (64, 3076, 4, 16.0), (64, 3076, 4, 17.0), (96, 3100, 2, 6.0), (96, 3080, 8, 24.0), (256, 3088, 16, 48.0)])
 def test_filter_segments(nx, ny, factor, delta):
     G = _gpu()
     print("filter", nx, ny, factor, delta, flush=True)
