@@ -1139,6 +1139,15 @@ static int fused_rows(int nx, int ny, int strip, int cus, int cap) {
   return (int)(ry < 1 ? 1 : ry);
 }
 
+// Strip width of the fused closure kernel and of the input vectors: 512 lanes for wide
+// grids with FP32 compute, 256 otherwise, 64 for narrow grids and where 256 would leave
+// more than 0.3 of their lanes idle (300 x 1000 FP32 11.2 against 13.7 us, 332 x 145 5.5
+// against 5.9; 400^2 8.5 against 8.8, 500^2 10.1 against 9.7).
+static int strip_width(int nx, bool fp32) {
+  if (fp32 && nx >= 1024) return 512;
+  return nx >= 256 && 10 * (int64_t)nx >= 7 * ((nx + 255) / 256 * 256) ? 256 : 64;
+}
+
 // Non-temporal stores pay off once the two population buffers no longer fit
 // in the 256 MB Infinity Cache; below that the next step re-reads them from it.
 static bool streaming_stores(const Launch& L) {
@@ -1150,8 +1159,12 @@ static void launch_les_s(const Launch& L, const S* src, S* dst, const Rates<C>& 
   // Segments sized for one workgroup per compute unit, two for k_fused_les_f
   // beyond the Infinity Cache (two fit a compute unit; measured 4096^2 FP32
   // 448 against 466 us, 8192^2 within 1 % either way, while the cache-resident
-  // 1024^2 sweep prefers one: 28.7 against 31.4 us).
-  const int per_cu = (sizeof(C) == 4 && NT) ? 2 : 1;
+  // 1024^2 sweep prefers one: 28.7 against 31.4 us).  64-lane strips, of two waves, march
+  // four to a compute unit (FP64 two where one would have six rows), so that each has fewer
+  // rows to wait for: 97 x 2675 FP16 26.0 -> 13.4 us, 200 x 1500 FP32 24.2 -> 12.3,
+  // 200^2 BF16 6.9 -> 5.1, 100 x 1000 FP64 12.2 -> 10.4 (180^2 FP64 6.9 against 7.2).
+  const bool two64 = (int64_t)L.ny * ((L.nx + W - 1) / W) >= 6 * (int64_t)L.cus;
+  const int per_cu = W == 64 ? (sizeof(C) == 4 ? 4 : (two64 ? 2 : 1)) : ((sizeof(C) == 4 && NT) ? 2 : 1);
   const int ry = fused_rows(L.nx, L.ny, W, L.cus * per_cu, sizeof(C) == 4 ? 128 : 64);
   const int strips = (L.nx + W - 1) / W, segs = (L.ny + ry - 1) / ry;
   // one-dimensional grid, numbered XCD-contiguously in the kernel
@@ -1211,19 +1224,19 @@ static void launch_fused(const Launch& L, const S* src, S* dst, const Rates<C>& 
                          dst, L.nx, L.ny, L.pitch, r);
     return;
   }
-  // Strip width: 512 lanes for wide grids with FP32 compute, 256 otherwise (the
-  // LDS ring of a 512-lane FP64 strip would exceed 64 KB), 64 for narrow
-  // grids.  Measured with the lattice-row layout and XCD-contiguous numbering:
+  // Strips of 512 lanes for wide grids (the LDS ring of a 512-lane FP64 strip would
+  // exceed 64 KB).  Measured with the lattice-row layout and XCD-contiguous numbering:
   // 256-lane strips (two or four workgroups per compute unit) against 512 take
   // 0-10 % longer with FP32 storage at 4096^2 and 8192^2 and 16-18 % longer
   // with FP16 at 8192^2 (with the earlier two-dimensional grids: up to 1.6x).
+  const int W = strip_width(L.nx, sizeof(C) == 4);
   if constexpr (sizeof(C) == 4) {
-    if (L.nx >= 1024) {
+    if (W == 512) {
       launch_les<S, C, 512, NT, QG>(L, src, dst, r, corr);
       return;
     }
   }
-  if (L.nx >= 256)
+  if (W == 256)
     launch_les<S, C, 256, NT, QG>(L, src, dst, r, corr);
   else
     launch_les<S, C, 64, NT, QG>(L, src, dst, r, corr);
@@ -1236,8 +1249,8 @@ static hipError_t cell_inputs_typed(const Launch& L, int64_t t, CellIn* out) {
   if (layout_at(L, t) != kLayoutPull) return hipErrorInvalidValue;
   const char* pk = static_cast<const char*>(L.work) + L.off_mlp;
   if constexpr (sizeof(typename ComputeOf<S>::type) == 4) {
-    const int W = L.nx >= 1024 ? 512 : (L.nx >= 256 ? 256 : 64);
-    const int ry = fused_rows(L.nx, L.ny, W, L.cus, 128);
+    const int W = strip_width(L.nx, true);
+    const int ry = fused_rows(L.nx, L.ny, W, W == 64 ? 4 * L.cus : L.cus, 128);
     const dim3 g(((L.nx + W - 1) / W) * ((L.ny + ry - 1) / ry));  // numbered XCD-contiguously in the kernel
     if (W == 512)
       hipLaunchKernelGGL((k_cell_inputs_f<S, 512>), g, dim3(512 + 64), 0, L.stream, current_buffer<S>(L), L.nx, L.ny,
