@@ -33,7 +33,9 @@ namespace lbm {
 template <int LOGN>
 struct Fft {
   static constexpr int N = 1 << LOGN;
-  static constexpr int LOGE = N <= 64 ? 2 : 4;
+  // radix 4 where few transforms fill the chip (n = 128, diagnostics, moments and spectra:
+  // 71 us a call against 76)
+  static constexpr int LOGE = N <= 128 ? 2 : 4;
   static constexpr int E = 1 << LOGE;         // points per thread, the radix of the passes
   static constexpr int T = N / E;             // threads per transform
   // transforms per workgroup: 512 threads where n allows, few on small grids, whose
