@@ -7,7 +7,7 @@
 // bin |Z|^2 / n^4; all FP64, all sums in a fixed order.
 //
 // A transform of n = 2^LOGN points is held in registers, E = 16 points per thread
-// (4 up to n = 64; Stockham form, radix E with one smaller pass at the end): in
+// (4 up to n = 128; Stockham form, radix E with one smaller pass at the end): in
 // every pass thread t of T = n / E has the points t + T m, m < E, does its
 // butterflies and exchanges the results through LDS, real parts first, then
 // imaginary parts, so up to n = 16384 fit one workgroup.  Both the first read and
