@@ -56,13 +56,16 @@ MsShape ms_shape(const Launch& L, int halo, int max_lanes, int per_cu_lds) {
 // 6.3, BF16 64^2 2.9 against 4.4, 256^2 3.7 against 4.1, 512^2 5.4 against 5.8.  Flat
 // grids of 16-bit storage, whose few rows per segment are mostly recomputed, stay
 // too (8000 x 64 closure on 14.3 against 12.1, 32768 x 20 off 14.0 against 10.7;
-// FP32 8000 x 64 13.7 against 15.6).
+// FP32 8000 x 64 13.7 against 15.6), and FP16 near 1024^2, whose conversions
+// outweigh what the caches leave to save there (closure off 15.6 against 13.7, on 21.9
+// against 21.1; 724^2 8.3 against 10.4, 1448^2 21.1 against 26.1).
 int multi_steps(const Launch& L) {
   if (L.schedule != LBM_SCHED_FUSED || L.learned || L.nx < 16 || L.ny < 16) return 1;
   const int64_t cells = int64_t(L.nx) * L.ny;
   const size_t bytes = storage_bytes(L.dtype);
   const bool les = L.k2 != 0.0;
   const int most = ms_most_steps(bytes, les, L.qg);
+  if (L.dtype == LBM_FP16 && L.nx >= 1024 && cells >= 800000 && cells < 1300000) return 1;
   if (!les) return bytes == 2 && cells >= 300000 && L.ny < 64 ? 1 : most;
   if (bytes <= 4) return cells >= 360000 && (bytes == 4 || L.ny >= 128) ? most : 1;
   return cells >= 400000 ? most : (cells >= (L.qg == 9 ? 140000 : 160000) ? 2 : 1);
