@@ -128,7 +128,7 @@ __device__ __forceinline__ void aa_scatter(S* A, uint32_t pq, const MsTile& t, i
   const uint32_t xc = st ? cx.c : kDropOffset, xe = st ? cx.e : kDropOffset, xw = st ? cx.w : kDropOffset;
 #pragma unroll
   for (int q = 0; q < kQ; ++q)
-    buf_store<S, false>(encode<S>(v[q]), qcy(q) > 0 ? rn : (qcy(q) < 0 ? rs : rc),
+    buf_store<S, false>(narrow<S>(v[q]), qcy(q) > 0 ? rn : (qcy(q) < 0 ? rs : rc),
                         qcx(q) > 0 ? xe : (qcx(q) < 0 ? xw : xc), uint32_t(q) * pq);
 }
 
@@ -209,7 +209,7 @@ k_aa_lagged_steps(S* A, typename ComputeOf<S>::type* mb, const S* rows, const S*
   const int end = t.y1 + 4;                         // iterations first .. end - 1
 
   auto collide = [&](const Quad* ss, const Quad* sc, const Quad* sn, C* v) __attribute__((always_inline)) {
-    const Mom<C> m = moments_of<5>(v);
+    const Mom<C> m = moments_of<5, kUnits<S>>(v);
     C gr[4][2];
     constexpr int kAtOnce = sizeof(C) == 8 ? 2 : 4;  // FP64: as many fields as there are registers
 #pragma unroll
@@ -223,7 +223,7 @@ k_aa_lagged_steps(S* A, typename ComputeOf<S>::type* mb, const S* rows, const S*
     const C ir = C(1) / (r.rho0 + m.drho);
     const Closure<C> cl =
         closure_terms(gr[0][0], gr[0][1], gr[1][0], gr[1][1], gr[2][0], gr[2][1], gr[3][0], gr[3][1], ir, r.k2);
-    collide_q<5, true>(v, m, cl, r);
+    collide_q<5, true, false, kUnits<S>>(v, m, cl, r);
   };
   // slot of population q (i mod 3 = u, i mod 2 = par), and of row i in the ring of six
   auto slot = [](int q, int u, int par) { return ms_row<5>(q) + (qcy(q) > 0 ? u : (qcy(q) == 0 ? par : 0)); };
@@ -248,12 +248,12 @@ k_aa_lagged_steps(S* A, typename ComputeOf<S>::type* mb, const S* rows, const S*
         __builtin_amdgcn_sched_barrier(0);
       }
       C v[kQ];
-      decode_raw<S, C, 5>(raw[u0], v);
-      const Mom<C> m = moments_of<5>(v);
+      widen_raw<S, C, 5>(raw[u0], v);
+      const Mom<C> m = moments_of<5, kUnits<S>>(v);
       lds.prev[u0][l] = pm[u0];
       lds.mom[six(u0, par)][l] = Quad{m.mx, m.my, m.dbx, m.dby};
       __syncthreads();
-      decode_raw<S, C, 5>(raw[u1], v);
+      widen_raw<S, C, 5>(raw[u1], v);
       collide(lds.prev[u2], lds.prev[u1], lds.prev[u0], v);
       if constexpr (LATE) {
         __builtin_amdgcn_sched_barrier(0);
@@ -261,7 +261,7 @@ k_aa_lagged_steps(S* A, typename ComputeOf<S>::type* mb, const S* rows, const S*
         __builtin_amdgcn_sched_barrier(0);
       }
 #pragma unroll
-      for (int q = 0; q < kQ; ++q) lds.pop[slot(q, u0, par)][l] = encode<S>(v[q]);
+      for (int q = 0; q < kQ; ++q) lds.pop[slot(q, u0, par)][l] = narrow<S>(v[q]);
       __syncthreads();
     };
     load(first, raw[0], pm[0]);
@@ -281,8 +281,8 @@ k_aa_lagged_steps(S* A, typename ComputeOf<S>::type* mb, const S* rows, const S*
     auto iter = [&](int i, int par, auto uc) __attribute__((always_inline)) {
       constexpr int u0 = decltype(uc)::value, u1 = (u0 + 2) % 3, u2 = (u0 + 1) % 3;  // rows i - 3, i - 4, i - 5
 #pragma unroll
-      for (int q = 0; q < kQ; ++q) vs[u0][q] = decode<C>(lds.pop[slot(q, u0, par)][l - qcx(q)]);
-      const Mom<C> m = moments_of<5>(vs[u0]);
+      for (int q = 0; q < kQ; ++q) vs[u0][q] = widen<C>(lds.pop[slot(q, u0, par)][l - qcx(q)]);
+      const Mom<C> m = moments_of<5, kUnits<S>>(vs[u0]);
       const int y = i - 3;
       const bool mine = y >= t.y0 && y < t.y1;
       const uint32_t xo = owner && mine ? uint32_t(x) * uint32_t(sizeof(C)) : kDropOffset;

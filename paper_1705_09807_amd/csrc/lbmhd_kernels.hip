@@ -59,19 +59,19 @@ k_fused_dns_pair(const S* __restrict__ src, S* __restrict__ dst, int nx, int ny,
   pull_pair<S, C, QG>(src, pitch, nx, rw, x, a, b);
   const Closure<C> cl = {C(0), C(0), C(0), C(0)};
   {
-    const Mom<C> m = moments_of<QG>(a);
-    collide_q<QG, false>(a, m, cl, r);
+    const Mom<C> m = moments_of<QG, kUnits<S>>(a);
+    collide_q<QG, false, false, kUnits<S>>(a, m, cl, r);
   }
   {
-    const Mom<C> m = moments_of<QG>(b);
-    collide_q<QG, false>(b, m, cl, r);
+    const Mom<C> m = moments_of<QG, kUnits<S>>(b);
+    collide_q<QG, false, false, kUnits<S>>(b, m, cl, r);
   }
   const uint32_t xo = uint32_t(x) * uint32_t(sizeof(S));
 #pragma unroll
   for (int q = 0; q < kPop<QG>; ++q) {
     nv2 t;
-    t.x = encode<S>(a[q]);
-    t.y = encode<S>(b[q]);
+    t.x = narrow<S>(a[q]);
+    t.y = narrow<S>(b[q]);
     store<NT>(reinterpret_cast<nv2*>(at(dst + q * pitch, rw.c, xo)), t);
   }
 }
@@ -88,11 +88,11 @@ k_fused_dns(const S* __restrict__ src, S* __restrict__ dst, int nx, int ny, int6
   const Cols cl = cols_of<S>(x, nx);
   C v[kPop<QG>];
   pull_cell<S, C, QG>(src, pitch, rw, cl, v);
-  const Mom<C> m = moments_of<QG>(v);
+  const Mom<C> m = moments_of<QG, kUnits<S>>(v);
   const Closure<C> zero = {C(0), C(0), C(0), C(0)};
-  collide_q<QG, false>(v, m, zero, r);
+  collide_q<QG, false, false, kUnits<S>>(v, m, zero, r);
 #pragma unroll
-  for (int q = 0; q < kPop<QG>; ++q) store<NT>(at(dst + q * pitch, rw.c, cl.c), encode<S>(v[q]));
+  for (int q = 0; q < kPop<QG>; ++q) store<NT>(at(dst + q * pitch, rw.c, cl.c), narrow<S>(v[q]));
 }
 
 // Closure off, 16-bit storage, nx a multiple of 4: four cells per thread, so
@@ -128,36 +128,36 @@ k_fused_dns_quad(const S* __restrict__ src, S* __restrict__ dst, int nx, int ny,
     const uint32_t so = uint32_t(q) * pq;
     const V4 t = buf_load_v<V4>(rr, x0, so);
     if (qcx(q) == 0) {
-      v[0][q] = decode<C>(t.x);
-      v[1][q] = decode<C>(t.y);
-      v[2][q] = decode<C>(t.z);
-      v[3][q] = decode<C>(t.w);
+      v[0][q] = widen<C>(t.x);
+      v[1][q] = widen<C>(t.y);
+      v[2][q] = widen<C>(t.z);
+      v[3][q] = widen<C>(t.w);
     } else if (qcx(q) > 0) {
-      v[0][q] = decode<C>(buf_load<S>(rr, xw, so));
-      v[1][q] = decode<C>(t.x);
-      v[2][q] = decode<C>(t.y);
-      v[3][q] = decode<C>(t.z);
+      v[0][q] = widen<C>(buf_load<S>(rr, xw, so));
+      v[1][q] = widen<C>(t.x);
+      v[2][q] = widen<C>(t.y);
+      v[3][q] = widen<C>(t.z);
     } else {
-      v[0][q] = decode<C>(t.y);
-      v[1][q] = decode<C>(t.z);
-      v[2][q] = decode<C>(t.w);
-      v[3][q] = decode<C>(buf_load<S>(rr, x4, so));
+      v[0][q] = widen<C>(t.y);
+      v[1][q] = widen<C>(t.z);
+      v[2][q] = widen<C>(t.w);
+      v[3][q] = widen<C>(buf_load<S>(rr, x4, so));
     }
   }
   const Closure<C> cl = {C(0), C(0), C(0), C(0)};
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
-    const Mom<C> m = moments19(v[k]);
-    collide19<false>(v[k], m, cl, r, swapped_rest<S>(k, 4));
+    const Mom<C> m = moments19<kUnits<S>>(v[k]);
+    collide19<false, false, kUnits<S>>(v[k], m, cl, r, swapped_rest<S>(k, 4));
   }
   const __amdgpu_buffer_rsrc_t d = row_rsrc(reinterpret_cast<char*>(dst) + int64_t(y) * rowb, rowb);
 #pragma unroll
   for (int q = 0; q < kQ; ++q) {
     V4 t;
-    t.x = encode<S>(v[0][q]);
-    t.y = encode<S>(v[1][q]);
-    t.z = encode<S>(v[2][q]);
-    t.w = encode<S>(v[3][q]);
+    t.x = narrow<S>(v[0][q]);
+    t.y = narrow<S>(v[1][q]);
+    t.z = narrow<S>(v[2][q]);
+    t.w = narrow<S>(v[3][q]);
     buf_store_v<V4, NT>(t, d, x0, uint32_t(q) * pq);
   }
 }
@@ -209,8 +209,8 @@ k_fused_les_f(const S* __restrict__ src, S* __restrict__ dst, int nx, int ny, in
   };
   auto put = [&](int sl, int widx, const RawCell<S, QG>& c) __attribute__((always_inline)) {
     C v[NP];
-    decode_raw<S, C, QG>(c, v);
-    const Mom<C> m = moments_of<QG>(v);
+    widen_raw<S, C, QG>(c, v);
+    const Mom<C> m = moments_of<QG, kUnits<S>>(v);
     ring[sl][0][widx] = m.mx;
     ring[sl][1][widx] = m.my;
     ring[sl][2][widx] = m.dbx;
@@ -278,15 +278,15 @@ k_fused_les_f(const S* __restrict__ src, S* __restrict__ dst, int nx, int ny, in
       grad3x3<C, STENCIL>(ring[sc][k][l + 1], ring[sc][k][l - 1], ring[sn][k][l], ring[ss][k][l], ring[sn][k][l + 1],
                           ring[sn][k][l - 1], ring[ss][k][l + 1], ring[ss][k][l - 1], gr[k][0], gr[k][1]);
     C cur[NP];
-    decode_raw<S, C, QG>(rcur, cur);
-    const Mom<C> m = moments_of<QG>(cur);
+    widen_raw<S, C, QG>(rcur, cur);
+    const Mom<C> m = moments_of<QG, kUnits<S>>(cur);
     const C ir = C(1) / (r.rho0 + m.drho);
     Closure<C> cl;
     if constexpr (MODE == kClosureFull) {
       cl = closure_terms_full(gr, m.mx, m.my, r.bx0 + m.dbx, r.by0 + m.dby, ir, r.k2);
     } else {
       if constexpr (LOCAL)
-        local_gradients(cur, m, r, gr[1][0] - gr[0][1], gr);
+        local_gradients<kUnits<S>>(cur, m, r, gr[1][0] - gr[0][1], gr);
       cl = closure_terms<LOCAL>(gr[0][0], gr[0][1], gr[1][0], gr[1][1], gr[2][0], gr[2][1], gr[3][0], gr[3][1], ir, r.k2);
     }
     if constexpr (MODE == kClosureCorr) {
@@ -296,10 +296,10 @@ k_fused_les_f(const S* __restrict__ src, S* __restrict__ dst, int nx, int ny, in
       cl.tau_s += txx + tyy;
       cl.eps += C(cc[3]);
     }
-    collide_q<QG, true, LOCAL>(cur, m, cl, r);
+    collide_q<QG, true, LOCAL, kUnits<S>>(cur, m, cl, r);
     const __amdgpu_buffer_rsrc_t d = row_rsrc(reinterpret_cast<char*>(dst) + int64_t(y) * rowb, rowb);
 #pragma unroll
-    for (int q = 0; q < NP; ++q) buf_store<S, NT>(encode<S>(cur[q]), d, xo_store, uint32_t(q) * pq);
+    for (int q = 0; q < NP; ++q) buf_store<S, NT>(narrow<S>(cur[q]), d, xo_store, uint32_t(q) * pq);
     __builtin_amdgcn_sched_barrier(0);
     put(slot(y + 2), widx, rt);
     if constexpr (MODE == kClosureCorr) {
@@ -349,17 +349,29 @@ __device__ __forceinline__ void aa_segment(int nx, int& x0, int& y) {
   y = vb / nseg;
 }
 
-template <typename S, typename C, bool ODD>
+// DECODED: in natural units, not in stored ones (for sums alone, which take the decode
+// into their additions).  ORDERED (FP16): widened after the last load is issued (in the
+// lagged sweep a few loads are otherwise moved behind the waits for the others).
+template <typename S, typename C, bool ODD, bool DECODED = false, bool ORDERED = false>
 __device__ __forceinline__ void aa_load(const S* __restrict__ A, int64_t pitch, const Rows& rw, const Cols& cl,
                                         C v[kQ]) {
+  S raw[kQ];
 #pragma unroll
   for (int q = 0; q < kQ; ++q) {
     if (!ODD) {
-      v[q] = decode<C>(*at(A + q * pitch, rw.c, cl.c));
+      raw[q] = *at(A + q * pitch, rw.c, cl.c);
     } else {
       const uint32_t xo = qcx(q) > 0 ? cl.w : (qcx(q) < 0 ? cl.e : cl.c);  // x - c_q
       const int64_t yo = qcy(q) > 0 ? rw.s : (qcy(q) < 0 ? rw.n : rw.c);
-      v[q] = decode<C>(*at(A + qopp(q) * pitch, yo, xo));
+      raw[q] = *at(A + qopp(q) * pitch, yo, xo);
+    }
+    if (!ORDERED) v[q] = DECODED ? decode<C>(raw[q]) : widen<C>(raw[q]);
+  }
+  if constexpr (ORDERED) {
+#pragma unroll
+    for (int q = 0; q < kQ; ++q) {
+      if constexpr (kUnits<S> != 1) asm volatile("" : "+v"(raw[q]));
+      v[q] = widen<C>(raw[q]);
     }
   }
 }
@@ -370,11 +382,11 @@ __device__ __forceinline__ void aa_store(S* __restrict__ A, int64_t pitch, const
 #pragma unroll
   for (int q = 0; q < kQ; ++q) {
     if (!ODD) {
-      *at(A + qopp(q) * pitch, rw.c, cl.c) = encode<S>(v[q]);
+      *at(A + qopp(q) * pitch, rw.c, cl.c) = narrow<S>(v[q]);
     } else {
       const uint32_t xo = qcx(q) > 0 ? cl.e : (qcx(q) < 0 ? cl.w : cl.c);  // x + c_q
       const int64_t yo = qcy(q) > 0 ? rw.n : (qcy(q) < 0 ? rw.s : rw.c);
-      *at(A + q * pitch, yo, xo) = encode<S>(v[q]);
+      *at(A + q * pitch, yo, xo) = narrow<S>(v[q]);
     }
   }
 }
@@ -389,9 +401,9 @@ __global__ void __launch_bounds__(kAARow) k_aa_dns(S* __restrict__ A, int nx, in
   const Cols cl = cols_of<S>(x, nx);
   C v[kQ];
   aa_load<S, C, ODD>(A, pitch, rw, cl, v);
-  const Mom<C> m = moments19(v);
+  const Mom<C> m = moments19<kUnits<S>>(v);
   const Closure<C> zero = {C(0), C(0), C(0), C(0)};
-  collide19<false>(v, m, zero, r);
+  collide19<false, false, kUnits<S>>(v, m, zero, r);
   aa_store<S, C, ODD>(A, pitch, rw, cl, v);
 }
 
@@ -407,7 +419,7 @@ k_aa_moments(const S* __restrict__ A, C* __restrict__ mb, int nx, int ny, int64_
   const Rows rw = rows_of<S>(y, ny, pitch);
   const Cols cl = cols_of<S>(x, nx);
   C v[kQ];
-  aa_load<S, C, ODD>(A, pitch, rw, cl, v);
+  aa_load<S, C, ODD, true>(A, pitch, rw, cl, v);
   const Mom<C> m = moments19(v);
   const int64_t n = (int64_t)nx * ny, c0 = (int64_t)y * nx + x;
   mb[c0] = m.mx;
@@ -460,15 +472,15 @@ k_aa_les(S* __restrict__ A, const C* __restrict__ mb, int nx, int ny, int64_t pi
   const Cols cl = cols_of<S>(x, nx);
   C v[kQ];
   aa_load<S, C, ODD>(A, pitch, rw, cl, v);
-  const Mom<C> m = moments19(v);
+  const Mom<C> m = moments19<kUnits<S>>(v);
   C gr[4][2];
   tile_gradients<C, STENCIL>(tile, threadIdx.x + 1, gr);
   const C ir = C(1) / (r.rho0 + m.drho);
   constexpr bool LOCAL = STENCIL >= LBM_STENCIL_LOCAL_ISO9;
-  if constexpr (LOCAL) local_gradients(v, m, r, gr[1][0] - gr[0][1], gr);
+  if constexpr (LOCAL) local_gradients<kUnits<S>>(v, m, r, gr[1][0] - gr[0][1], gr);
   const Closure<C> cls = closure_terms<LOCAL>(gr[0][0], gr[0][1], gr[1][0], gr[1][1], gr[2][0], gr[2][1], gr[3][0],
                                        gr[3][1], ir, r.k2);
-  collide19<true, LOCAL>(v, m, cls, r);
+  collide19<true, LOCAL, kUnits<S>>(v, m, cls, r);
   aa_store<S, C, ODD>(A, pitch, rw, cl, v);
 }
 
@@ -490,8 +502,8 @@ k_aa_les_lagged(S* __restrict__ A, const C* __restrict__ mb_prev, C* __restrict_
   const Rows rw = rows_of<S>(y, ny, pitch);
   const Cols cl = cols_of<S>(x, nx);
   C v[kQ];
-  aa_load<S, C, ODD>(A, pitch, rw, cl, v);
-  const Mom<C> m = moments19(v);
+  aa_load<S, C, ODD, false, kUnits<S> != 1>(A, pitch, rw, cl, v);
+  const Mom<C> m = moments19<kUnits<S>>(v);
   const int64_t n = (int64_t)nx * ny, c0 = (int64_t)y * nx + x;
   mb_next[c0] = m.mx;
   mb_next[n + c0] = m.my;
@@ -502,7 +514,7 @@ k_aa_les_lagged(S* __restrict__ A, const C* __restrict__ mb_prev, C* __restrict_
   const C ir = C(1) / (r.rho0 + m.drho);
   const Closure<C> cls = closure_terms(gr[0][0], gr[0][1], gr[1][0], gr[1][1], gr[2][0], gr[2][1], gr[3][0],
                                        gr[3][1], ir, r.k2);
-  collide19<true>(v, m, cls, r);
+  collide19<true, false, kUnits<S>>(v, m, cls, r);
   aa_store<S, C, ODD>(A, pitch, rw, cl, v);
 }
 
@@ -711,7 +723,7 @@ k_cell_inputs(const S* __restrict__ src, int nx, int ny, int64_t pitch, RestRef 
     yk = yk < 0 ? yk + ny : (yk >= ny ? yk - ny : yk);
     C v[kQ];
     pull_cell<S, C, 5>(src, pitch, rows_of<S>(yk, ny, pitch), cl, v);
-    const Mom<C> m = moments19(v);
+    const Mom<C> m = moments19<kUnits<S>>(v);
     const float r = float(C(ref.rho0) + m.drho);
     const float ux = float(m.mx) / r, uy = float(m.my) / r;
     const float bx = float(C(ref.bx0) + m.dbx), by = float(C(ref.by0) + m.dby);

@@ -103,7 +103,7 @@ __device__ __forceinline__ void ms_store(S* __restrict__ dst, uint32_t pq, const
   const __amdgpu_buffer_rsrc_t d = row_rsrc(reinterpret_cast<char*>(dst) + int64_t(mine ? y : t.y0) * rowb, rowb);
   const uint32_t xo = owner && mine ? cx.c : kDropOffset;
 #pragma unroll
-  for (int q = 0; q < kPop<QG>; ++q) buf_store<S, false>(encode<S>(v[q]), d, xo, uint32_t(q) * pq);
+  for (int q = 0; q < kPop<QG>; ++q) buf_store<S, false>(narrow<S>(v[q]), d, xo, uint32_t(q) * pq);
 }
 
 // Closure off, K steps per launch.  A workgroup holds K groups of T = blockDim / K
@@ -135,12 +135,12 @@ __device__ __forceinline__ void dns_march(DnsLds<S, QG, K, LN>& lds, const MsTil
   const int end = t.y1 + 2 * (K - 1);               // iterations first .. end - 1
   const Closure<C> off = {C(0), C(0), C(0), C(0)};
   auto collide = [&](C* v) __attribute__((always_inline)) {
-    const Mom<C> m = moments_of<QG>(v);
-    collide_q<QG, false>(v, m, off, r, swapped);
+    const Mom<C> m = moments_of<QG, kUnits<S>>(v);
+    collide_q<QG, false, false, kUnits<S>>(v, m, off, r, swapped);
   };
   auto hand_on = [&](int s, int par, const C* v) __attribute__((always_inline)) {
 #pragma unroll
-    for (int q = 0; q < NP; ++q) lds.pop[s][par][q][l] = encode<S>(v[q]);
+    for (int q = 0; q < NP; ++q) lds.pop[s][par][q][l] = narrow<S>(v[q]);
   };
   using N0 = std::integral_constant<int, 0>;
   using N1 = std::integral_constant<int, 1>;
@@ -156,7 +156,7 @@ __device__ __forceinline__ void dns_march(DnsLds<S, QG, K, LN>& lds, const MsTil
       load(min(i + AHEAD, last), raw[(u + AHEAD) % NR]);
       __builtin_amdgcn_sched_barrier(0);
       C v[NP];
-      decode_raw<S, C, QG>(raw[u % NR], v);
+      widen_raw<S, C, QG>(raw[u % NR], v);
       collide(v);
       hand_on(0, u & 1, v);
       __syncthreads();
@@ -179,7 +179,7 @@ __device__ __forceinline__ void dns_march(DnsLds<S, QG, K, LN>& lds, const MsTil
       constexpr int u = decltype(uc)::value, st = decltype(sc)::value;
 #pragma unroll
       for (int q = 0; q < NP; ++q)
-        row[(u + 1 + qcy<QG>(q)) & 3][q] = decode<C>(lds.pop[st - 1][(u & 1) ^ 1][q][l - qcx<QG>(q)]);
+        row[(u + 1 + qcy<QG>(q)) & 3][q] = widen<C>(lds.pop[st - 1][(u & 1) ^ 1][q][l - qcx<QG>(q)]);
       if constexpr (sizeof(S) == 8) __builtin_amdgcn_sched_barrier(0);  // registers: the reads before the collision
       C v[NP];
 #pragma unroll
@@ -280,14 +280,14 @@ __device__ __forceinline__ void les_march(LesLds<S, MODE, QG, K, LN>& lds, const
   const int end = t.y1 + 3 * (K - 1) + 1;           // iterations first .. end - 1
 
   auto put = [&](int s, int sl, const C* v) __attribute__((always_inline)) {
-    const Mom<C> m = moments_of<QG>(v);
+    const Mom<C> m = moments_of<QG, kUnits<S>>(v);
     lds.mom[s][sl][l] = Quad{m.mx, m.my, m.dbx, m.dby};
     if constexpr (NF == 5) lds.rho[s][sl][l] = m.drho;
   };
   // closure and collision of a cell whose row sits in slot sc of step s's ring, its
   // southern and northern neighbours' rows in ss and sn
   auto collide = [&](int s, int ss, int sc, int sn, C* v) __attribute__((always_inline)) {
-    const Mom<C> m = moments_of<QG>(v);
+    const Mom<C> m = moments_of<QG, kUnits<S>>(v);
     const auto& q = lds.mom[s];
     C gr[NF][2];
     // FP64: two fields at a time, which the registers have room for
@@ -309,16 +309,16 @@ __device__ __forceinline__ void les_march(LesLds<S, MODE, QG, K, LN>& lds, const
       cl = closure_terms_full(gr, m.mx, m.my, r.bx0 + m.dbx, r.by0 + m.dby, ir, r.k2);
     } else {
       if constexpr (LOCAL)
-        local_gradients(v, m, r, gr[1][0] - gr[0][1], gr);
+        local_gradients<kUnits<S>>(v, m, r, gr[1][0] - gr[0][1], gr);
       cl = closure_terms<LOCAL>(gr[0][0], gr[0][1], gr[1][0], gr[1][1], gr[2][0], gr[2][1], gr[3][0], gr[3][1], ir, r.k2);
     }
-    collide_q<QG, true, LOCAL>(v, m, cl, r);
+    collide_q<QG, true, LOCAL, kUnits<S>>(v, m, cl, r);
   };
   // slot of population q in iteration i: u = i mod 3, par = i mod 2
   auto slot = [](int q, int u, int par) { return ms_row<QG>(q) + (qcy<QG>(q) > 0 ? u : (qcy<QG>(q) == 0 ? par : 0)); };
   auto hand_on = [&](int s, int u, int par, const C* v) __attribute__((always_inline)) {
 #pragma unroll
-    for (int q = 0; q < NP; ++q) lds.pop[s][slot(q, u, par)][l] = encode<S>(v[q]);
+    for (int q = 0; q < NP; ++q) lds.pop[s][slot(q, u, par)][l] = narrow<S>(v[q]);
   };
   using N0 = std::integral_constant<int, 0>;
   using N1 = std::integral_constant<int, 1>;
@@ -331,10 +331,10 @@ __device__ __forceinline__ void les_march(LesLds<S, MODE, QG, K, LN>& lds, const
       load(min(i + 1, last), raw[u2]);
       __builtin_amdgcn_sched_barrier(0);
       C v[NP];
-      decode_raw<S, C, QG>(raw[u0], v);
+      widen_raw<S, C, QG>(raw[u0], v);
       put(0, u0, v);
       __syncthreads();
-      decode_raw<S, C, QG>(raw[u1], v);
+      widen_raw<S, C, QG>(raw[u1], v);
       collide(0, u2, u1, u0, v);
       hand_on(0, u0, par, v);
       __syncthreads();
@@ -350,7 +350,7 @@ __device__ __forceinline__ void les_march(LesLds<S, MODE, QG, K, LN>& lds, const
     auto iter = [&](int i, int par, auto uc, auto sc) __attribute__((always_inline)) {
       constexpr int u0 = decltype(uc)::value, u1 = (u0 + 2) % 3, u2 = (u0 + 1) % 3, st = decltype(sc)::value;
 #pragma unroll
-      for (int q = 0; q < NP; ++q) vs[u0][q] = decode<C>(lds.pop[st - 1][slot(q, u0, par)][l - qcx<QG>(q)]);
+      for (int q = 0; q < NP; ++q) vs[u0][q] = widen<C>(lds.pop[st - 1][slot(q, u0, par)][l - qcx<QG>(q)]);
       put(st, u0, vs[u0]);
       __syncthreads();
       C v[NP];
