@@ -1,10 +1,9 @@
 // C ABI of the filtered LB-MHD engine (lbmhd.h, lbmhd_learned.h): parameter
 // validation, rates, buffer binding, time/parity bookkeeping and error
-// reporting.  The per-cell arithmetic and all device work live in
-// lbmhd_kernels.hip and lbmhd_learned.hip.
+// reporting.  The per-cell arithmetic and all device work live in the .hip sources
+// beside it, the number of timesteps of each launch in lbmhd_plan.cpp.
 #include <hip/hip_runtime.h>
 
-#include <algorithm>
 #include <cmath>
 #include <cstdint>
 #include <cstdio>
@@ -147,6 +146,8 @@ lbm::Launch at_time(lbm_ctx* ctx, int64_t t) {
 
 }  // namespace
 
+bool lbm::launch_of(const lbm_params* p, Launch* L) { return check_params(p, L) == LBM_OK; }
+
 extern "C" {
 
 size_t lbm_state_bytes(const lbm_params* p) {
@@ -257,21 +258,11 @@ int lbm_step(lbm_ctx* ctx, int64_t n) {
   }
   if (n > 0) note_recording(ctx);
   const bool fused = ctx->L.schedule == LBM_SCHED_FUSED;
-  const int most = n > 1 ? (fused ? lbm::multi_steps(ctx->L) : lbm::multi_steps_inplace(ctx->L)) : 1;
-  // fused: as few sweeps as possible, of nearly equal numbers of steps; as many as steps
-  // in parity once a graph holds steps (4096^2 FP32 closure off, 10 steps: 4 sweeps for 3).
-  // In place: an even number of steps from even times.
-  int64_t sweeps = (n + most - 1) / most;
-  if (ctx->recorded) sweeps += (n - sweeps) & 1;
-  for (int64_t left = n; left > 0; --sweeps) {
-    int adv;
+  // once a graph holds steps, as many sweeps of the fused schedule as steps in parity
+  lbm::StepPlan plan(ctx->L, n, ctx->recorded);
+  for (int64_t left = n; left > 0;) {
+    const int adv = plan.next(left, ctx->t);
     hipError_t e;
-    if (fused) {
-      adv = int((left + sweeps - 1) / sweeps);
-    } else {
-      adv = ctx->t % 2 ? 1 : int(std::min<int64_t>(left, most));
-      if (adv > 1) adv &= ~1;
-    }
     if (adv > 1) {
       e = fused ? lbm::launch_steps(ctx->L, adv) : lbm::launch_steps_inplace(ctx->L, adv);
     } else {

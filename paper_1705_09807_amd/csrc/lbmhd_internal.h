@@ -61,13 +61,51 @@ size_t state_bytes(int nx, int ny, int dtype, int schedule, int qg);
 // Work layout for the given geometry; returns total bytes and fills offsets.
 size_t work_layout(Launch& L);
 
+// Shapes and steps of the fused schedule's sweeps (lbmhd_plan.cpp).
+constexpr int kMostSteps = 4;
+// Most steps per launch: what the LDS holds in groups of 256 columns (FP64 with the
+// closure: 128, whose registers allow no more).
+constexpr int ms_most_steps(size_t bytes, bool les, int qg) {
+  if (bytes == 8) return qg == 9 && !les ? 2 : 3;
+  return les || qg == 9 ? 3 : 4;
+}
+// Closure off: grids below this many cells load their rows three ahead (see launch_dns).
+constexpr int64_t dns_deep_cells(size_t bytes) { return bytes == 8 ? 400000 : (bytes == 4 ? 100000 : 300000); }
+// Columns per group, columns stored per strip, rows per segment, workgroups.
+struct MsShape {
+  int lanes, w, ry, blocks;
+};
+MsShape ms_shape(const Launch& L, int halo, int max_lanes, int per_cu_lds);
+bool streaming_stores(const Launch& L);
+int strip_width(int nx, bool fp32);
+int fused_rows(int nx, int ny, int strip, int cus, int cap);
+int les_rows(const Launch& L, int strip);
+
+// The launches of lbm_step(n): next(left, t) is how many steps the next one takes, with
+// `left` of the n steps left at time t.  keep_parity (fused schedule): as many launches as
+// steps in parity.
+class StepPlan {
+ public:
+  StepPlan(const Launch& L, int64_t n, bool keep_parity);
+  int next(int64_t left, int64_t t);
+
+ private:
+  static constexpr int kTail = 24;
+  bool fused = true, one = false;
+  int most = 1, best = 1, parity = 0;
+  int64_t leading = 0;
+  int8_t next_of[2][kTail + 1];
+};
+
+// Parameters checked and the rates and geometry filled (no buffers); false if invalid.
+bool launch_of(const lbm_params* p, Launch* L);
+
 // Launchers: enqueue on L.stream, return the first HIP error.
 hipError_t launch_init_kh(const Launch& L, const lbm_kh_params& kh);
 hipError_t launch_init_sech2(const Launch& L, const lbm_sech2_params& jet);
 hipError_t launch_init_moments(const Launch& L, int64_t t, const double* mom);
-// Fused schedule: the most timesteps one launch can advance (1: launch_step
-// only), and k > 1 steps in one launch, from buffer cur into the other one.
-int multi_steps(const Launch& L);
+// Fused schedule: k > 1 steps in one launch (at most ms_most_steps), from buffer cur
+// into the other one.
 hipError_t launch_steps(const Launch& L, int k);
 // In-place schedule: the most timesteps (1, 2 or 4) one sweep can advance from an even
 // time, and k = 2 or 4 steps in one.

@@ -1136,48 +1136,9 @@ static C* moment_set(const Launch& L, int k) {
   return reinterpret_cast<C*>(static_cast<char*>(L.work) + L.off_mb + (size_t)k * stride);
 }
 
-// Rows per workgroup of the fused closure kernel.  Measured on MI355X over
-// 1024^2 .. 16384^2 (512-lane FP32 strips): one workgroup per compute unit is
-// fastest (every strip segment runs concurrently from start to end, and the
-// two halo rows re-read per segment are amortised over many rows) as long as
-// a segment then holds at most 128 rows (FP32) or 64 rows (FP64); larger
-// grids run more, 64-row segments (4096^2: 440 us at 128 rows = one per
-// compute unit, 444 us at 64; 8192^2: 1764 us at 64 rows, 1781 us at 512).
-static int fused_rows(int nx, int ny, int strip, int cus, int cap) {
-  const int64_t strips = (nx + strip - 1) / strip;
-  const int64_t blocks = cus / strips > 1 ? cus / strips : 1;  // segments per strip column
-  int64_t ry = (ny + blocks - 1) / blocks;
-  if (ry > cap) ry = 64;
-  return (int)(ry < 1 ? 1 : ry);
-}
-
-// Strip width of the fused closure kernel and of the input vectors: 512 lanes for wide
-// grids with FP32 compute, 256 otherwise, 64 for narrow grids and where 256 would leave
-// more than 0.3 of their lanes idle (300 x 1000 FP32 11.2 against 13.7 us, 332 x 145 5.5
-// against 5.9; 400^2 8.5 against 8.8, 500^2 10.1 against 9.7).
-static int strip_width(int nx, bool fp32) {
-  if (fp32 && nx >= 1024) return 512;
-  return nx >= 256 && 10 * (int64_t)nx >= 7 * ((nx + 255) / 256 * 256) ? 256 : 64;
-}
-
-// Non-temporal stores pay off once the two population buffers no longer fit
-// in the 256 MB Infinity Cache; below that the next step re-reads them from it.
-static bool streaming_stores(const Launch& L) {
-  return 2.0 * double(9 + 2 * L.qg) * double(L.nx) * double(L.ny) * double(storage_bytes(L.dtype)) > 256.0e6;
-}
-
 template <typename S, typename C, int W, bool NT, int MODE, int QG, int STENCIL>
 static void launch_les_s(const Launch& L, const S* src, S* dst, const Rates<C>& r, const float* corr) {
-  // Segments sized for one workgroup per compute unit, two for k_fused_les_f
-  // beyond the Infinity Cache (two fit a compute unit; measured 4096^2 FP32
-  // 448 against 466 us, 8192^2 within 1 % either way, while the cache-resident
-  // 1024^2 sweep prefers one: 28.7 against 31.4 us).  64-lane strips, of two waves, march
-  // four to a compute unit (FP64 two where one would have six rows), so that each has fewer
-  // rows to wait for: 97 x 2675 FP16 26.0 -> 13.4 us, 200 x 1500 FP32 24.2 -> 12.3,
-  // 200^2 BF16 6.9 -> 5.1, 100 x 1000 FP64 12.2 -> 10.4 (180^2 FP64 6.9 against 7.2).
-  const bool two64 = (int64_t)L.ny * ((L.nx + W - 1) / W) >= 6 * (int64_t)L.cus;
-  const int per_cu = W == 64 ? (sizeof(C) == 4 ? 4 : (two64 ? 2 : 1)) : ((sizeof(C) == 4 && NT) ? 2 : 1);
-  const int ry = fused_rows(L.nx, L.ny, W, L.cus * per_cu, sizeof(C) == 4 ? 128 : 64);
+  const int ry = les_rows(L, W);
   const int strips = (L.nx + W - 1) / W, segs = (L.ny + ry - 1) / ry;
   // one-dimensional grid, numbered XCD-contiguously in the kernel
   hipLaunchKernelGGL((k_fused_les_f<S, W, STENCIL, NT, MODE, QG>), dim3(strips * segs), dim3(W + 64), 0, L.stream,

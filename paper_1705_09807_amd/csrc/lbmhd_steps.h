@@ -42,19 +42,6 @@
 
 namespace lbm {
 
-// Most steps per launch: what the LDS holds in groups of 256 columns (FP64 with the
-// closure: 128, whose registers allow no more).
-constexpr int ms_most_steps(size_t bytes, bool les, int qg) {
-  if (bytes == 8) return qg == 9 && !les ? 2 : 3;
-  return les || qg == 9 ? 3 : 4;
-}
-
-// Columns per group, columns stored per strip, rows per segment, workgroups.
-struct MsShape {
-  int lanes, w, ry, blocks;
-};
-MsShape ms_shape(const Launch& L, int halo, int max_lanes, int per_cu_lds);
-
 // Strip, segment and group of this thread (workgroups numbered XCD-contiguously: the
 // strips of a segment run side by side on one XCD and share the lines at their
 // edges in its L2).
@@ -404,6 +391,9 @@ static hipError_t launch_k_steps(const Launch& L) {
   using C = typename ComputeOf<S>::type;
   using Lds = std::conditional_t<MODE == kClosureOff, DnsLds<S, QG, K, LN>, LesLds<S, MODE, QG, K, LN>>;
   static_assert(sizeof(Lds) <= 160 * 1024, "LDS of a compute unit");
+  // as the time estimate of 16-bit sweeps assumes
+  static_assert(sizeof(S) > 2 || MODE == kClosureOff || (160 * 1024 / sizeof(Lds) > 1) == (MODE != kClosureFull || K < 3),
+                "workgroups per compute unit");
   const MsShape sh = ms_shape(L, MODE != kClosureOff ? 2 * K - 1 : K - 1, LN, 160 * 1024 / sizeof(Lds));
   const auto kernel = [] {
     if constexpr (MODE == kClosureOff)
@@ -459,8 +449,7 @@ static hipError_t launch_k(const Launch& L, int k) {
 // instead (64^2 FP32, three steps 6.0 us each either way).
 template <typename S, int QG>
 static hipError_t launch_dns(const Launch& L, int k) {
-  const int64_t deep = sizeof(S) == 8 ? 400000 : (sizeof(S) == 4 ? 100000 : 300000);
-  if (int64_t(L.nx) * L.ny < deep) return launch_k<S, kClosureOff, QG, sizeof(S) == 8 ? 64 : 128>(L, k);
+  if (int64_t(L.nx) * L.ny < dns_deep_cells(sizeof(S))) return launch_k<S, kClosureOff, QG, sizeof(S) == 8 ? 64 : 128>(L, k);
   return launch_k<S, kClosureOff, QG, 256>(L, k);
 }
 
