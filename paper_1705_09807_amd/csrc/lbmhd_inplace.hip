@@ -349,18 +349,33 @@ static bool inplace_plan(const Launch& L, int k, InplacePlan& p) {
 // Below these sizes the one-step sweeps stay: the state then lives in the caches, few
 // workgroups march and the copies are a launch of their own.  Measured, us per step,
 // several steps against one (closure off / synchronous / lagged gradients): FP32
-// 1024^2 20.0/38.9/27.9 against 24.3/40.9/29.7, 1448^2 26.3/51.1/44.5 against
-// 46.3/79.3/56.8, 4096^2 157/301/368 against 449/768/556; FP64 512^2 16.4/50.9/40.6
+// 850^2 16.3/29.5/23.0 against 17.6/30.5/21.9, 1000^2 18.2/33.5/28.0 against 23.2/39.7/28.5,
+// 1024^2 19.1/37.6/27.0 against 23.9/40.5/29.4, 1448^2 25.0/50.2/44.2 against
+// 46.0/78.2/56.4, 4096^2 157/301/368 against 449/768/556; FP64 512^2 16.4/50.9/40.6
 // against 12.8/23.0/16.7, 1024^2 32.0/52.6/43.7 against 45.7/78.6/57.1, 4096^2
-// 555/617/787 against 898/1527/1111; BF16 2048^2 47.1/80.7/69.2 against
-// 45.7/88.4/107.9, 4096^2 151/237/242 against 232/472/452.
-int multi_steps_inplace(const Launch& L) {
+// 555/617/787 against 898/1527/1111; 16-bit 2048^2 47.5/80.3/68.7 against 44.8/86.1/97.0
+// (BF16), 2900^2 82.0/136.9/124.2 against 113.9/252.5/204, 4096^2 154/241/240 against
+// 229/473/368.  Narrow strips, whose copied and recomputed columns are many to those
+// stored, stay too: FP32 64 x 24000 42.0/89.8/61.9 against 33.2/61.7/44.0, 128 x 9000
+// -/49.7/32.9 against -/45.0/31.8 (128 x 20000 41.2/89.5/72.9 against 55.0/93.7/91.9), FP64
+// 64 x 16000 48.7/75.0/60.0 against 44.2/77.0/54.0, BF16 synchronous 128 x 32768 117 against
+// 98 (200 x 32768 129 against 232).  Two steps with the closure off, where four would fit:
+// FP32 1024^2 21.5 against 23.9, 128 x 20000 61.6 against 55.0; 16-bit 2900^2 123 against 113
+// (FP16), 4096^2 236 against 229 (BF16).
+InplaceSteps multi_steps_inplace(const Launch& L) {
   InplacePlan p;
   const int64_t cells = int64_t(L.nx) * L.ny;
   const size_t bytes = storage_bytes(L.dtype);
-  const int64_t least = bytes == 8 ? 1000000 : (bytes == 4 ? 1500000 : (L.k2 == 0.0 ? 8000000 : 4000000));
-  if (cells < least || L.nx < 16 || L.ny < 16 || !inplace_plan(L, 2, p)) return 1;
-  return L.k2 == 0.0 && L.dtype != LBM_FP64 && inplace_plan(L, 4, p) ? 4 : 2;
+  const bool les = L.k2 != 0.0;
+  const int64_t least = bytes >= 4 ? 1000000 : (les ? 4000000 : 8000000);
+  if (cells < least || L.nx < 16 || L.ny < 16 || !inplace_plan(L, 2, p)) return {1, 1};
+  const bool wide = p.e.w >= 160;
+  if (bytes == 4 && cells < 1500000 && !wide) return {1, 1};
+  if (bytes == 2 && les && L.schedule == LBM_SCHED_AA && !wide) return {1, 1};
+  if (p.e.w < 80) return {1, 1};
+  if (les || bytes == 8) return {2, 2};
+  const int most = inplace_plan(L, 4, p) ? 4 : 2;
+  return {bytes == 4 && wide ? 2 : most, most};
 }
 
 template <typename S, bool LAGGED, int K, int LN, typename Kernel>

@@ -92,7 +92,7 @@ class StepPlan {
  private:
   static constexpr int kTail = 24;
   bool fused = true, one = false;
-  int most = 1, best = 1, parity = 0;
+  int least_steps = 1, most = 1, best = 1, parity = 0;
   int64_t leading = 0;
   int8_t next_of[2][kTail + 1];
 };
@@ -107,9 +107,12 @@ hipError_t launch_init_moments(const Launch& L, int64_t t, const double* mom);
 // Fused schedule: k > 1 steps in one launch (at most ms_most_steps), from buffer cur
 // into the other one.
 hipError_t launch_steps(const Launch& L, int k);
-// In-place schedule: the most timesteps (1, 2 or 4) one sweep can advance from an even
-// time, and k = 2 or 4 steps in one.
-int multi_steps_inplace(const Launch& L);
+// In-place schedule: the fewest and the most timesteps (2 or 4; both 1: none) of a sweep of
+// several from an even time, and k = 2 or 4 steps in one.
+struct InplaceSteps {
+  int least, most;
+};
+InplaceSteps multi_steps_inplace(const Launch& L);
 hipError_t launch_steps_inplace(const Launch& L, int k);
 // State at time t -> t + 1 (fused schedule: from buffer cur into the other
 // one); with the learned closure, corr_refresh = false

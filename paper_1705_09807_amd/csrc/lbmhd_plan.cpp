@@ -214,7 +214,9 @@ StepPlan::StepPlan(const Launch& L, int64_t n, bool keep_parity) {
     return;
   }
   if (!fused) {
-    most = multi_steps_inplace(L);
+    const InplaceSteps s = multi_steps_inplace(L);
+    least_steps = s.least;
+    most = s.most;
     one = most == 1;
     return;
   }
@@ -257,8 +259,8 @@ int StepPlan::next(int64_t left, int64_t t) {
   if (one) return 1;
   if (!fused) {
     // an even number of steps from even times
-    const int k = t % 2 ? 1 : int(std::min<int64_t>(left, most));
-    return k > 1 ? k & ~1 : 1;
+    const int k = t % 2 ? 1 : int(std::min<int64_t>(left, most)) & ~1;
+    return k >= least_steps ? k : 1;
   }
   if (leading > 0) {
     --leading;

@@ -26,6 +26,10 @@ CASES += [(1203, 1201, 6, 3, dict(dtype="fp16", delta=3.0, closure="full")),
           (701, 703, 4, 2, dict(dtype="bf16", delta=3.0, closure="full", grad_stencil="central5"))]
 CASES += [(66, 6001, 5, 3, dict(dtype="fp32", delta=4.0)), (40, 9001, 3, 3, dict(dtype="fp32", delta=3.0, mag_lattice="d2q9")),
           (32768, 20, 4, 2, dict(dtype="fp64", delta=4.0))]
+CASES += [(1003, 1000, 6, 4, dict(dtype="fp32", delta=0.0, schedule="aa")),
+          (1024, 1000, 2, 2, dict(dtype="fp32", delta=0.0, schedule="aa")),
+          (1003, 1000, 5, 2, dict(dtype="fp32", delta=4.0, schedule="aa")),
+          (1003, 1000, 5, 2, dict(dtype="fp32", delta=4.0, schedule="aa_lagged"))]
 
 
 @pytest.mark.parametrize("nx,ny,n,k,kw", CASES)

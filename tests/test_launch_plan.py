@@ -38,6 +38,20 @@ def test_in_place(schedule, delta, dtype):
             assert launch_plan(200, 200, n, t=t, dtype=dtype, schedule=schedule, delta=delta) == [1] * n
 
 
+@pytest.mark.parametrize("dtype,schedule,delta,nx,ny,n,want", [
+    # as measured on both sides: FP32 from 10^6 cells, not on strips of few columns
+    ("fp32", "aa", 0.0, 1024, 1024, 4, [4]), ("fp32", "aa", 0.0, 1024, 1024, 6, [4, 2]),
+    ("fp32", "aa", 2.0, 1024, 1024, 4, [2, 2]), ("fp32", "aa_lagged", 2.0, 5000, 201, 4, [2, 2]),
+    ("fp32", "aa", 2.0, 990, 1000, 2, [1, 1]), ("fp32", "aa_lagged", 2.0, 64, 24000, 2, [1, 1]),
+    ("fp32", "aa", 2.0, 128, 9000, 2, [1, 1]), ("fp32", "aa", 2.0, 128, 20000, 2, [2]),
+    ("fp32", "aa", 0.0, 128, 20000, 6, [4, 1, 1]), ("fp64", "aa", 0.0, 64, 24000, 2, [1, 1]),
+    # two steps of 16-bit storage with the closure off are slower than one and one
+    ("bf16", "aa", 0.0, 4096, 4096, 6, [4, 1, 1]), ("fp16", "aa", 0.0, 4096, 4096, 2, [1, 1]),
+    ("bf16", "aa", 2.0, 128, 32768, 2, [1, 1]), ("bf16", "aa_lagged", 2.0, 128, 32768, 2, [2])])
+def test_in_place_sizes(dtype, schedule, delta, nx, ny, n, want):
+    assert launch_plan(nx, ny, n, dtype=dtype, schedule=schedule, delta=delta) == want
+
+
 @pytest.mark.parametrize("dtype", ["fp16", "bf16"])
 def test_grids_alike_take_alike_launches(dtype):
     """Closure off, about 2^20 cells: no shape keeps to one step."""
