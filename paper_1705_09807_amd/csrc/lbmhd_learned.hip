@@ -24,6 +24,7 @@
 #include <stdint.h>
 
 #include <mutex>
+#include <type_traits>
 
 #include "lbmhd_device.h"
 #include "lbmhd_internal.h"
@@ -870,7 +871,10 @@ k_filter_x(const double* __restrict__ mom, int nx, int ny, int R, int rows, cons
   const int tid = threadIdx.x, lane = tid & 63;
   const int k0 = 3 * __builtin_amdgcn_readfirstlane(tid >> 6);
   const int cx = nx / FACTOR;
-  const int X0 = blockIdx.x * 64 * B, count = 64 * P + 2 * R;
+  const int X0 = blockIdx.x * 64 * B;
+  // fine cells of the segment's outputs: few on narrow grids and at a ragged end (lanes past
+  // the last output read cells that are not there; their sums are dropped)
+  const int count = min(64 * P, (cx - X0) * FACTOR) + 2 * R;
   const int y0 = blockIdx.y * rows, y1 = min(y0 + rows, ny);
   const int64_t n = (int64_t)nx * ny, cn = (int64_t)cx * ny;
   const double* v = prod + k0 * P * NI + lane;
@@ -884,9 +888,11 @@ k_filter_x(const double* __restrict__ mom, int nx, int ny, int R, int rows, cons
   auto load = [&](int y) __attribute__((always_inline)) {
     const double* row = mom + (int64_t)y * nx;
 #pragma unroll
-    for (int i = 0; i < NE; ++i)
+    for (int i = 0; i < NE; ++i) {
+      if (256 * i >= count) break;  // uniform
 #pragma unroll
       for (int k = 0; k < 5; ++k) f[i][k] = row[k * n + xs[i]];
+    }
   };
   load(y0);
   for (int y = y0; y < y1; ++y) {
@@ -910,22 +916,23 @@ k_filter_x(const double* __restrict__ mom, int nx, int ny, int R, int rows, cons
   }
 }
 
-// y pass: a lane computes kFilterYB outputs of one column, so a row it reads
-// serves several of them.  Measured 4096^2 by 4, R = 24: 503 us with one output
-// per thread, 202 us.
-constexpr int kFilterYB = 4;
+// y pass: a lane computes B outputs of one column, so a row it reads serves several of them,
+// where that leaves enough waves to hide the loads' latency (filter_y_outputs).  Measured
+// 4096^2 by 4, R = 24: 503 us with one output per thread, 202 us with four.
+template <int B>
 __global__ void __launch_bounds__(64)
 k_filter_y(const double* __restrict__ tmp, int nx, int ny, int factor, int R, const double* __restrict__ taps,
            double* __restrict__ out) {
+  constexpr int U = B == 1 ? 8 : 4;  // rows in flight
   const int cx = nx / factor, cy = ny / factor;
-  const int X = blockIdx.x * 64 + threadIdx.x, Y = blockIdx.y * kFilterYB, k = blockIdx.z;
+  const int X = blockIdx.x * 64 + threadIdx.x, Y = blockIdx.y * B, k = blockIdx.z;
   if (X >= cx) return;
   const int64_t cn = (int64_t)cx * ny;
   const double* col = tmp + k * cn + X;
-  double acc[kFilterYB];
+  double acc[B];
 #pragma unroll
-  for (int b = 0; b < kFilterYB; ++b) acc[b] = 0.0;
-  const int end = 2 * R + (kFilterYB - 1) * factor;
+  for (int b = 0; b < B; ++b) acc[b] = 0.0;
+  const int end = 2 * R + (B - 1) * factor;
   int yy = (Y * factor - R) % ny;
   if (yy < 0) yy += ny;
   auto next = [&]() __attribute__((always_inline)) {
@@ -936,25 +943,25 @@ k_filter_y(const double* __restrict__ tmp, int nx, int ny, int factor, int R, co
   auto some = [&](int t) __attribute__((always_inline)) {
     const double a = next();
 #pragma unroll
-    for (int b = 0; b < kFilterYB; ++b) {
+    for (int b = 0; b < B; ++b) {
       const int r = t - b * factor;
       if (r >= 0 && r <= 2 * R) acc[b] += taps[r] * a;  // uniform
     }
   };
   int t = 0;
-  for (; t < (kFilterYB - 1) * factor && t <= end; ++t) some(t);
-  for (; t + 3 <= 2 * R; t += 4) {  // every tap exists
-    double a[4];
+  for (; t < (B - 1) * factor && t <= end; ++t) some(t);
+  for (; t + U - 1 <= 2 * R; t += U) {  // every tap exists
+    double a[U];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) a[j] = next();
+    for (int j = 0; j < U; ++j) a[j] = next();
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
+    for (int j = 0; j < U; ++j)
 #pragma unroll
-      for (int b = 0; b < kFilterYB; ++b) acc[b] += taps[t + j - b * factor] * a[j];
+      for (int b = 0; b < B; ++b) acc[b] += taps[t + j - b * factor] * a[j];
   }
   for (; t <= end; ++t) some(t);
 #pragma unroll
-  for (int b = 0; b < kFilterYB; ++b)
+  for (int b = 0; b < B; ++b)
     if (Y + b < cy) out[(int64_t)k * cx * cy + (int64_t)(Y + b) * cx + X] = acc[b];
 }
 
@@ -1224,6 +1231,16 @@ static hipError_t launch_filter_x(const double* mom, int nx, int ny, int R, cons
   return hipGetLastError();
 }
 
+// Outputs per lane of the y pass: fewer where its waves are too few to hide a lane's chain
+// of loads.  Measured, the whole filter with one, two and four: 256^2 by 4 (768 waves of
+// one output) 32.0, 32.6 and 37.6 us, 256^2 by 16 45, 59 and 82, 1024^2 by 8 (3072) 47.5, 49.4 and
+// 60.2, 1536^2 by 8 (6912) 66.6, 65.6 and 74.7, 1536^2 by 4 (27648) 122, 125 and 109 with R = 24
+// and 85.8, 77.8 and 80.0 with R = 6, 4096^2 by 2 1067, 842 and 777.
+static int filter_y_outputs(int cx, int cy) {
+  const int64_t waves = (int64_t)12 * ((cx + 63) / 64) * cy;  // of one output per lane
+  return waves >= 12288 ? 4 : (waves >= 6144 ? 2 : 1);
+}
+
 hipError_t launch_filter(const double* mom, int nx, int ny, int factor, double delta, double* out, void* work,
                          hipStream_t st) {
   const int R = filter_radius(delta);
@@ -1241,9 +1258,17 @@ hipError_t launch_filter(const double* mom, int nx, int ny, int factor, double d
     default: e = launch_filter_x<16, false>(mom, nx, ny, R, taps, tmp, st);
   }
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_filter_y, dim3((cx + 63) / 64, (cy + kFilterYB - 1) / kFilterYB, 12), dim3(64), 0, st, tmp, nx,
-                     ny, factor, R, taps, out);
-  return hipGetLastError();
+  const auto y_pass = [&](auto b) {
+    constexpr int B = decltype(b)::value;
+    hipLaunchKernelGGL(k_filter_y<B>, dim3((cx + 63) / 64, (cy + B - 1) / B, 12), dim3(64), 0, st, tmp, nx, ny, factor,
+                       R, taps, out);
+    return hipGetLastError();
+  };
+  switch (filter_y_outputs(cx, cy)) {
+    case 1: return y_pass(std::integral_constant<int, 1>{});
+    case 2: return y_pass(std::integral_constant<int, 2>{});
+    default: return y_pass(std::integral_constant<int, 4>{});
+  }
 }
 
 hipError_t launch_closure_samples(const double* c12, int nx, int ny, double delta, int stencil, float* x, float* t,
