@@ -37,7 +37,7 @@ struct Launch {
   size_t off_mb = 0;              // moment planes for the in-place closure sweep
                                   // (two sets for the lagged schedule, set t & 1
                                   // holding the moments of step t - 1)
-  size_t off_edges = 0;           // room of 5 FP64 planes: copied cells of the in-place sweeps of several steps
+  size_t off_edges = 0;           // in place: room of 5 FP64 planes, copied cells of the sweeps of several steps
   size_t off_part = 0;            // per-block reduction partials
   size_t off_final = 0;           // final reduction values
   int diag_blocks = 0;

@@ -1076,7 +1076,7 @@ size_t work_layout(Launch& L) {
   if (L.schedule == LBM_SCHED_AA) off += align256(4 * n * cbytes);
   if (L.schedule == LBM_SCHED_AA_LAGGED) off += 2 * align256(4 * n * cbytes);
   L.off_edges = off;
-  off += align256(5 * n * sizeof(double));
+  if (L.schedule != LBM_SCHED_FUSED) off += align256(5 * n * sizeof(double));
   const int64_t want = ((int64_t)n + 255) / 256;
   L.diag_blocks = (int)(want < kDiagBlocksMax ? (want < 1 ? 1 : want) : kDiagBlocksMax);
   L.off_part = off;
