@@ -128,8 +128,9 @@ static double les16_time(const Launch& L, int k) {
   }
   // one strip of at most 192 lanes
   if (s.lanes > 128 && s.lanes <= 192 && s.w == L.nx) row *= 0.88;
-  // two workgroups on a compute unit against one
-  const double share = s.blocks > L.cus ? (k == 2 ? 1.7 : 1.94) : 1.0;
+  // two workgroups on a compute unit against one (8192^2 BF16 three steps 1780 us; two 1415,
+  // FP16 1590)
+  const double share = s.blocks > L.cus ? (k == 2 ? 1.85 : 1.94) : 1.0;
   return base + row * share * rows;
 }
 
