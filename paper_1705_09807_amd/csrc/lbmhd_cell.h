@@ -138,8 +138,11 @@ static Rates<C> make_rates(const Launch& L) {
 // Per-cell arithmetic of the method.  The expressions are evaluated as
 // written: contraction is off and every fused multiply-add is spelled out, so
 // a cell's result does not depend on the kernel, or on the copy of an unrolled
-// body, that evaluates it.  Sweeps of one and of several steps, and the
-// schedules, can then be mixed freely with the same bits.
+// body, that evaluates it.  Sweeps of one and of several steps can then be mixed freely
+// with the same bits, and the schedules give the same; one exception: 16-bit storage with
+// the closure off and a width of whole quads, where the two-buffer schedule sums the rest
+// population of one column in four in another order than the in-place one (swapped_rest),
+// so that these states differ in last bits and are not the same shifted along x.
 // ---------------------------------------------------------------------------
 template <typename C>
 struct Mom {
@@ -275,11 +278,12 @@ __device__ __forceinline__ void collide19(C v[kQ], const Mom<C>& m, const Closur
   collide_q<5, LES, LOCAL, U>(v, m, cl, r, swapped);
 }
 
-// 16-bit storage, closure off, nx a multiple of 4: one column in four rounds its rest
-// population from the two products in the other order (FP16 the third, BF16 the
-// second), as the sweep of four columns a thread always has.  A difference in the last
-// bit of FP32 would now and then become one of a stored 16-bit value, so the sweeps
-// keep it: runs and saved states continue with the same bits.
+// 16-bit storage, closure off, nx a multiple of 4, two-buffer schedule: one column in four
+// rounds its rest population from the two products in the other order (FP16 the third, BF16
+// the second), as the sweep of four columns a thread always has.  A difference in the last
+// bit of FP32 would now and then become one of a stored 16-bit value, so every sweep of
+// that schedule keeps it: runs and saved states continue with the same bits.  In sweeps of
+// several steps it costs a multiply-add and a select per cell and step.
 template <typename S>
 __device__ __forceinline__ bool swapped_rest(int x, int nx) {
   if constexpr (sizeof(S) == 2) return (nx & 3) == 0 && (x & 3) == (std::is_same_v<S, __bf16> ? 1 : 2);

@@ -27,7 +27,8 @@
 //
 // All arithmetic that defines the method (moments, closure, collision) lives
 // in the __device__ functions of lbmhd_cell.h and lbmhd_device.h and is shared
-// by every kernel, so all schedules compute identical values.
+// by every kernel, so all schedules with the same gradients compute identical values
+// (but for the last bits of 16-bit runs without closure: swapped_rest).
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
