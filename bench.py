@@ -41,9 +41,10 @@ NU = ETA = 2e-4
 GHOST = 1.6
 LES_N, LES_DELTA = 1024, 4.0
 DNS_N = 4096
-# sources of the kernels that the counter summaries in profiles/ were taken on
+# sources of the kernels, and of their launch shapes, that the counter summaries in profiles/
+# were taken on; a summary's hash is written by the run that takes its counters
 KERNEL_SRC = [os.path.join(ROOT, "paper_1705_09807_amd", "csrc", f)
-              for f in ("lbmhd_steps.h", "lbmhd_steps_16bit.hip", "lbmhd_cell.h", "lbmhd_device.h")]
+              for f in ("lbmhd_steps.h", "lbmhd_shape.cpp", "lbmhd_cell.h", "lbmhd_device.h")]
 # Most timesteps per launch of the fused schedule on the large grids here (the
 # library's ms_most_steps), by closure off / on; the learned closure takes one.
 STEPS_PER_LAUNCH = {False: 4, True: 3}

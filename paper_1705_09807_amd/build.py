@@ -20,7 +20,8 @@ INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(PKG, "liblbmhd.so")
 
 SOURCES = ["lbmhd_kernels.hip", "lbmhd_steps_fp64.hip", "lbmhd_steps_fp32.hip", "lbmhd_steps_16bit.hip", "lbmhd_inplace.hip",
-           "lbmhd_learned.hip", "lbmhd_spectra.hip", "lbmhd_plan.cpp", "lbmhd_api.cpp"]
+           "lbmhd_learned.hip", "lbmhd_spectra.hip", "lbmhd_shape.cpp", "lbmhd_plan.cpp",
+           "lbmhd_api.cpp"]
 
 # Packed FP32 instructions are disabled for all device code; the host pass
 # warns that it does not know the feature, which is harmless.

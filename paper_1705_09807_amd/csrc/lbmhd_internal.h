@@ -1,5 +1,5 @@
-// Internal interface between the C ABI (lbmhd_api.cpp) and the kernel
-// launchers (lbmhd_kernels.hip).  Not installed, not part of the ABI.
+// Internal interface between the C ABI (lbmhd_api.cpp), the host code that shapes and
+// plans the launches and the kernel launchers (.hip).  Not installed, not part of the ABI.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -61,7 +61,7 @@ size_t state_bytes(int nx, int ny, int dtype, int schedule, int qg);
 // Work layout for the given geometry; returns total bytes and fills offsets.
 size_t work_layout(Launch& L);
 
-// Shapes and steps of the fused schedule's sweeps (lbmhd_plan.cpp).
+// Shapes of the fused schedule's sweeps (lbmhd_shape.cpp).
 constexpr int kMostSteps = 4;
 // Most steps per launch: what the LDS holds in groups of 256 columns (FP64 with the
 // closure: 128, whose registers allow no more).
@@ -81,7 +81,7 @@ int strip_width(int nx, bool fp32);
 int fused_rows(int nx, int ny, int strip, int cus, int cap);
 int les_rows(const Launch& L, int strip);
 
-// The launches of lbm_step(n): next(left, t) is how many steps the next one takes, with
+// The launches of lbm_step(n) (lbmhd_plan.cpp): next(left, t) is how many steps the next one takes, with
 // `left` of the n steps left at time t.  keep_parity (fused schedule): as many launches as
 // steps in parity.
 class StepPlan {
