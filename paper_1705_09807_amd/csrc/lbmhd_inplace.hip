@@ -14,8 +14,9 @@
 // block, and writes slots of cells at most one outside it (the last step's
 // streaming): no slot is read by one workgroup and written by another.  Within a
 // workgroup a row is stored two or more iterations after the rows it touches were
-// read, behind a barrier.  The copies take the place of the diagnostics' moment
-// planes in the work buffer.
+// read, behind a barrier.  The copies lie in the work buffer, in the room of five
+// FP64 planes that an in-place context has for them (one-step sweeps run where that
+// is too little).
 //
 // The results equal those of one-step sweeps bit for bit.
 #include <algorithm>

@@ -81,9 +81,9 @@ int strip_width(int nx, bool fp32);
 int fused_rows(int nx, int ny, int strip, int cus, int cap);
 int les_rows(const Launch& L, int strip);
 
-// The launches of lbm_step(n) (lbmhd_plan.cpp): next(left, t) is how many steps the next one takes, with
-// `left` of the n steps left at time t.  keep_parity (fused schedule): as many launches as
-// steps in parity.
+// The launches of lbm_step(n) (lbmhd_plan.cpp): next(left, t) is how many steps the next
+// one takes, with `left` of the n steps left at time t.  keep_parity (fused schedule): as
+// many launches as steps in parity.
 class StepPlan {
  public:
   StepPlan(const Launch& L, int64_t n, bool keep_parity);

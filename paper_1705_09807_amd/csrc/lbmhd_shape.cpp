@@ -5,20 +5,21 @@
 
 namespace lbm {
 
-// Measured on MI355X, 256^2 .. 8192^2, microseconds per step:
+// Measured on MI355X, 256^2 .. 8192^2, microseconds per step over long runs:
 //  * groups of 256 columns, of 128 with the closure off on small grids, where
-//    more and narrower strips fill the chip (512^2 FP32 5.4 against 7.2, 2048^2 36.8
-//    against 34.1);
+//    more and narrower strips fill the chip (FP32 512^2 4.1 against 5.1, 700^2 5.4 against
+//    6.2; 2048^2 39.8 against 33.0, though 1024^2 8.5 against 9.7);
 //  * one workgroup per compute unit: few, tall segments keep few rows of the
-//    state open and recompute least (4096^2 FP32 closure on 175 against 180 with
-//    two, 2048^2 51 against 59); two for 16-bit storage on tall segments, where
-//    the arithmetic of two hides each other's barriers (8192^2 BF16 588 against
-//    620, 4096^2 161 against 157);
+//    state open and recompute least (FP32 closure on 4096^2 170.5 against 178.1 with
+//    two, 2048^2 49.8 against 56.8, 1024^2 17.4 against 25.0); two for 16-bit storage on
+//    tall segments, where the arithmetic of two hides each other's barriers (BF16 8192^2
+//    597 against 630, on the shorter segments of 4096^2 161.6 against 154.1);
 //  * on large grids strips of whole 64-byte sectors where that takes at most 1/32
-//    more strips (8192^2 FP32 closure off 503 against 544, on 665 against 708),
-//    with D2Q9, whose rows are longest, whole 128-byte lines for at most 1/8 more
-//    (4096^2 closure off 240 against 318, on 249 against 299); 16-bit storage is
-//    bound by its arithmetic and takes the fewest strips.
+//    more strips (FP32 closure on 16384 x 4096 860 against 892, 8192^2 690 against 693,
+//    off 3100 x 4096 95.4 against 101.4; most widths within 1 %), with D2Q9, whose
+//    rows are longest, whole 128-byte lines for at most 1/8 more (4096^2 closure off
+//    248 against 318, on 247 against 301); 16-bit storage is bound by its arithmetic and
+//    takes the fewest strips.
 MsShape ms_shape(const Launch& L, int halo, int max_lanes, int per_cu_lds) {
   const int64_t cells = int64_t(L.nx) * L.ny;
   const int bytes = int(storage_bytes(L.dtype));

@@ -18,14 +18,16 @@
 // would, and the arithmetic is the shared per-cell code, evaluated as written:
 // the results equal those of one-step sweeps bit for bit.
 //
-// Measured, us per step, one-step sweep -> K steps per launch: 4096^2 FP32
-// closure off 411 -> 130 (K = 4), on 442 -> 173 (K = 3); 8192^2 BF16 855 -> 370
-// and 940 -> 597; 4096^2 FP64 955 -> 343 and 873 -> 350; 1024^2 FP32 25.7 -> 10.3
-// and 27.7 -> 17.8; 4096^2 D2Q9 FP32 590 -> 253 and 627 -> 249; 1500 x 1001 D2Q9
-// FP64 with density gradients 163 -> 52.  What bounds it now:
-// at 4096^2 FP32 a launch moves its 2.55 GB at 4.6-4.9 TB/s with the closure and
+// Measured, us per step over long runs (the first thirty launches or so of the sweeps
+// that the arithmetic bounds are slower: 1024^2 FP32 closure on 77 us, then 52-57), one-step
+// sweep -> K steps per launch: 4096^2 FP32 closure off 410 -> 131 (K = 4), on
+// 445 -> 170 (K = 3); 8192^2 BF16 844 -> 379 and 951 -> 597, FP16 854 -> 377 and
+// 960 -> 647; 4096^2 FP64 953 -> 344 and 851 -> 344; 1024^2 FP32 25.2 -> 9.7 and
+// 27.3 -> 17.4; 4096^2 D2Q9 FP32 589 -> 250 and 624 -> 249; 1500 x 1001 D2Q9
+// FP64 with density gradients 128 -> 51.  What bounds it now:
+// at 4096^2 FP32 a launch moves its 2.55 GB at 4.9-5.0 TB/s with the closure and
 // the vector ALUs busy about half the time; 16-bit storage is bound by the vector
-// ALUs (8192^2 BF16: about 230 instructions a cell and step, 410 of the 588 us).
+// ALUs (8192^2 BF16: about 230 instructions a cell and step, 410 of the 597 us).
 // The same steps evaluated one after another by one group of waves (each lane
 // every step of its column) took 252 us at K = 2 and 224 at K = 3 (4096^2 FP32,
 // closure on): a wave's arithmetic, its LDS and its loads then wait on each other.

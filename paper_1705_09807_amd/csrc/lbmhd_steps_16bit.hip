@@ -1,5 +1,5 @@
-// Multi-step sweeps (lbmhd_steps.h) for FP16 and BF16 storage, and their
-// dispatch.
+// Multi-step sweeps (lbmhd_steps.h) for FP16 and BF16 storage, and the dispatch on the
+// storage type.
 #include "lbmhd_steps.h"
 
 namespace lbm {
